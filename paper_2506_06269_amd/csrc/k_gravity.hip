@@ -26,69 +26,7 @@
 
 namespace sidm {
 
-// ---------------------------------------------------------------- masses, tiles
-// Smallest and largest mass per streaming block, then per halo: cmass[h] is
-// the common mass when all masses of the halo are equal (else 0), and
-// cmass[n_halos + h] the largest mass.  With a
-// status array, a halo that scatters (sigma_m > 0) without a common mass is
-// flagged: the probability of a pair takes the mass of one member, which is
-// only symmetric when the masses are equal (each run of the paper's Table 1
-// has one particle mass), so such a halo is not scattered.
-__global__ __launch_bounds__(kStreamBlock) void k_block_mass_range(
-    const double* __restrict__ m, const StreamBlock* __restrict__ blocks, double* __restrict__ bsum)
-{
-    __shared__ double lo[kStreamBlock], hi[kStreamBlock];
-    const StreamBlock B = blocks[blockIdx.x];
-    const int t = threadIdx.x;
-    const double mi = m[B.start + (t < B.count ? t : 0)];
-    lo[t] = mi;
-    hi[t] = mi;
-    __syncthreads();
-    for (int s = kStreamBlock / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            lo[t] = fmin(lo[t], lo[t + s]);
-            hi[t] = fmax(hi[t], hi[t + s]);
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        bsum[7 * (int64_t)blockIdx.x + 0] = lo[0];
-        bsum[7 * (int64_t)blockIdx.x + 1] = hi[0];
-    }
-}
-
-__global__ __launch_bounds__(kStreamBlock) void k_halo_mass(
-    const HaloDev* __restrict__ halos, const double* __restrict__ bsum, double* __restrict__ cmass,
-    int* __restrict__ status)
-{
-    __shared__ double lo[kStreamBlock], hi[kStreamBlock];
-    const HaloDev& H = halos[blockIdx.x];
-    const int t = threadIdx.x;
-    const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
-    double l = INFINITY, u = -INFINITY;
-    for (int64_t b = t; b < nb; b += kStreamBlock) {
-        l = fmin(l, bsum[7 * (H.stream_block0 + b) + 0]);
-        u = fmax(u, bsum[7 * (H.stream_block0 + b) + 1]);
-    }
-    lo[t] = l;
-    hi[t] = u;
-    __syncthreads();
-    for (int s = kStreamBlock / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            lo[t] = fmin(lo[t], lo[t + s]);
-            hi[t] = fmax(hi[t], hi[t + s]);
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        const bool equal = lo[0] == hi[0];
-        cmass[blockIdx.x] = equal ? lo[0] : 0.0;
-        cmass[gridDim.x + blockIdx.x] = hi[0];   // the largest mass
-        if (status && !equal && H.sigma_m > 0.0)
-            atomicOr(&status[blockIdx.x], SIDM_DEV_UNEQUAL_MASS);
-    }
-}
-
+// ---------------------------------------------------------------- frames
 // Frame of a sorted position: the compact sub-range of its bucket that holds
 // it; its centre is the midpoint of the sub-range's box.
 __device__ inline void frame_of(const HaloDev& H, const SubRange* __restrict__ sub,
@@ -999,19 +937,8 @@ __global__ void k_ticket_reset(DevCounters* __restrict__ c)
     if (threadIdx.x == 0) c->ticket = 0ull;
 }
 
-// The common mass of each halo (w.cref) and the unequal-mass flag of the
-// halos that scatter (w.status).
-hipError_t launch_mass_check(const Plan& P, Scratch& w, const double* m, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_block_mass_range, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0, st,
-                       m, w.blocks, w.bsum);
-    hipLaunchKernelGGL(k_halo_mass, dim3(P.n_halos), dim3(kStreamBlock), 0, st, w.halos, w.bsum,
-                       w.cref, w.status);
-    return hipGetLastError();
-}
-
 // Expects the cell list of the current positions (sorted copies sx, sy, sz, sm
-// and perm) to be in place.  tick > 0: tick of a cycle of 2^bmax block steps
+// and perm, the common masses cref) to be in place.  tick > 0: tick of a cycle of 2^bmax block steps
 // (bins in w.bin).
 hipError_t launch_tree_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_state* s,
                                int tick, int bmax, hipStream_t st);
@@ -1021,10 +948,6 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
                           int bmax)
 {
     const unsigned nb = (unsigned)P.n_blocks;
-    hipLaunchKernelGGL(k_block_mass_range, dim3(nb), dim3(kStreamBlock), 0, st, s->m, w.blocks,
-                       w.bsum);
-    hipLaunchKernelGGL(k_halo_mass, dim3(P.n_halos), dim3(kStreamBlock), 0, st, w.halos, w.bsum,
-                       w.cref, (int*)nullptr);
     if (P.has_tree) {
         // tree halos: one partial row per particle from the walk
         if (tile_begin) (void)hipEventRecord(tile_begin, st);

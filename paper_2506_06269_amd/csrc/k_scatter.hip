@@ -575,17 +575,12 @@ hipError_t launch_reset(const Plan& P, Scratch& w, hipStream_t st)
     return hipGetLastError();
 }
 
-int launch_sort_keys(Scratch& w, int64_t n, int key_bits, hipStream_t st);
-hipError_t launch_mass_check(const Plan& P, Scratch& w, const double* m, hipStream_t st);
-
-// The scattering pass's checks of its contract: a common mass in every halo
-// that scatters, and ids unique within each halo (the id check reuses the
-// cell list's sort buffers, which hold nothing the later passes read).
-hipError_t launch_contract_checks(const Plan& P, const sidm_state* s, Scratch& w, hipStream_t st)
+// The scattering pass's check that ids are unique within each halo (it reuses
+// the cell list's sort buffers, which hold nothing the later passes read; that
+// a halo that scatters has one common mass is checked with the cell list).
+hipError_t launch_id_check(const Plan& P, const sidm_state* s, Scratch& w, hipStream_t st)
 {
     if (!P.any_scatter) return hipSuccess;
-    hipError_t e = launch_mass_check(P, w, s->m, st);
-    if (e != hipSuccess) return e;
     // the hash table: the radix sort's two key buffers, 2 max_particles words
     const unsigned long long cap = 2ull * (unsigned long long)w.max_particles;
     if ((int64_t)cap < 2 * P.n_sorted) return hipErrorInvalidValue;
@@ -635,7 +630,7 @@ hipError_t launch_scatter(const Plan& P, const sidm_state* s, Scratch& w, uint32
                           sidm_event* out_events, int64_t out_cap, hipStream_t st,
                           hipEvent_t after_pairs)
 {
-    hipError_t e = launch_contract_checks(P, s, w, st);
+    hipError_t e = launch_id_check(P, s, w, st);
     if (e != hipSuccess) return e;
     const int split = search_split(P.n_buckets, kPairSplitMax);
     auto pairs = [&](auto kern) {

@@ -3,63 +3,139 @@
 // bounding box, halo rank in the high bits) by a stable LSD radix sort, cut
 // into buckets of kBucket consecutive particles, and the bucket bounding boxes
 // are merged kFanout at a time into a search tree per halo.
+//
+// A launch that only waits for the previous one costs 3 to 5 us, whatever it
+// does, so up to a few 10^5 particles the list is bound by its number of
+// launches: calls whose halos all have at most kSmallN particles sort each
+// halo in one workgroup's LDS (k_cell_small), larger ones take one launch per
+// radix digit (k_sort_pass).
 #include "sidm_plan.hpp"
 #include "sidm_steps.hpp"
 
 namespace sidm {
 
-// ---------------------------------------------------------------- bounding boxes
-__global__ __launch_bounds__(kStreamBlock) void k_block_bbox(
-    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const StreamBlock* __restrict__ blocks, double* __restrict__ bout)
+// ---------------------------------------------------------------- wave reductions
+// v moved by a DPP control (rotations within rows of 16 lanes)
+template <int CTRL>
+__device__ inline double dpp_f64(double v)
 {
-    __shared__ double lo[3][kStreamBlock], hi[3][kStreamBlock];
-    const StreamBlock B = blocks[blockIdx.x];
-    const int t = threadIdx.x;
-    const int64_t i = B.start + (t < B.count ? t : 0);
-    const double p[3] = {x[i], y[i], z[i]};
-    for (int c = 0; c < 3; ++c) { lo[c][t] = p[c]; hi[c][t] = p[c]; }
-    __syncthreads();
-    for (int s = kStreamBlock / 2; s > 0; s >>= 1) {
-        if (t < s)
-            for (int c = 0; c < 3; ++c) {
-                lo[c][t] = fmin(lo[c][t], lo[c][t + s]);
-                hi[c][t] = fmax(hi[c][t], hi[c][t + s]);
-            }
-        __syncthreads();
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Minimum / maximum over each row of 16 lanes, on every lane of the row.
+__device__ inline double row_min(double v)
+{
+    v = fmin(v, dpp_f64<0x128>(v));   // row_ror:8
+    v = fmin(v, dpp_f64<0x124>(v));
+    v = fmin(v, dpp_f64<0x122>(v));
+    return fmin(v, dpp_f64<0x121>(v));
+}
+
+__device__ inline double row_max(double v)
+{
+    v = fmax(v, dpp_f64<0x128>(v));
+    v = fmax(v, dpp_f64<0x124>(v));
+    v = fmax(v, dpp_f64<0x122>(v));
+    return fmax(v, dpp_f64<0x121>(v));
+}
+
+// ... and over the rows of the wave (v uniform within each row).
+__device__ inline double rows_min(double v)
+{
+    v = fmin(v, __shfl_xor(v, 16, 64));
+    return fmin(v, __shfl_xor(v, 32, 64));
+}
+
+__device__ inline double rows_max(double v)
+{
+    v = fmax(v, __shfl_xor(v, 16, 64));
+    return fmax(v, __shfl_xor(v, 32, 64));
+}
+
+// ---------------------------------------------------------------- bounding boxes
+// Box and mass range of a workgroup's particles: per-thread extrema e (min x,
+// y, z, m, max x, y, z, m) reduced over NW waves; every thread returns the
+// result.  red: 8 * NW words of LDS.
+template <int NW>
+__device__ inline void block_range(double (&e)[kRange], double* red)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int c = 0; c < kRange; ++c) {
+        e[c] = c < 4 ? rows_min(row_min(e[c])) : rows_max(row_max(e[c]));
+        if (lane == 0) red[c * NW + wv] = e[c];
     }
-    if (t < 3) {
-        bout[7 * (int64_t)blockIdx.x + t] = lo[t][0];
-        bout[7 * (int64_t)blockIdx.x + 3 + t] = hi[t][0];
+    __syncthreads();
+    static_assert(16 % NW == 0, "the waves' results repeat in a row of lanes");
+#pragma unroll
+    for (int c = 0; c < kRange; ++c) {
+        const double v = red[c * NW + lane % NW];
+        e[c] = c < 4 ? row_min(v) : row_max(v);
     }
 }
 
-__global__ __launch_bounds__(kStreamBlock) void k_halo_bbox(
-    const HaloDev* __restrict__ halos, const double* __restrict__ bin, double* __restrict__ bbox)
+// The common mass of a halo (cmass[h], 0 when its masses differ) and its
+// largest (cmass[n_halos + h]).  With a status array, a halo that scatters
+// (sigma_m > 0) without a common mass is flagged: the probability of a pair
+// takes the mass of one member, which is only symmetric when the masses are
+// equal (each run of the paper's Table 1 has one particle mass), so such a
+// halo is not scattered.
+__device__ inline void put_mass(const HaloDev& H, int h, int n_halos, double lo, double hi,
+                                double* __restrict__ cmass, int* __restrict__ status)
 {
-    __shared__ double lo[3][kStreamBlock], hi[3][kStreamBlock];
+    const bool equal = lo == hi;
+    cmass[h] = equal ? lo : 0.0;
+    cmass[n_halos + h] = hi;
+    if (status && !equal && H.sigma_m > 0.0) atomicOr(&status[h], SIDM_DEV_UNEQUAL_MASS);
+}
+
+// Per streaming block: its range.  The launch also clears the work space of
+// the sort that follows (n_zero words).
+__global__ __launch_bounds__(kStreamBlock) void k_block_range(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const double* __restrict__ m, const StreamBlock* __restrict__ blocks,
+    double* __restrict__ brange, uint32_t* __restrict__ zero, int64_t n_zero)
+{
+    __shared__ double red[kRange * (kStreamBlock / 64)];
+    const StreamBlock B = blocks[blockIdx.x];
+    const int t = threadIdx.x;
+    for (int64_t i = (int64_t)blockIdx.x * kStreamBlock + t; i < n_zero;
+         i += (int64_t)gridDim.x * kStreamBlock)
+        zero[i] = 0u;
+    const int64_t i = B.start + (t < B.count ? t : 0);
+    const double px = x[i], py = y[i], pz = z[i], mi = m[i];
+    double e[kRange] = {px, py, pz, mi, px, py, pz, mi};
+    block_range<kStreamBlock / 64>(e, red);
+    if (t == 0)
+        for (int c = 0; c < kRange; ++c) brange[kRange * (int64_t)blockIdx.x + c] = e[c];
+}
+
+constexpr int kRangeThreads = 1024;
+__global__ __launch_bounds__(kRangeThreads) void k_halo_range(
+    const HaloDev* __restrict__ halos, const double* __restrict__ brange,
+    double* __restrict__ bbox, double* __restrict__ cmass, int* __restrict__ status)
+{
+    __shared__ double red[kRange * (kRangeThreads / 64)];
     const HaloDev& H = halos[blockIdx.x];
     const int t = threadIdx.x;
     const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
-    double l[3] = {INFINITY, INFINITY, INFINITY}, u[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t b = t; b < nb; b += kStreamBlock)
-        for (int c = 0; c < 3; ++c) {
-            l[c] = fmin(l[c], bin[7 * (H.stream_block0 + b) + c]);
-            u[c] = fmax(u[c], bin[7 * (H.stream_block0 + b) + 3 + c]);
+    double e[kRange] = {INFINITY, INFINITY, INFINITY, INFINITY,
+                        -INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int64_t b = t; b < nb; b += kRangeThreads)
+        for (int c = 0; c < kRange; ++c) {
+            const double v = brange[kRange * (H.stream_block0 + b) + c];
+            e[c] = c < 4 ? fmin(e[c], v) : fmax(e[c], v);
         }
-    for (int c = 0; c < 3; ++c) { lo[c][t] = l[c]; hi[c][t] = u[c]; }
-    __syncthreads();
-    for (int s = kStreamBlock / 2; s > 0; s >>= 1) {
-        if (t < s)
-            for (int c = 0; c < 3; ++c) {
-                lo[c][t] = fmin(lo[c][t], lo[c][t + s]);
-                hi[c][t] = fmax(hi[c][t], hi[c][t + s]);
-            }
-        __syncthreads();
-    }
-    if (t < 3) {
-        bbox[6 * blockIdx.x + t] = lo[t][0];
-        bbox[6 * blockIdx.x + 3 + t] = hi[t][0];
+    block_range<kRangeThreads / 64>(e, red);
+    if (t == 0) {
+        for (int c = 0; c < 3; ++c) {
+            bbox[6 * blockIdx.x + c] = e[c];
+            bbox[6 * blockIdx.x + 3 + c] = e[4 + c];
+        }
+        put_mass(H, blockIdx.x, gridDim.x, e[3], e[7], cmass, status);
     }
 }
 
@@ -82,65 +158,113 @@ __device__ inline unsigned quant16(double v, double lo, double inv)
     return (unsigned)q;
 }
 
-__global__ __launch_bounds__(kStreamBlock) void k_morton_keys(
-    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const StreamBlock* __restrict__ blocks, const HaloDev* __restrict__ halos,
-    const double* __restrict__ bbox, unsigned long long* __restrict__ keys,
-    uint32_t* __restrict__ vals, const int8_t* __restrict__ bin, int tick, int bmax,
-    int rank_shift)
+// Sort key of particle i (without the halo's rank): the Morton code over the
+// halo's box (lo, and 65535 / its largest side).  In a tick of block steps the
+// inactive particles of a direct-sum halo sort after its active ones (bit 48),
+// so the active ones fill whole i-blocks.
+__device__ inline unsigned long long morton_key(const HaloDev& H, double px, double py, double pz,
+                                                const double* lo, double inv,
+                                                const int8_t* __restrict__ bin, int64_t i,
+                                                int tick, int bmax, int rank_shift)
 {
-    const StreamBlock B = blocks[blockIdx.x];
-    const int t = threadIdx.x;
-    if (t >= B.count) return;
-    const HaloDev& H = halos[B.halo];
-    const int64_t i = B.start + t;
-    const double* bb = bbox + 6 * B.halo;
-    double ext = fmax(fmax(bb[3] - bb[0], bb[4] - bb[1]), bb[5] - bb[2]);
-    const double inv = ext > 0.0 ? 65535.0 / ext : 0.0;
-    const unsigned long long code = spread3(quant16(x[i], bb[0], inv)) |
-                                    (spread3(quant16(y[i], bb[1], inv)) << 1) |
-                                    (spread3(quant16(z[i], bb[2], inv)) << 2);
-    const int64_t pos = H.sbase + (i - H.offset);
-    // in a tick of block steps the inactive particles of a direct-sum halo sort
-    // after its active ones (bit 48), so the active ones fill whole i-blocks
-    unsigned long long later = 0ull;
+    unsigned long long key = spread3(quant16(px, lo[0], inv)) |
+                             (spread3(quant16(py, lo[1], inv)) << 1) |
+                             (spread3(quant16(pz, lo[2], inv)) << 2);
     if (rank_shift > 48 && tick > 0 && !(H.tree_alpha > 0.0) &&
         !bin_active(H, bin[i], local_tick(H, tick, bmax)))
-        later = 1ull << 48;
-    keys[pos] = ((unsigned long long)H.rank << rank_shift) | later | code;
-    vals[pos] = (uint32_t)i;
+        key |= 1ull << 48;
+    return key;
+}
+
+__device__ inline double key_scale(const double* lo, const double* hi)
+{
+    const double ext = fmax(fmax(hi[0] - lo[0], hi[1] - lo[1]), hi[2] - lo[2]);
+    return ext > 0.0 ? 65535.0 / ext : 0.0;
 }
 
 // ---------------------------------------------------------------- radix sort
-constexpr int kTile = kSortBlock * kSortItems;
+constexpr int kDigits = 1 << kSortBits;
+constexpr int kSortWaves = kSortBlock / 64;
 
-__global__ __launch_bounds__(kSortBlock) void k_sort_count(
-    const unsigned long long* __restrict__ keys, int64_t n, int shift, uint32_t* __restrict__ hist,
-    int64_t nblk)
+// Keys and indices of `group` streaming blocks per workgroup, and the number
+// of keys with each value of each digit (hist: kDigits words per pass).
+__global__ __launch_bounds__(kStreamBlock) void k_morton_keys(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const StreamBlock* __restrict__ blocks, int64_t n_blocks, int group,
+    const HaloDev* __restrict__ halos, const double* __restrict__ bbox,
+    unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
+    const int8_t* __restrict__ bin, int tick, int bmax, int rank_shift, int passes,
+    uint32_t* __restrict__ hist)
 {
-    __shared__ uint32_t cnt[1 << kSortBits];
+    __shared__ uint32_t cnt[kSortMaxPasses][kDigits];
     const int t = threadIdx.x;
-    cnt[t] = 0;
+    for (int p = 0; p < passes; ++p) cnt[p][t] = 0u;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kTile;
-    for (int r = 0; r < kSortItems; ++r) {
-        const int64_t i = base + (int64_t)r * kSortBlock + t;
-        if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & 0xFF], 1u);
+    const int64_t b0 = (int64_t)blockIdx.x * group;
+    const int64_t b1 = b0 + group < n_blocks ? b0 + group : n_blocks;
+    for (int64_t b = b0; b < b1; ++b) {
+        const StreamBlock B = blocks[b];
+        if (t >= B.count) continue;
+        const HaloDev& H = halos[B.halo];
+        const int64_t i = B.start + t;
+        const double* bb = bbox + 6 * B.halo;
+        const unsigned long long key =
+            ((unsigned long long)H.rank << rank_shift) |
+            morton_key(H, x[i], y[i], z[i], bb, key_scale(bb, bb + 3), bin, i, tick, bmax,
+                       rank_shift);
+        const int64_t pos = H.sbase + (i - H.offset);
+        keys[pos] = key;
+        vals[pos] = (uint32_t)i;
+        for (int p = 0; p < passes; ++p)
+            atomicAdd(&cnt[p][(key >> (kSortBits * p)) & (kDigits - 1)], 1u);
     }
     __syncthreads();
-    hist[(int64_t)t * nblk + blockIdx.x] = cnt[t];
+    for (int p = 0; p < passes; ++p)
+        if (cnt[p][t]) atomicAdd(&hist[p * kDigits + t], cnt[p][t]);
 }
 
-// Exclusive scan of len counts, in place, in three launches: each of nseg
-// blocks sums its segment of seg entries (a multiple of the tile), one block
-// scans the nseg sums, and each block rescans its segment from its offset in
-// tiles of kScanTile entries, four consecutive ones per thread (coalesced).
-constexpr int kScanThreads = 256;
-constexpr int kScanTile = 4 * kScanThreads;
+// Lanes of the wave whose digit equals this lane's.
+__device__ inline unsigned long long match_digit(uint32_t d)
+{
+    unsigned long long peers = ~0ull;
+#pragma unroll
+    for (int bit = 0; bit < kSortBits; ++bit) {
+        const bool set = (d >> bit) & 1u;
+        const unsigned long long m = __ballot(set);
+        peers &= set ? m : ~m;
+    }
+    return peers;
+}
 
-// Exclusive prefix of v over the block's threads (in thread order); total
-// receives the block's sum.  Every thread of the block must call it.
-__device__ inline uint32_t block_scan_excl(uint32_t v, uint32_t* sw, uint32_t& total)
+// Ranks of a wave's items among its earlier ones with the same digit: item r
+// of lane l is the wave's (64 r + l)-th.  cnt: the wave's count per digit
+// (zero on entry, its totals on return).
+template <int IPT, class K>
+__device__ inline void wave_rank(const K (&key)[IPT], int shift, uint32_t* cnt, uint32_t (&rank)[IPT],
+                                 uint32_t (&dig)[IPT])
+{
+    const unsigned long long below = (1ull << (threadIdx.x & 63)) - 1ull;
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const uint32_t d = (uint32_t)(key[r] >> shift) & (kDigits - 1);
+        const unsigned long long peers = match_digit(d);
+        const uint32_t before = cnt[d];
+        const uint32_t in = (uint32_t)__popcll(peers & below);
+        // the wave's lanes run together: every lane has read the count before
+        // the last of its peers moves it on
+        __builtin_amdgcn_wave_barrier();
+        if ((peers & ~below) >> (threadIdx.x & 63) == 1ull)
+            cnt[d] = before + in + 1u;
+        __builtin_amdgcn_wave_barrier();
+        rank[r] = before + in;
+        dig[r] = d;
+    }
+}
+
+// Exclusive prefix over kDigits values, value d on thread d < kDigits of the
+// block (others pass 0 and ignore the result); every thread of the block must
+// call it.  sw: kDigits / 64 words of LDS.
+__device__ inline uint32_t digit_scan(uint32_t v, uint32_t* sw)
 {
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     uint32_t inc = v;
@@ -148,175 +272,215 @@ __device__ inline uint32_t block_scan_excl(uint32_t v, uint32_t* sw, uint32_t& t
         const uint32_t u = __shfl_up(inc, o, 64);
         if (lane >= o) inc += u;
     }
-    if (lane == 63) sw[wv] = inc;
+    if (t < kDigits && lane == 63) sw[wv] = inc;
     __syncthreads();
     uint32_t off = 0;
-    total = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) {
-        const uint32_t s = sw[w];
-        if (w < wv) off += s;
-        total += s;
-    }
-    __syncthreads();   // sw is reused by the next call
+    for (int w = 0; w < kDigits / 64; ++w)
+        if (w < wv) off += sw[w];
     return off + inc - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ a,
-                                                              int64_t len, int64_t seg,
-                                                              uint32_t* __restrict__ part)
-{
-    __shared__ uint32_t sw[kScanThreads / 64];
-    const int64_t b0 = (int64_t)blockIdx.x * seg;
-    const int64_t b1 = b0 + seg < len ? b0 + seg : len;
-    uint32_t s = 0;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += kScanThreads) s += a[i];
-    uint32_t total;
-    (void)block_scan_excl(s, sw, total);
-    if (threadIdx.x == 0) part[blockIdx.x] = total;
-}
+// One digit of the stable LSD sort in one launch.  Workgroups take tiles of
+// kSortBlock * IPT keys in the order of a ticket, so a tile's predecessors are
+// held by workgroups that run or have run; each publishes its count of every
+// digit in one word (state in the top two bits, so a word is either whole or
+// absent), then adds up its predecessors' words, newest first, back to the
+// first one that already holds a running total (Merrill and Garland's
+// decoupled look-back).  A workgroup waits only for lower tickets, which never
+// wait for higher ones, so every wait ends.
+//
+// Bound by latency, not by the 24 bytes per key that it moves: 8.4 us per
+// digit at 65536 keys, 15.7 at 500009, 22.7 at 2^20, 45 at 2.4 million.  The
+// five launches it replaced (tile counts, three for their scan, a scatter that
+// took a tile's keys 256 at a time between barriers) took 37, 39, 41 and 68.
+constexpr uint32_t kTileSum = 1u << 30, kTileTotal = 2u << 30, kTileValue = kTileSum - 1u;
+constexpr int kLookBack = 8;   // words read at once
 
-// Exclusive scan of n <= kScanMaxSeg segment sums, in place, by one block.
-__global__ __launch_bounds__(kScanMaxSeg) void k_scan_parts(uint32_t* __restrict__ part, int n)
-{
-    __shared__ uint32_t p[kScanMaxSeg];
-    const int t = threadIdx.x;
-    const uint32_t v = t < n ? part[t] : 0u;
-    p[t] = v;
-    __syncthreads();
-    for (int off = 1; off < kScanMaxSeg; off <<= 1) {
-        const uint32_t u = t >= off ? p[t - off] : 0u;
-        __syncthreads();
-        p[t] += u;
-        __syncthreads();
-    }
-    if (t < n) part[t] = p[t] - v;
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t* __restrict__ a,
-                                                             int64_t len, int64_t seg,
-                                                             const uint32_t* __restrict__ part)
-{
-    __shared__ uint32_t sw[kScanThreads / 64];
-    const int64_t b0 = (int64_t)blockIdx.x * seg;
-    const int64_t b1 = b0 + seg < len ? b0 + seg : len;
-    uint32_t carry = part[blockIdx.x];
-    for (int64_t t0 = b0; t0 < b1; t0 += kScanTile) {
-        const int64_t i0 = t0 + 4 * (int64_t)threadIdx.x;
-        uint32_t v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = i0 + q < b1 ? a[i0 + q] : 0u;
-        uint32_t total;
-        uint32_t run = carry + block_scan_excl(v[0] + v[1] + v[2] + v[3], sw, total);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (i0 + q < b1) a[i0 + q] = run;
-            run += v[q];
-        }
-        carry += total;
-    }
-}
-
-// Stable scatter: items of a tile are taken 256 at a time in index order; the
-// rank of an item among equal digits is the running count of the digit plus
-// the count in earlier waves plus the count in lower lanes of its own wave.
-__global__ __launch_bounds__(kSortBlock) void k_sort_scatter(
+template <int IPT>
+__global__ __launch_bounds__(kSortBlock) void k_sort_pass(
     const unsigned long long* __restrict__ kin, const uint32_t* __restrict__ vin,
     unsigned long long* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift,
-    const uint32_t* __restrict__ hist, int64_t nblk)
+    const uint32_t* __restrict__ hist, uint32_t* __restrict__ ticket, uint32_t* __restrict__ tiles)
 {
-    constexpr int kWaves = kSortBlock / 64;
-    __shared__ uint32_t run[1 << kSortBits];
-    __shared__ uint32_t wcnt[kWaves][1 << kSortBits];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    run[t] = hist[(int64_t)t * nblk + blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * kTile;
-    const unsigned long long lt = (1ull << lane) - 1ull;
-    for (int r = 0; r < kSortItems; ++r) {
-        const int64_t i = base + (int64_t)r * kSortBlock + t;
-        const bool valid = i < n;
-        const unsigned long long key = valid ? kin[i] : 0ull;
-        const uint32_t val = valid ? vin[i] : 0u;
-        const uint32_t d = (uint32_t)(key >> shift) & 0xFFu;
+    __shared__ uint32_t cnt[kSortWaves][kDigits];
+    __shared__ uint32_t sw[kDigits / 64];
+    __shared__ uint32_t tile_s;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    if (t == 0) tile_s = atomicAdd(ticket, 1u);
 #pragma unroll
-        for (int q = 0; q < kWaves; ++q) wcnt[q][t] = 0;
-        __syncthreads();
-        unsigned long long peers = __ballot(valid);
+    for (int q = 0; q < kSortWaves; ++q) cnt[q][t] = 0u;
+    const uint32_t first = digit_scan(hist[t], sw);   // keys with a smaller digit
+    const int64_t tile = tile_s;
+    const int64_t base = tile * (kSortBlock * IPT) + wv * (64 * IPT) + lane;
+    unsigned long long key[IPT];
+    uint32_t val[IPT], rank[IPT], dig[IPT];
 #pragma unroll
-        for (int bit = 0; bit < kSortBits; ++bit) {
-            const bool set = (d >> bit) & 1u;
-            const unsigned long long m = __ballot(set);
-            peers &= set ? m : ~m;
-        }
-        const uint32_t rank = (uint32_t)__popcll(peers & lt);
-        if (valid && rank == (uint32_t)__popcll(peers) - 1u) wcnt[w][d] = rank + 1u;
-        __syncthreads();
-        {
-            uint32_t acc = run[t];
+    for (int r = 0; r < IPT; ++r) {
+        const int64_t i = base + 64 * r;
+        // past the end: the last keys of the last tile, digit kDigits - 1 in
+        // every pass, behind every real key
+        key[r] = i < n ? kin[i] : ~0ull;
+        val[r] = i < n ? vin[i] : 0u;
+    }
+    wave_rank<IPT>(key, shift, cnt[wv], rank, dig);
+    __syncthreads();
+    uint32_t sum = 0u;
 #pragma unroll
-            for (int q = 0; q < kWaves; ++q) {
-                const uint32_t c = wcnt[q][t];
-                wcnt[q][t] = acc;
-                acc += c;
+    for (int q = 0; q < kSortWaves; ++q) sum += cnt[q][t];
+    uint32_t* mine = tiles + tile * kDigits + t;
+    __hip_atomic_store(mine, sum | (tile == 0 ? kTileTotal : kTileSum), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t before = 0u;
+    for (int64_t j = tile - 1; j >= 0;) {
+        uint32_t w[kLookBack];
+#pragma unroll
+        for (int q = 0; q < kLookBack; ++q)
+            w[q] = j >= q ? __hip_atomic_load(tiles + (j - q) * kDigits + t, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT)
+                          : kTileTotal;
+        bool go = true;
+#pragma unroll
+        for (int q = 0; q < kLookBack; ++q) {
+            go = go && w[q] != 0u;
+            if (go) {
+                before += w[q] & kTileValue;
+                --j;
+                if (w[q] & kTileTotal) {
+                    j = -1;
+                    go = false;
+                }
             }
-            run[t] = acc;
         }
-        __syncthreads();
-        if (valid) {
-            const uint32_t pos = wcnt[w][d] + rank;
-            kout[pos] = key;
-            vout[pos] = val;
-        }
-        __syncthreads();
+    }
+    if (tile > 0)
+        __hip_atomic_store(mine, (before + sum) | kTileTotal, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t acc = first + before;
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q) {
+        const uint32_t c = cnt[q][t];
+        cnt[q][t] = acc;
+        acc += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        if (base + 64 * r >= n) continue;
+        const uint32_t pos = cnt[wv][dig[r]] + rank[r];
+        kout[pos] = key[r];
+        vout[pos] = val[r];
     }
 }
 
-// ---------------------------------------------------------------- permute
-__global__ __launch_bounds__(kStreamBlock) void k_permute(
-    int64_t n, const uint32_t* __restrict__ order, const double* __restrict__ x,
-    const double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ vx,
-    const double* __restrict__ vy, const double* __restrict__ vz, const double* __restrict__ m,
-    const uint32_t* __restrict__ id, const double* __restrict__ h, double* __restrict__ sx,
-    double* __restrict__ sy, double* __restrict__ sz, double4* __restrict__ sp4,
-    double* __restrict__ svx,
-    double* __restrict__ svy, double* __restrict__ svz, double* __restrict__ sm,
-    uint32_t* __restrict__ sid, double* __restrict__ sh, uint32_t* __restrict__ perm)
+// ---------------------------------------------------------------- small halos
+// Box, masses, keys and the whole sort of one halo of at most 1024 * IPT
+// particles in one workgroup: the keys stay in registers, each digit's
+// exchange goes through LDS.  Bound by one CU's vector issue (the ballots of
+// the ranks): 51 us for 8192 keys, 19 us for 1500, where the general path takes
+// ten launches and about 85 us (and took 33 launches and 230 us).
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64;
+static_assert(kSmallN == 8 * kSmallThreads, "the largest instantiation below");
+
+template <int IPT>
+__global__ __launch_bounds__(kSmallThreads) void k_cell_small(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const double* __restrict__ m, const HaloDev* __restrict__ halos, double* __restrict__ cmass,
+    int* __restrict__ status, unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
+    const int8_t* __restrict__ bin, int tick, int bmax, int rank_shift)
 {
-    const int64_t p = (int64_t)blockIdx.x * kStreamBlock + threadIdx.x;
-    if (p >= n) return;
-    const uint32_t o = order[p];
-    const double px = x[o], py = y[o], pz = z[o];
-    sx[p] = px; sy[p] = py; sz[p] = pz;
-    sp4[p] = make_double4(px, py, pz, 0.0);
-    if (vx) { svx[p] = vx[o]; svy[p] = vy[o]; svz[p] = vz[o]; }
-    sm[p] = m[o];
-    if (id) sid[p] = id[o];
-    sh[p] = h ? h[o] : 0.0;
-    perm[p] = o;
+    __shared__ unsigned long long skey[kSmallThreads * IPT];
+    __shared__ uint16_t sidx[kSmallThreads * IPT];
+    __shared__ uint32_t cnt[kSmallWaves][kDigits];
+    __shared__ double red[kRange * kSmallWaves];
+    __shared__ uint32_t sw[kDigits / 64];
+    const HaloDev& H = halos[blockIdx.x];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int n = (int)H.n, q0 = wv * (64 * IPT) + lane;
+    double px[IPT], py[IPT], pz[IPT];
+    double e[kRange] = {INFINITY, INFINITY, INFINITY, INFINITY,
+                        -INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const int q = q0 + 64 * r;
+        px[r] = py[r] = pz[r] = 0.0;
+        if (q < n) {
+            const int64_t i = H.offset + q;
+            px[r] = x[i]; py[r] = y[i]; pz[r] = z[i];
+            const double v[4] = {px[r], py[r], pz[r], m[i]};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                e[c] = fmin(e[c], v[c]);
+                e[4 + c] = fmax(e[4 + c], v[c]);
+            }
+        }
+    }
+    block_range<kSmallWaves>(e, red);
+    if (t == 0) put_mass(H, blockIdx.x, gridDim.x, e[3], e[7], cmass, status);
+    const double inv = key_scale(e, e + 4);
+    unsigned long long key[IPT];
+    uint32_t id[IPT], rank[IPT], dig[IPT];
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const int q = q0 + 64 * r;
+        // past the end: behind every real key in every pass
+        key[r] = q < n ? morton_key(H, px[r], py[r], pz[r], e, inv, bin, H.offset + q, tick, bmax,
+                                    rank_shift)
+                       : ~0ull;
+        id[r] = (uint32_t)q;
+    }
+    const int bits = rank_shift > 48 && tick > 0 ? 49 : 48;
+    for (int shift = 0; shift < bits; shift += kSortBits) {
+#pragma unroll
+        for (int q = 0; q < kDigits / 64; ++q) cnt[wv][64 * q + lane] = 0u;
+        __builtin_amdgcn_wave_barrier();
+        wave_rank<IPT>(key, shift, cnt[wv], rank, dig);
+        __syncthreads();
+        uint32_t sum = 0u;
+        if (t < kDigits)
+            for (int w = 0; w < kSmallWaves; ++w) sum += cnt[w][t];
+        uint32_t acc = digit_scan(sum, sw);
+        if (t < kDigits)
+            for (int w = 0; w < kSmallWaves; ++w) {
+                const uint32_t c = cnt[w][t];
+                cnt[w][t] = acc;
+                acc += c;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            const uint32_t pos = cnt[wv][dig[r]] + rank[r];
+            skey[pos] = key[r];
+            sidx[pos] = (uint16_t)id[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            key[r] = skey[q0 + 64 * r];
+            id[r] = sidx[q0 + 64 * r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const int q = q0 + 64 * r;
+        if (q >= n) continue;
+        keys[H.sbase + q] = key[r] | ((unsigned long long)H.rank << rank_shift);
+        vals[H.sbase + q] = (uint32_t)(H.offset + id[r]);
+    }
 }
 
-// ---------------------------------------------------------------- boxes
-__device__ inline double wave_min(double v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-__device__ inline double wave_max(double v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
+// ---------------------------------------------------------------- permute and boxes
+// Box of the lanes [lo, hi) of the wave, on every lane.
 __device__ inline void range_box(int lo, int hi, int lane, double px, double py, double pz,
                                  double* o)
 {
     const bool in = lane >= lo && lane < hi;
-    o[0] = wave_min(in ? px : INFINITY);
-    o[1] = wave_min(in ? py : INFINITY);
-    o[2] = wave_min(in ? pz : INFINITY);
-    o[3] = wave_max(in ? px : -INFINITY);
-    o[4] = wave_max(in ? py : -INFINITY);
-    o[5] = wave_max(in ? pz : -INFINITY);
+    o[0] = rows_min(row_min(in ? px : INFINITY));
+    o[1] = rows_min(row_min(in ? py : INFINITY));
+    o[2] = rows_min(row_min(in ? pz : INFINITY));
+    o[3] = rows_max(row_max(in ? px : -INFINITY));
+    o[4] = rows_max(row_max(in ? py : -INFINITY));
+    o[5] = rows_max(row_max(in ? pz : -INFINITY));
 }
 
 __device__ inline double box_diag2(const double* b)
@@ -325,12 +489,13 @@ __device__ inline double box_diag2(const double* b)
     return ex * ex + ey * ey + ez * ez;
 }
 
-// Split point of the lanes [lo, hi) at their coarsest internal Morton boundary,
-// kept only if it at least halves the count-weighted extent (count x box
-// diagonal summed over the pieces): a dense group is then separated from a few
-// far members even when the far piece stays large.  -1 if not kept.
+// Split point of the lanes [lo, hi), whose box is `full`, at their coarsest
+// internal Morton boundary, kept only if it at least halves the count-weighted
+// extent (count x box diagonal summed over the pieces, whose boxes are ba and
+// bb): a dense group is then separated from a few far members even when the
+// far piece stays large.  -1 if not kept.
 __device__ inline int split_range(int lo, int hi, int lane, unsigned long long key, double px,
-                                  double py, double pz, double* ba, double* bb)
+                                  double py, double pz, const double* full, double* ba, double* bb)
 {
     if (hi - lo < 2) return -1;
     const unsigned long long kf = __shfl(key, lo, 64), kl = __shfl(key, hi - 1, 64);
@@ -339,8 +504,6 @@ __device__ inline int split_range(int lo, int hi, int lane, unsigned long long k
     const bool low = lane >= lo && lane < hi && !(((key ^ kf) >> hb) & 1ull);
     const int s = lo + __popcll(__ballot(low));
     if (s <= lo || s >= hi) return -1;
-    double full[6];
-    range_box(lo, hi, lane, px, py, pz, full);
     range_box(lo, s, lane, px, py, pz, ba);
     range_box(s, hi, lane, px, py, pz, bb);
     const double before = (hi - lo) * sqrt(box_diag2(full));
@@ -348,71 +511,81 @@ __device__ inline int split_range(int lo, int hi, int lane, unsigned long long k
     return after < 0.5 * before ? s : -1;
 }
 
-// One wave per bucket: the box, up to kSubMax compact sub-ranges, and (when
-// cbox is given) the boxes of its chunks of kChunk particles (an empty
-// chunk gets the empty box [+inf, -inf], which no distance test passes).
-__global__ __launch_bounds__(256) void k_bucket_boxes(
-    const BucketInfo* __restrict__ buckets, int64_t nb, const double* __restrict__ sx,
-    const double* __restrict__ sy, const double* __restrict__ sz,
-    const unsigned long long* __restrict__ skeys, double* __restrict__ box,
-    SubRange* __restrict__ sub, int* __restrict__ sub_n, double* __restrict__ cbox)
+// One wave per bucket: gathers its particles into the sorted arrays, and
+// writes its box, up to kSubMax compact sub-ranges (two levels of splits) and
+// (when cbox is given) the boxes of its chunks of kChunk particles (an empty
+// chunk gets the empty box [+inf, -inf], which no distance test passes).  A
+// chunk is a row of 16 lanes: its box is what the row reduction leaves.
+static_assert(kChunk == 16, "a chunk is a row of lanes");
+__global__ __launch_bounds__(256) void k_bucket_fill(
+    const BucketInfo* __restrict__ buckets, int64_t nb, const uint32_t* __restrict__ order,
+    const unsigned long long* __restrict__ skeys, const double* __restrict__ x,
+    const double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ vx,
+    const double* __restrict__ vy, const double* __restrict__ vz, const double* __restrict__ m,
+    const uint32_t* __restrict__ id, const double* __restrict__ h, double* __restrict__ sx,
+    double* __restrict__ sy, double* __restrict__ sz, double4* __restrict__ sp4,
+    double* __restrict__ svx, double* __restrict__ svy, double* __restrict__ svz,
+    double* __restrict__ sm, uint32_t* __restrict__ sid, double* __restrict__ sh,
+    uint32_t* __restrict__ perm, double* __restrict__ box, SubRange* __restrict__ sub,
+    int* __restrict__ sub_n, double* __restrict__ cbox)
 {
     const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= nb) return;
     const int lane = threadIdx.x & 63;
     const BucketInfo B = buckets[b];
-    const int64_t p = B.start + (lane < B.count ? lane : 0);
-    const double px = sx[p], py = sy[p], pz = sz[p];
+    const bool live = lane < B.count;
+    const int64_t p = B.start + (live ? lane : 0);
+    const uint32_t o = order[p];
     const unsigned long long key = skeys[p];
-    double full[6];
-    range_box(0, B.count, lane, px, py, pz, full);
+    const double px = x[o], py = y[o], pz = z[o];
+    if (live) {
+        sx[p] = px; sy[p] = py; sz[p] = pz;
+        sp4[p] = make_double4(px, py, pz, 0.0);
+        if (vx) { svx[p] = vx[o]; svy[p] = vy[o]; svz[p] = vz[o]; }
+        sm[p] = m[o];
+        if (id) sid[p] = id[o];
+        sh[p] = h ? h[o] : 0.0;
+        perm[p] = o;
+    }
+    double e[6] = {row_min(live ? px : INFINITY),  row_min(live ? py : INFINITY),
+                   row_min(live ? pz : INFINITY),  row_max(live ? px : -INFINITY),
+                   row_max(live ? py : -INFINITY), row_max(live ? pz : -INFINITY)};
+    if (cbox && (lane & 15) == 0)
+        for (int q = 0; q < 6; ++q) cbox[6 * (kChunks * b + (lane >> 4)) + q] = e[q];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) e[q] = q < 3 ? rows_min(e[q]) : rows_max(e[q]);
     if (lane == 0)
-        for (int q = 0; q < 6; ++q) box[6 * b + q] = full[q];
-    if (cbox)
-        for (int g = 0; g < kChunks; ++g) {
-            double cb[6];
-            range_box(g * kChunk, min(B.count, (g + 1) * kChunk), lane, px, py, pz, cb);
-            if (lane == 0)
-                for (int q = 0; q < 6; ++q) cbox[6 * (kChunks * b + g) + q] = cb[q];
-        }
-    // up to two levels of splits
-    int lo[kSubMax], hi[kSubMax];
-    double bx[kSubMax][6];
-    int n = 1;
-    lo[0] = 0; hi[0] = B.count;
-    for (int q = 0; q < 6; ++q) bx[0][q] = full[q];
-    for (int level = 0; level < 2; ++level) {
-        const int m = n;
-        for (int r = 0; r < m; ++r) {
-            double ba[6], bb[6];
-            const int sp = split_range(lo[r], hi[r], lane, key, px, py, pz, ba, bb);
-            if (sp > 0 && n < kSubMax) {
-                lo[n] = sp; hi[n] = hi[r];
-                hi[r] = sp;
-                for (int q = 0; q < 6; ++q) { bx[r][q] = ba[q]; bx[n][q] = bb[q]; }
-                ++n;
-            }
-        }
-    }
-    if (lane == 0) {
-        // sub-ranges in particle order
-        for (int a = 1; a < n; ++a)
-            for (int c = a; c > 0 && lo[c] < lo[c - 1]; --c) {
-                int t = lo[c]; lo[c] = lo[c - 1]; lo[c - 1] = t;
-                t = hi[c]; hi[c] = hi[c - 1]; hi[c - 1] = t;
-                for (int q = 0; q < 6; ++q) {
-                    const double v = bx[c][q]; bx[c][q] = bx[c - 1][q]; bx[c - 1][q] = v;
-                }
-            }
-        for (int r = 0; r < n; ++r) {
+        for (int q = 0; q < 6; ++q) box[6 * b + q] = e[q];
+    int n = 0;
+    auto emit = [&](int lo, int hi, const double* bx) {
+        if (lane == 0) {
             SubRange R;
-            R.off = lo[r];
-            R.cnt = hi[r] - lo[r];
-            for (int q = 0; q < 6; ++q) R.box[q] = bx[r][q];
-            sub[kSubMax * b + r] = R;
+            R.off = lo;
+            R.cnt = hi - lo;
+            for (int q = 0; q < 6; ++q) R.box[q] = bx[q];
+            sub[kSubMax * b + n] = R;
         }
-        sub_n[b] = n;
+        ++n;
+    };
+    auto half = [&](int lo, int hi, const double* bx) {
+        double ba[6], bb[6];
+        const int s = split_range(lo, hi, lane, key, px, py, pz, bx, ba, bb);
+        if (s > 0) {
+            emit(lo, s, ba);
+            emit(s, hi, bb);
+        } else {
+            emit(lo, hi, bx);
+        }
+    };
+    double ba[6], bb[6];
+    const int s = split_range(0, B.count, lane, key, px, py, pz, e, ba, bb);
+    if (s > 0) {
+        half(0, s, ba);
+        half(s, B.count, bb);
+    } else {
+        emit(0, B.count, e);
     }
+    if (lane == 0) sub_n[b] = n;
 }
 
 // The largest kernel size of every bucket and (when chmax is given) of each of
@@ -426,21 +599,16 @@ __global__ __launch_bounds__(256) void k_bucket_hmax(
     const int lane = threadIdx.x & 63;
     const BucketInfo B = buckets[b];
     const double h = sh[B.start + (lane < B.count ? lane : 0)];
-    const double v = wave_max(h);
+    const double v = rows_max(row_max(h));
     if (lane == 0) hmax[b] = v;
-    if (chmax)
-        for (int g = 0; g < kChunks; ++g) {
-            const double c = wave_max(lane < B.count && lane / kChunk == g ? h : 0.0);
-            if (lane == 0) chmax[kChunks * b + g] = c;
-        }
+    if (!chmax) return;
+    const double c = fmax(row_max(lane < B.count ? h : 0.0), 0.0);
+    if ((lane & 15) == 0) chmax[kChunks * b + (lane >> 4)] = c;
 }
 
-__global__ __launch_bounds__(256) void k_node_boxes(const NodeTask* __restrict__ tasks,
-                                                     int64_t nt, double* __restrict__ box)
+// ---------------------------------------------------------------- tree nodes
+__device__ inline void node_box(const NodeTask T, double* __restrict__ box)
 {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= nt) return;
-    const NodeTask T = tasks[k];
     double o[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
     for (int c = 0; c < T.nchild; ++c) {
         const double* b = box + 6 * (T.child0 + c);
@@ -452,78 +620,123 @@ __global__ __launch_bounds__(256) void k_node_boxes(const NodeTask* __restrict__
     for (int q = 0; q < 6; ++q) box[6 * T.node + q] = o[q];
 }
 
-__global__ __launch_bounds__(256) void k_node_hmax(const NodeTask* __restrict__ tasks, int64_t nt,
-                                                    double* __restrict__ hmax)
+__device__ inline void node_hmax(const NodeTask T, double* __restrict__ hmax)
 {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= nt) return;
-    const NodeTask T = tasks[k];
     double v = 0.0;
     for (int c = 0; c < T.nchild; ++c) v = fmax(v, hmax[T.child0 + c]);
     hmax[T.node] = v;
 }
 
+// One wide level of nodes: their boxes, or (HMAX) their largest kernel sizes.
+template <bool HMAX>
+__global__ __launch_bounds__(256) void k_node_level(const NodeTask* __restrict__ tasks, int64_t nt,
+                                                    double* __restrict__ a)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= nt) return;
+    if (HMAX) node_hmax(tasks[k], a);
+    else node_box(tasks[k], a);
+}
+
+// The levels above: one workgroup, one level after the other (a launch each
+// cost more than the work).
+template <bool HMAX>
+__global__ __launch_bounds__(kTopThreads) void k_node_top(const NodeTask* __restrict__ tasks,
+                                                          TopLevels L, double* a)
+{
+    for (int l = L.first; l < L.n_levels; ++l) {
+        for (int64_t k = L.off[l - 1] + threadIdx.x; k < L.off[l]; k += kTopThreads) {
+            if (HMAX) node_hmax(tasks[k], a);
+            else node_box(tasks[k], a);
+        }
+        __syncthreads();
+    }
+}
+
+
 // ---------------------------------------------------------------- launchers
 static unsigned grid_of(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-// about four tiles per segment, at most kScanMaxSeg segments
-static void launch_scan(uint32_t* a, int64_t len, uint32_t* part, hipStream_t st)
-{
-    int64_t nseg = (len + 4 * kScanTile - 1) / (4 * kScanTile);
-    nseg = nseg < 1 ? 1 : (nseg > kScanMaxSeg ? kScanMaxSeg : nseg);
-    int64_t seg = (len + nseg - 1) / nseg;
-    seg = (seg + kScanTile - 1) / kScanTile * kScanTile;
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nseg), dim3(kScanThreads), 0, st, a, len, seg,
-                       part);
-    hipLaunchKernelGGL(k_scan_parts, dim3(1), dim3(kScanMaxSeg), 0, st, part, (int)nseg);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nseg), dim3(kScanThreads), 0, st, a, len, seg,
-                       part);
-}
-
-// Stable LSD radix sort of keys[0] (with vals[0]) over their low key_bits
-// bits, n keys; returns the index of the buffer pair that holds the result.
-int launch_sort_keys(Scratch& w, int64_t n, int key_bits, hipStream_t st)
+// Stable LSD radix sort of keys[0] (with vals[0]) over their low key_bits bits,
+// n keys (digit counts in w.sort_ws); returns the index of the buffer pair
+// that holds the result.
+static int launch_sort(Scratch& w, int64_t n, int passes, hipStream_t st)
 {
     int cur = 0;
-    const int passes = (key_bits + kSortBits - 1) / kSortBits;
-    const int64_t nblk = (n + kTile - 1) / kTile;
+    const int ipt = sort_items(n);
+    const int64_t ntile = sort_tiles(n);
     for (int p = 0; p < passes; ++p) {
-        const int shift = p * kSortBits;
-        hipLaunchKernelGGL(k_sort_count, dim3((unsigned)nblk), dim3(kSortBlock), 0, st,
-                           w.keys[cur], n, shift, w.hist, nblk);
-        launch_scan(w.hist, nblk * (1 << kSortBits), w.scan_part, st);
-        hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)nblk), dim3(kSortBlock), 0, st,
-                           w.keys[cur], w.vals[cur], w.keys[cur ^ 1], w.vals[cur ^ 1], n, shift,
-                           w.hist, nblk);
+        uint32_t* hist = w.sort_ws + p * kDigits;
+        uint32_t* ticket = w.sort_ws + kSortMaxPasses * kDigits + p;
+        uint32_t* tiles = w.sort_ws + kSortHead + p * ntile * kDigits;
+        auto pass = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)ntile), dim3(kSortBlock), 0, st, w.keys[cur],
+                               w.vals[cur], w.keys[cur ^ 1], w.vals[cur ^ 1], n, p * kSortBits,
+                               hist, ticket, tiles);
+        };
+        if (ipt == 4) pass(k_sort_pass<4>);
+        else if (ipt == 8) pass(k_sort_pass<8>);
+        else pass(k_sort_pass<16>);
         cur ^= 1;
     }
     return cur;
 }
 
+template <bool HMAX>
+static void launch_nodes(const Plan& P, Scratch& w, double* a, hipStream_t st)
+{
+    const TopLevels T = top_levels(P);
+    for (int l = 1; l < T.first; ++l) {
+        const int64_t t0 = P.level_task_off[l - 1], nt = P.level_task_off[l] - t0;
+        hipLaunchKernelGGL(k_node_level<HMAX>, dim3(grid_of(nt, 256)), dim3(256), 0, st,
+                           w.node_tasks + t0, nt, a);
+    }
+    if (T.first < T.n_levels)
+        hipLaunchKernelGGL(k_node_top<HMAX>, dim3(1), dim3(kTopThreads), 0, st, w.node_tasks, T, a);
+}
+
+// The cell list of the current positions, the halos' bounding boxes and their
+// common masses (w.cref).  status: the halos' status words, where a halo that
+// scatters with unequal masses is flagged (null: not checked).
 hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipStream_t st,
-                            int tick, int bmax)
+                            int* status, int tick, int bmax)
 {
     const int64_t n = P.n_sorted;
-    hipLaunchKernelGGL(k_block_bbox, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0, st, s->x,
-                       s->y, s->z, w.blocks, w.bsum);
-    hipLaunchKernelGGL(k_halo_bbox, dim3(P.n_halos), dim3(kStreamBlock), 0, st, w.halos, w.bsum,
-                       w.bbox);
-    hipLaunchKernelGGL(k_morton_keys, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0, st, s->x,
-                       s->y, s->z, w.blocks, w.halos, w.bbox, w.keys[0], w.vals[0], w.bin,
-                       tick, bmax, P.rank_shift);
-    const int cur = launch_sort_keys(w, n, P.key_bits, st);
-    hipLaunchKernelGGL(k_permute, dim3(grid_of(n, kStreamBlock)), dim3(kStreamBlock), 0, st, n,
-                       w.vals[cur], s->x, s->y, s->z, s->vx, s->vy, s->vz, s->m, s->id, s->h,
-                       w.sx, w.sy, w.sz, w.sp4, w.svx, w.svy, w.svz, w.sm, w.sid, w.sh, w.perm);
-    w.skeys = w.keys[cur];
-    hipLaunchKernelGGL(k_bucket_boxes, dim3(grid_of(P.n_buckets, 4)), dim3(256), 0, st, w.buckets,
-                       P.n_buckets, w.sx, w.sy, w.sz, w.skeys, w.box, w.sub, w.sub_n, w.cbox);
-    for (int l = 1; l < P.n_levels; ++l) {
-        const int64_t t0 = P.level_task_off[l - 1], nt = P.level_task_off[l] - t0;
-        if (nt > 0)
-            hipLaunchKernelGGL(k_node_boxes, dim3(grid_of(nt, 256)), dim3(256), 0, st,
-                               w.node_tasks + t0, nt, w.box);
+    int cur = 0;
+    if (P.n_max <= kSmallN) {
+        auto small = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(P.n_halos), dim3(kSmallThreads), 0, st, s->x, s->y, s->z,
+                               s->m, w.halos, w.cref, status, w.keys[0], w.vals[0], w.bin, tick,
+                               bmax, P.rank_shift);
+        };
+        if (P.n_max <= kSmallThreads) small(k_cell_small<1>);
+        else if (P.n_max <= 2 * kSmallThreads) small(k_cell_small<2>);
+        else if (P.n_max <= 4 * kSmallThreads) small(k_cell_small<4>);
+        else small(k_cell_small<8>);
+    } else {
+        const int passes = (P.key_bits + kSortBits - 1) / kSortBits;
+        const int64_t n_zero = kSortHead + passes * sort_tiles(n) * kDigits;
+        if (passes > kSortMaxPasses || n > (int64_t)kTileValue || n_zero > w.sort_ws_n)
+            return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_block_range, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0, st,
+                           s->x, s->y, s->z, s->m, w.blocks, w.brange, w.sort_ws, n_zero);
+        hipLaunchKernelGGL(k_halo_range, dim3(P.n_halos), dim3(kRangeThreads), 0, st, w.halos,
+                           w.brange, w.bbox, w.cref, status);
+        // at most 16 blocks per workgroup; from 64 workgroups on, fewer of them
+        // are better: each adds up to kDigits words per pass to the same counts
+        // (65536 particles: 10.3 us with 256 workgroups, 7.5 us with 64)
+        const int group = (int)std::max<int64_t>(1, std::min<int64_t>(16, P.n_blocks / 64));
+        hipLaunchKernelGGL(k_morton_keys, dim3(grid_of(P.n_blocks, group)), dim3(kStreamBlock), 0,
+                           st, s->x, s->y, s->z, w.blocks, P.n_blocks, group, w.halos, w.bbox,
+                           w.keys[0], w.vals[0], w.bin, tick, bmax, P.rank_shift, passes,
+                           w.sort_ws);
+        cur = launch_sort(w, n, passes, st);
     }
+    hipLaunchKernelGGL(k_bucket_fill, dim3(grid_of(P.n_buckets, 4)), dim3(256), 0, st, w.buckets,
+                       P.n_buckets, w.vals[cur], w.keys[cur], s->x, s->y, s->z, s->vx, s->vy,
+                       s->vz, s->m, s->id, s->h, w.sx, w.sy, w.sz, w.sp4, w.svx, w.svy, w.svz,
+                       w.sm, w.sid, w.sh, w.perm, w.box, w.sub, w.sub_n, w.cbox);
+    launch_nodes<false>(P, w, w.box, st);
     return hipGetLastError();
 }
 
@@ -531,12 +744,7 @@ hipError_t launch_tree_hmax(const Plan& P, Scratch& w, hipStream_t st)
 {
     hipLaunchKernelGGL(k_bucket_hmax, dim3(grid_of(P.n_buckets, 4)), dim3(256), 0, st, w.buckets,
                        P.n_buckets, w.sh, w.hmax, w.chmax);
-    for (int l = 1; l < P.n_levels; ++l) {
-        const int64_t t0 = P.level_task_off[l - 1], nt = P.level_task_off[l] - t0;
-        if (nt > 0)
-            hipLaunchKernelGGL(k_node_hmax, dim3(grid_of(nt, 256)), dim3(256), 0, st,
-                               w.node_tasks + t0, nt, w.hmax);
-    }
+    launch_nodes<true>(P, w, w.hmax, st);
     return hipGetLastError();
 }
 

@@ -48,7 +48,7 @@ int64_t gravity_slots(int device);
 int64_t gravity_slots(int device, const GravShape& shape, bool mixed);
 int64_t gravity_sym_slots(int device, const GravShape& shape);
 hipError_t launch_cell_list(const Plan& plan, const sidm_state* s, Scratch& w, hipStream_t st,
-                            int tick = 0, int bmax = 0);
+                            int* status, int tick = 0, int bmax = 0);
 hipError_t launch_knn(const Plan& plan, const sidm_state* s, Scratch& w, uint32_t* nbr, int k_max,
                       hipStream_t st);
 hipError_t launch_tree_hmax(const Plan& plan, Scratch& w, hipStream_t st);
@@ -430,7 +430,7 @@ sidm_status sidm_gravity(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos,
     if ((r = enter(c, halos, n_halos, s, st, cap)) != SIDM_OK) return r;
     if ((r = guard(c, st, cap)) != SIDM_OK) return r;
     hipError_t e = launch_tree_terms_reset(c->w, n_halos, st);
-    if (e == hipSuccess) e = launch_cell_list(c->plan, s, c->w, st);
+    if (e == hipSuccess) e = launch_cell_list(c->plan, s, c->w, st, nullptr);
     if (e == hipSuccess)
         e = launch_gravity(prec == SIDM_PREC_MIXED, c->plan, c->w, s, 0, st, nullptr, nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "gravity launch");
@@ -450,7 +450,7 @@ sidm_status sidm_knn_h(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos, con
     if ((r = enter(c, halos, n_halos, s, st, cap)) != SIDM_OK) return r;
     hipError_t e = launch_reset(c->plan, c->w, st);
     if (e == hipSuccess && (r = guard(c, st, cap)) != SIDM_OK) return r;
-    if (e == hipSuccess) e = launch_cell_list(c->plan, s, c->w, st);
+    if (e == hipSuccess) e = launch_cell_list(c->plan, s, c->w, st, nullptr);
     if (e == hipSuccess) e = launch_knn(c->plan, s, c->w, nbr, max_k(halos, n_halos), st);
     if (e != hipSuccess) return hip_fail(c, e, "kNN launch");
     publish(c, st, cap);
@@ -478,7 +478,7 @@ sidm_status sidm_scatter(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos,
     }
     hipError_t e = launch_reset(c->plan, c->w, st);
     if (e == hipSuccess && (r = guard(c, st, captured)) != SIDM_OK) return r;
-    if (e == hipSuccess) e = launch_cell_list(c->plan, s, c->w, st);
+    if (e == hipSuccess) e = launch_cell_list(c->plan, s, c->w, st, c->w.status);
     if (e == hipSuccess) e = launch_tree_hmax(c->plan, c->w, st);
     if (e == hipSuccess)
         e = launch_scatter(c->plan, s, c->w, step, events, events ? cap : 0, st, nullptr);
@@ -581,7 +581,7 @@ sidm_status sidm_kdk_step(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos,
             e = launch_kick_drift(c->w.blocks, P.n_blocks, c->w.halos, s->x, s->y, s->z, s->vx,
                                   s->vy, s->vz, s->ax, s->ay, s->az, st);
         mark(1);
-        if (e == hipSuccess) e = launch_cell_list(P, s, c->w, st);
+        if (e == hipSuccess) e = launch_cell_list(P, s, c->w, st, c->w.status);
         mark(5);
         if (e == hipSuccess)
             e = launch_gravity(prec == SIDM_PREC_MIXED, P, c->w, s, 1, st, tm ? E[2] : nullptr,
@@ -596,7 +596,7 @@ sidm_status sidm_kdk_step(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos,
         for (int tick = 1; tick <= (1 << bmax) && e == hipSuccess; ++tick) {
             e = launch_tick_drift(c->w.blocks, P.n_blocks, c->w.halos, s->x, s->y, s->z, s->vx,
                                   s->vy, s->vz, tick, bmax, st);
-            if (e == hipSuccess) e = launch_cell_list(P, s, c->w, st, tick, bmax);
+            if (e == hipSuccess) e = launch_cell_list(P, s, c->w, st, c->w.status, tick, bmax);
             if (e == hipSuccess)
                 e = launch_gravity(prec == SIDM_PREC_MIXED, P, c->w, s, 1, st, nullptr, nullptr,
                                    tick, bmax);
@@ -959,7 +959,7 @@ sidm_status sidm_autotune(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos,
             c->shape = cand;
             c->plan_valid = false;
             if ((r = enter(c, halos, n_halos, s, st, cap)) != SIDM_OK) break;
-            e = launch_cell_list(c->plan, s, c->w, st);
+            e = launch_cell_list(c->plan, s, c->w, st, nullptr);
             double ms = 1e300;
             const int runs = (flags & SIDM_TUNE_QUICK) ? 2 : 4;
             for (int rep = 0; rep < runs && e == hipSuccess; ++rep) {

@@ -20,9 +20,10 @@ constexpr int kGravThreads = 256;    // threads per gravity block
 constexpr int kGravTileJ = 256;      // j-particles per LDS tile
 constexpr int kTickSplit = 16;       // j-splits of a block-step tick
 constexpr int kSortBits = 8;         // radix digit width
-constexpr int kSortItems = 16;       // keys per thread per sort block
-constexpr int kSortBlock = 256;
-constexpr int kScanMaxSeg = 1024;   // blocks of the multi-block exclusive scan at most
+constexpr int kSortBlock = 256;      // threads per sort tile
+constexpr int kSortMaxPasses = 8;    // 64-bit keys
+constexpr int kRange = 8;            // box and mass range: min x, y, z, m, max x, y, z, m
+constexpr int64_t kSmallN = 8192;    // halos up to this size are sorted by one workgroup
 
 // Shape of the direct-sum gravity launch: i-particles per thread, threads per
 // block (also the j-particles of one LDS tile), and whether the blocks are

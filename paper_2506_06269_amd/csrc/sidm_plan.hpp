@@ -104,6 +104,7 @@ struct Scratch {
     int64_t nodes_cap = 0;        // bucket boxes + tree nodes
     // gravity
     double* bsum = nullptr;       // 7 doubles per streaming block
+    double* brange = nullptr;     // kRange doubles per streaming block
     double* cref = nullptr;       // per halo: the common mass if all are equal, else 0
     double* radius = nullptr;     // per halo: radius of the central density
     sidm_center* center = nullptr;    // per halo: centre of the tidal-radius search
@@ -129,9 +130,8 @@ struct Scratch {
     // cell list
     unsigned long long* keys[2] = {nullptr, nullptr};
     uint32_t* vals[2] = {nullptr, nullptr};
-    uint32_t* hist = nullptr;
-    uint32_t* scan_part = nullptr;    // segment sums of the histogram scan
-    int64_t hist_cap = 0;
+    uint32_t* sort_ws = nullptr;  // digit counts, tickets and tile words of the sort
+    int64_t sort_ws_n = 0;
     double *sx = nullptr, *sy = nullptr, *sz = nullptr;
     double4* sp4 = nullptr;       // sorted positions as (x, y, z, 0): one load per candidate
     double *svx = nullptr, *svy = nullptr, *svz = nullptr;
@@ -147,7 +147,6 @@ struct Scratch {
     int* sub_n = nullptr;         // sub-ranges per bucket
     double* cbox = nullptr;       // 6 per chunk, kChunks per bucket (searches only)
     double* chmax = nullptr;      // largest h per chunk, kChunks per bucket (pair search)
-    unsigned long long* skeys = nullptr;   // sorted keys (one of keys[0..1])
     double* hmax = nullptr;       // 1 per node
     // scattering
     unsigned long long* owner = nullptr;
@@ -172,7 +171,7 @@ struct Plan {
     bool any_scatter = false;         // some halo has sigma_m > 0
     GravShape shape;                  // launch shape of the direct-sum tiles
     int halo_bits = 0;                // bits of a halo index
-    int64_t sort_blocks = 0;
+    int64_t n_max = 0;                // particles of the largest halo
     std::vector<HaloDev> halos;
     std::vector<StreamBlock> blocks;
     std::vector<GravItem> items;          // one-sided: the halos without symmetric tiles first
@@ -187,6 +186,50 @@ struct Plan {
     int64_t level_task_off[kMaxLevels + 1] = {};   // tasks of level l: [off[l-1], off[l])
     std::vector<int> rank_of;
 };
+
+// The levels of the search tree above the wide ones: all of the first level
+// with at most kTopThreads nodes and those above it, in one launch (977 nodes
+// in one workgroup took 23 us, against 6 + 7 us with a launch of their own).
+constexpr int kTopThreads = 256;
+struct TopLevels {
+    int64_t off[kMaxLevels + 1];      // tasks of level l: [off[l - 1], off[l])
+    int first, n_levels;
+};
+inline TopLevels top_levels(const Plan& P)
+{
+    TopLevels T;
+    for (int l = 0; l <= kMaxLevels; ++l) T.off[l] = P.level_task_off[l];
+    T.n_levels = P.n_levels;
+    T.first = 1;
+    while (T.first < P.n_levels && T.off[T.first] - T.off[T.first - 1] > kTopThreads) ++T.first;
+    return T;
+}
+
+// Keys per thread of a sort tile: the smallest tile that gives at most one
+// tile per compute unit, up to 16 (a tile's time grows with its keys per
+// thread, the look-back with the number of tiles; per digit with 4, 8 and 16:
+// 8.4, 8.9 and 11.5 us at 65536 keys, 20.6, 15.7 and 16.8 at 500009, 35, 26 and
+// 22.7 at 2^20).
+constexpr int64_t kSortTiles = 256;
+constexpr int sort_items(int64_t n)
+{
+    return n <= kSortTiles * kSortBlock * 4 ? 4 : n <= kSortTiles * kSortBlock * 8 ? 8 : 16;
+}
+constexpr int64_t sort_tiles(int64_t n)
+{
+    const int64_t tile = (int64_t)kSortBlock * sort_items(n);
+    return (n + tile - 1) / tile;
+}
+// Words of sort_ws: digit counts and a ticket per pass, then a word per pass,
+// tile and digit; for any n up to N.
+constexpr int64_t kSortHead = kSortMaxPasses * (1 << kSortBits) + 64;
+constexpr int64_t sort_words(int64_t N)
+{
+    const int64_t small = (N + kSortBlock * 4 - 1) / (kSortBlock * 4);
+    const int64_t a = small < kSortTiles ? small : kSortTiles;
+    const int64_t b = (N + kSortBlock * 16 - 1) / (kSortBlock * 16);
+    return kSortHead + (int64_t)kSortMaxPasses * (a > b ? a : b) * (1 << kSortBits);
+}
 
 template <typename T>
 inline bool dalloc(T*& p, int64_t count)
@@ -260,15 +303,14 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
     w.partial_rows = gravity_partial_rows(N);
     w.buckets_cap = N / kBucket + H + 1;
     w.nodes_cap = w.buckets_cap * 2 + (int64_t)H * (kMaxLevels + 1);
-    const int64_t sort_blocks = N / (kSortBlock * kSortItems) + 1;
-    w.hist_cap = sort_blocks * (1 << kSortBits) + 1;
+    w.sort_ws_n = sort_words(N);
     bool ok = dalloc(w.halos, H) && dalloc(w.blocks, nb) && dalloc(w.items, w.items_cap) &&
               dalloc(w.buckets, w.buckets_cap) && dalloc(w.node_tasks, w.nodes_cap) && dalloc(w.nodes, w.nodes_cap) &&
-              dalloc(w.bsum, 7 * nb) && dalloc(w.cref, 4 * H) && dalloc(w.radius, H) && dalloc(w.center, H) &&
+              dalloc(w.bsum, 7 * nb) && dalloc(w.brange, kRange * nb) && dalloc(w.cref, 4 * H) && dalloc(w.radius, H) && dalloc(w.center, H) &&
               dalloc(w.tidal, 8 * H) && dalloc(w.bbox, 6 * H) &&
               dalloc(w.xm32, N) &&  dalloc(w.partial, w.partial_rows) && dalloc(w.keys[0], 2 * N) &&
               dalloc(w.vals[0], N) && dalloc(w.vals[1], N) &&
-              dalloc(w.hist, w.hist_cap) && dalloc(w.scan_part, kScanMaxSeg) && dalloc(w.sx, N) && dalloc(w.sy, N) &&
+              dalloc(w.sort_ws, w.sort_ws_n) && dalloc(w.sx, N) && dalloc(w.sy, N) &&
               dalloc(w.sz, N) && dalloc(w.sp4, N) && dalloc(w.svx, N) && dalloc(w.svy, N) && dalloc(w.svz, N) &&
               dalloc(w.sh, N) && dalloc(w.sm, N) && dalloc(w.bin, N) &&
               dalloc(w.mom, w.nodes_cap) && dalloc(w.mom2, 6 * w.nodes_cap) && dalloc(w.tree_terms, H) && dalloc(w.sid, N) && dalloc(w.perm, N) &&
@@ -313,8 +355,8 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
 inline void free_scratch(Scratch& w)
 {
     dfree(w.halos); dfree(w.blocks); dfree(w.items); dfree(w.buckets); dfree(w.node_tasks); dfree(w.nodes);
-    dfree(w.bsum); dfree(w.cref); dfree(w.radius); dfree(w.center); dfree(w.tidal); dfree(w.bbox); dfree(w.xm32);  dfree(w.partial);
-    dfree(w.keys[0]); w.keys[1] = nullptr; dfree(w.vals[0]); dfree(w.vals[1]); dfree(w.hist); dfree(w.scan_part);
+    dfree(w.bsum); dfree(w.brange); dfree(w.cref); dfree(w.radius); dfree(w.center); dfree(w.tidal); dfree(w.bbox); dfree(w.xm32);  dfree(w.partial);
+    dfree(w.keys[0]); w.keys[1] = nullptr; dfree(w.vals[0]); dfree(w.vals[1]); dfree(w.sort_ws);
     dfree(w.sx); dfree(w.sy); dfree(w.sz); dfree(w.sp4); dfree(w.svx); dfree(w.svy); dfree(w.svz);
     dfree(w.items_tick); dfree(w.partial_tick);
     w.items_tick_cap = w.partial_tick_rows = 0;
@@ -575,6 +617,7 @@ inline bool build_plan(Plan& P, const Scratch& w, const sidm_halo* halos, int32_
         if (S.sigma_m > 0.0) P.any_scatter = true;
         H.sbase = sbase[h];
         H.rank = P.rank_of[h];
+        P.n_max = std::max(P.n_max, H.n);
         // streaming blocks
         H.stream_block0 = (int64_t)P.blocks.size();
         for (int64_t s0 = 0; s0 < S.n; s0 += kStreamBlock)
@@ -702,7 +745,6 @@ inline bool build_plan(Plan& P, const Scratch& w, const sidm_halo* halos, int32_
         if (H.max_bin > 0 && !(H.tree_alpha > 0.0)) P.rank_shift = 49;
     P.key_bits = P.rank_shift + hb;
     P.halo_bits = hb;
-    P.sort_blocks = (P.n_sorted + kSortBlock * kSortItems - 1) / (kSortBlock * kSortItems);
     if (prow > w.partial_rows || P.n_items > w.items_cap || P.n_blocks > w.blocks_cap ||
         P.n_buckets > w.buckets_cap || P.n_nodes > w.nodes_cap ||
         (int64_t)P.node_tasks.size() > w.nodes_cap) {

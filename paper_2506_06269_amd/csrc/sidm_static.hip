@@ -16,7 +16,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
                           hipStream_t st, hipEvent_t tile_begin, hipEvent_t tile_end, int tick = 0,
                           int bmax = 0);
 hipError_t launch_cell_list(const Plan& plan, const sidm_state* s, Scratch& w, hipStream_t st,
-                            int tick = 0, int bmax = 0);
+                            int* status, int tick = 0, int bmax = 0);
 int64_t gravity_slots(int device);
 
 namespace {
@@ -28,13 +28,11 @@ constexpr int64_t kBlocksMax = kMaxN / kStreamBlock + 1;
 constexpr int64_t kBucketsMax = kMaxN / kBucket + 1;
 constexpr int64_t kNodesMax = 2 * kBucketsMax + kMaxLevels + 1;
 constexpr int64_t kItemsMax = kMaxSplit * (kMaxN / kIBlock + 1);
-constexpr int64_t kSortBlocksMax = kMaxN / (kSortBlock * kSortItems) + 1;
-constexpr int64_t kHistMax = kSortBlocksMax * (1 << kSortBits) + 1;
 
 // Byte offsets of the buffers inside the array (each aligned to 256 bytes).
 struct Layout {
-    size_t halos, blocks, items, buckets, node_tasks, nodes, bsum, cref, bbox, xm32, partial;
-    size_t keys0, keys1, vals0, vals1, hist, scan_part, sx, sy, sz, sp4, sh, sm, perm, box, sub,
+    size_t halos, blocks, items, buckets, node_tasks, nodes, brange, cref, bbox, xm32, partial;
+    size_t keys0, keys1, vals0, vals1, sort_ws, sx, sy, sz, sp4, sh, sm, perm, box, sub,
         sub_n, total;
 };
 
@@ -55,7 +53,7 @@ constexpr Layout make_layout()
     L.buckets = take(off, sizeof(BucketInfo) * kBucketsMax);
     L.node_tasks = take(off, sizeof(NodeTask) * kNodesMax);
     L.nodes = take(off, sizeof(NodeChild) * kNodesMax);
-    L.bsum = take(off, sizeof(double) * 7 * kBlocksMax);
+    L.brange = take(off, sizeof(double) * kRange * kBlocksMax);
     L.cref = take(off, sizeof(double) * 4);
     L.bbox = take(off, sizeof(double) * 6);
     L.xm32 = take(off, sizeof(float) * 4 * kMaxN);
@@ -64,8 +62,7 @@ constexpr Layout make_layout()
     L.keys1 = take(off, sizeof(unsigned long long) * kMaxN);
     L.vals0 = take(off, sizeof(uint32_t) * kMaxN);
     L.vals1 = take(off, sizeof(uint32_t) * kMaxN);
-    L.hist = take(off, sizeof(uint32_t) * kHistMax);
-    L.scan_part = take(off, sizeof(uint32_t) * kScanMaxSeg);
+    L.sort_ws = take(off, sizeof(uint32_t) * sort_words(kMaxN));
     L.sx = take(off, sizeof(double) * kMaxN);
     L.sy = take(off, sizeof(double) * kMaxN);
     L.sz = take(off, sizeof(double) * kMaxN);
@@ -125,7 +122,7 @@ void carve(Scratch& w, unsigned char* base)
     w.buckets = (BucketInfo*)(base + L.buckets);
     w.node_tasks = (NodeTask*)(base + L.node_tasks);
     w.nodes = (NodeChild*)(base + L.nodes);
-    w.bsum = (double*)(base + L.bsum);
+    w.brange = (double*)(base + L.brange);
     w.cref = (double*)(base + L.cref);
     w.bbox = (double*)(base + L.bbox);
     w.xm32 = (float4*)(base + L.xm32);
@@ -134,8 +131,8 @@ void carve(Scratch& w, unsigned char* base)
     w.keys[1] = (unsigned long long*)(base + L.keys1);
     w.vals[0] = (uint32_t*)(base + L.vals0);
     w.vals[1] = (uint32_t*)(base + L.vals1);
-    w.hist = (uint32_t*)(base + L.hist);
-    w.scan_part = (uint32_t*)(base + L.scan_part);
+    w.sort_ws = (uint32_t*)(base + L.sort_ws);
+    w.sort_ws_n = sort_words(kMaxN);
     w.sx = (double*)(base + L.sx);
     w.sy = (double*)(base + L.sy);
     w.sz = (double*)(base + L.sz);
@@ -288,7 +285,7 @@ extern "C" sidm_status sidm_gravity_static(const sidm_halo* halo, const sidm_sta
     P.n_items = split * n_ib;
     P.key_bits = 48;
     P.rank_shift = 48;
-    P.sort_blocks = (n + kSortBlock * kSortItems - 1) / (kSortBlock * kSortItems);
+    P.n_max = n;
 
     Scratch w;
     carve(w, D.ptr);
@@ -304,7 +301,7 @@ extern "C" sidm_status sidm_gravity_static(const sidm_halo* halo, const sidm_sta
     local.vx = local.vy = local.vz = nullptr;
     local.id = nullptr;
     local.h = nullptr;
-    if (e == hipSuccess) e = launch_cell_list(P, &local, w, st);
+    if (e == hipSuccess) e = launch_cell_list(P, &local, w, st, nullptr);
     if (e == hipSuccess)
         e = launch_gravity(prec == SIDM_PREC_MIXED, P, w, &local, 0, st, nullptr, nullptr);
     if (e != hipSuccess) return fail(SIDM_ERR_HIP, "gravity launch: %s", hipGetErrorString(e));
