@@ -610,6 +610,12 @@ __global__ __launch_bounds__(NT, kSymWaves) void k_grav_sym(
     const double* __restrict__ cmass, int n_halos, unsigned long long* __restrict__ acc)
 {
     __shared__ SymLds<IREG, NT> L;
+    // nothing to do unless some halo has masses of this kind (the items of
+    // 2^20 particles took 0.41 ms to pass over)
+    int mine = 0;
+    for (int h = threadIdx.x; h < n_halos; h += NT)
+        if ((cmass[h] > 0.0) == EQM) mine = 1;
+    if (!__syncthreads_or(mine)) return;
     for (;;) {
         __syncthreads();   // every thread has read the previous `next`
         if (threadIdx.x == 0) L.next = (int64_t)atomicAdd(ticket, 1ull);
