@@ -401,15 +401,16 @@ sidm_status sidm_set_launch_shape(sidm_ctx *ctx, int32_t ireg, int32_t threads,
                                   int32_t persistent);
 
 /* Symmetric tiles.  The softened pair force of the direct sum (Sec. 2) is
- * antisymmetric: the force of j on i is minus that of i on j.  In mixed precision
- * the direct sum of a halo of at least min_n particles evaluates each
- * unordered pair once and applies it to both members; the reactions are
- * summed in 64-bit fixed point with integer atomics, so the result is
- * deterministic: it does not depend on the order in which the work items
- * finish.  The results agree with the one-sided tiles to FP32 rounding.
+ * antisymmetric: the force of j on i is minus that of i on j.  The direct sum of
+ * a halo of at least min_n particles (FP64: at least min_n and 40960) evaluates
+ * each unordered pair once and applies it to both members; the reactions are
+ * summed in fixed point (64 bits, FP64 128) with integer atomics, so the result
+ * is deterministic: it does not depend on the order in which the work items
+ * finish.  The results agree with the one-sided tiles to FP32 (FP64) rounding.
  * Halos need a softening eps > 0.  min_n = 0 turns them off; the default is
- * 4096.  FP64, tree halos and the ticks of a cycle of block time steps
- * (when some direct-sum halo has max_bin > 0) use the one-sided sums.
+ * 4096.  Tree halos, the ticks of a cycle of block time steps (when some
+ * direct-sum halo has max_bin > 0) and, in FP64, a halo with a value that is
+ * not finite or whose box is over 2^20 eps use the one-sided sums.
  * Changing it invalidates graphs captured before.  SIDM_ERR_INVALID for
  * min_n < 0. */
 sidm_status sidm_set_symmetric(sidm_ctx *ctx, int64_t min_n);

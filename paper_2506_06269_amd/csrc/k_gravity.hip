@@ -631,20 +631,18 @@ __global__ __launch_bounds__(NT, kSymWaves) void k_grav_sym(
     }
 }
 
-// Zero fixed-point totals of the particles of halos that take the symmetric tiles.
+// Zero fixed-point totals (`words` per particle) of the particles of halos that
+// take the symmetric tiles of this kind.
 __global__ __launch_bounds__(kStreamBlock) void k_sym_zero(const StreamBlock* __restrict__ blocks,
                                                            const HaloDev* __restrict__ halos,
-                                                           unsigned long long* __restrict__ acc)
+                                                           unsigned long long* __restrict__ acc,
+                                                           int kind, int words)
 {
     const StreamBlock B = blocks[blockIdx.x];
-    const int t = threadIdx.x;
     const HaloDev& H = halos[B.halo];
-    if (t >= B.count || !H.grav_sym) return;
-    const int64_t p = H.sbase + (B.start - H.offset) + t;
-    acc[4 * p + 0] = 0ull;
-    acc[4 * p + 1] = 0ull;
-    acc[4 * p + 2] = 0ull;
-    acc[4 * p + 3] = 0ull;
+    if (!(H.grav_sym & kind)) return;
+    unsigned long long* a = acc + words * (H.sbase + (B.start - H.offset));
+    for (int q = threadIdx.x; q < words * B.count; q += kStreamBlock) a[q] = 0ull;
 }
 
 // ---------------------------------------------------------------- FP64 tiles
@@ -745,6 +743,8 @@ __device__ inline void grav_fp64_body(const double* __restrict__ x, const double
     }
 }
 
+// sym_ok given: the halos whose FP64 sums the symmetric tiles have taken (see
+// put_mass) are passed over.
 template <int IREG, int NT, bool PERSIST>
 __global__ __launch_bounds__(NT) void k_grav_fp64(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
     unsigned long long* __restrict__ ticket, const HaloDev* __restrict__ halos,
     const double* __restrict__ cmass, double4* __restrict__ partial,
     const int8_t* __restrict__ bin, const uint32_t* __restrict__ perm, int tick, int bmax,
-    int tick_rows)
+    int tick_rows, const double* __restrict__ sym_ok)
 {
     __shared__ double4 tile[NT];
     __shared__ int64_t next;
@@ -767,7 +767,8 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
         }
         const GravItem it = items[k];
         const HaloDev& H = halos[it.halo];
-        if (item_active<IREG, NT>(it, H, bin, perm, tick, bmax)) {
+        const bool sym = sym_ok && (H.grav_sym & kSymFp64) && sym_ok[it.halo] != 0.0;
+        if (!sym && item_active<IREG, NT>(it, H, bin, perm, tick, bmax)) {
             const int64_t pbase = tick_rows ? H.tick_part_base : H.part_base;
             const double meq = cmass[it.halo];
             if (meq > 0.0)
@@ -776,6 +777,299 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
                 grav_fp64_body<IREG, NT, false>(x, y, z, m, it, H, 1.0, partial, tile, pbase);
         }
         if (!PERSIST) return;
+    }
+}
+
+// ---------------------------------------------------------------- symmetric FP64 tiles
+// The scheme of k_grav_sym in FP64 (the same work items).  Bound by the FP64
+// vector rate, one instruction per four cycles and SIMD: a pair takes 20
+// instructions and a v_rsq_f64 for both directions, where the one-sided tiles
+// take 16 and one for each; the sum of a j's reaction over the wave adds 63
+// instructions per four j, so more i-particles per thread are better.  Forces
+// of 524288 particles in 8 x 256: 100 ms (57 cycles per wave and interaction;
+// the instructions alone 53), 4 x 256 108 ms, one-sided 158 ms.  The atomics
+// take some 6 % (half of them taken out: 97 ms); they go up steeply with their
+// number (i-side sums flushed every 2048, 512 and 256 j: 26.2, 29.8 and 52 ms at
+// 262144), so those sums are kept in two levels, a tile's and the item's (one
+// plain sum over 2048 j showed in the error against the oracle).  Items cut finer for halos of 16384 to 32768 were slower (the
+// i-side flushes).
+//
+// The totals are 128-bit fixed point in two words that never carry into each
+// other: x = v 2^s is cut into its nearest integer and the remainder times
+// 2^kSymLow, each summed with integer atomics, so that the result does not
+// depend on the order in which items finish and keeps what FP64 holds of
+// every partial sum (a single word of 64 bits would round them at 2^-61 of the
+// bound, 10^-10 of the force on a particle at a halo's edge).
+constexpr int kSymLow = 44;
+
+__device__ inline void fixed_add(unsigned long long* a, double x)
+{
+    const double hi = rint(x);
+    atomicAdd(a + 0, (unsigned long long)(long long)hi);
+    atomicAdd(a + 1, (unsigned long long)(long long)rint((x - hi) * 0x1p44));
+}
+
+__device__ inline double fixed_value(const long long* q)
+{
+    return (double)q[0] + (double)q[1] * 0x1p-44;
+}
+
+struct Words {
+    int lo, hi;
+};
+__device__ inline Words words_of(double v)
+{
+    const long long u = __double_as_longlong(v);
+    return {(int)u, (int)(u >> 32)};
+}
+__device__ inline double of_words(int lo, int hi)
+{
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// swap32_add and swap16_add of doubles
+__device__ inline double swap32_add(double a, double b)
+{
+    const Words p = words_of(a), q = words_of(b);
+    const auto l = __builtin_amdgcn_permlane32_swap(p.lo, q.lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(p.hi, q.hi, false, false);
+    return of_words(l[0], h[0]) + of_words(l[1], h[1]);
+}
+__device__ inline double swap16_add(double a, double b)
+{
+    const Words p = words_of(a), q = words_of(b);
+    const auto l = __builtin_amdgcn_permlane16_swap(p.lo, q.lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(p.hi, q.hi, false, false);
+    return of_words(l[0], h[0]) + of_words(l[1], h[1]);
+}
+
+// The banks (of four lanes per row) in MASK take v moved by CTRL, the others
+// keep old.
+template <int CTRL, int MASK>
+__device__ inline double dpp_into(double old, double v)
+{
+    const Words o = words_of(old), p = words_of(v);
+    return of_words(__builtin_amdgcn_update_dpp(o.lo, p.lo, CTRL, 0xF, MASK, false),
+                    __builtin_amdgcn_update_dpp(o.hi, p.hi, CTRL, 0xF, MASK, false));
+}
+
+// The same, the other banks left undefined.
+template <int CTRL, int MASK>
+__device__ inline double dpp_only(double v)
+{
+    const Words p = words_of(v);
+    return of_words(__builtin_amdgcn_mov_dpp(p.lo, CTRL, 0xF, MASK, false),
+                    __builtin_amdgcn_mov_dpp(p.hi, CTRL, 0xF, MASK, false));
+}
+
+constexpr int kDppKeep = 0xE4;   // quad_perm [0, 1, 2, 3]
+
+// v[4 j + c] (slot j < 4; c = x, y, z, phi) summed over the wave: bank b of row
+// q returns, on each of its four lanes, the total of component sym_row_comp(q)
+// of slot sym_bank_slot(b).  Every stage halves the values a lane holds.
+__device__ inline int sym_bank_slot(int bank) { return ((bank & 1) << 1) | (bank >> 1); }
+
+__device__ inline double wave_sum4(const double (&v)[16])
+{
+    double u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        u[j] = swap16_add(swap32_add(v[4 * j], v[4 * j + 1]),
+                          swap32_add(v[4 * j + 2], v[4 * j + 3]));
+    double w[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        // lanes 0-7 of a row: slot 2j, lanes 8-15: slot 2j + 1
+        const double mine = dpp_into<kDppKeep, 0xC>(u[2 * j], u[2 * j + 1]);
+        const double other =
+            dpp_into<0x128, 0xC>(dpp_only<0x128, 0x3>(u[2 * j]), u[2 * j + 1]);   // row_ror:8
+        w[j] = mine + other;
+    }
+    // banks 0 and 2: w[0], banks 1 and 3: w[1]
+    const double mine = dpp_into<kDppKeep, 0xA>(w[0], w[1]);
+    const double other = dpp_into<0x124, 0xA>(dpp_only<0x12C, 0x5>(w[0]), w[1]);
+    double x = mine + other;
+    x += dpp_only<0x4E, 0xF>(x);   // quad_perm [2, 3, 0, 1]
+    x += dpp_only<0xB1, 0xF>(x);   // quad_perm [1, 0, 3, 2]
+    return x;
+}
+
+// The pairs of the i-particles with the first jn j of the tile (a multiple of
+// four): as tile_sym.
+template <int IREG, bool EQM>
+__device__ inline void tile_sym64(const double4* __restrict__ tile, int jn, const double* xi,
+                                  const double* yi, const double* zi, const double* mi,
+                                  double eps2, double* px, double* py, double* pz, double* pp,
+                                  double (*jp)[4], int lane)
+{
+    const int comp = sym_row_comp(lane >> 4), slot = sym_bank_slot((lane & 15) >> 2);
+    for (int g = 0; g < jn; g += 4) {
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double4 p = tile[g + q];
+            double rx = 0.0, ry = 0.0, rz = 0.0, rp = 0.0;
+#pragma unroll
+            for (int r = 0; r < IREG; ++r) {
+                // two pairs in flight: left alone the compiler interleaves all
+                // of a j's pairs and spills
+                if (r % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+                const double dx = p.x - xi[r], dy = p.y - yi[r], dz = p.z - zi[r];
+                const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
+                const double rinv = rsqrt_pos(r2);
+                const double w = rinv * (rinv * rinv);
+                if (EQM) {
+                    px[r] = fma(w, dx, px[r]);
+                    py[r] = fma(w, dy, py[r]);
+                    pz[r] = fma(w, dz, pz[r]);
+                    pp[r] += rinv;
+                    rx = fma(w, dx, rx);
+                    ry = fma(w, dy, ry);
+                    rz = fma(w, dz, rz);
+                    rp += rinv;
+                } else {
+                    const double wj = p.w * w, wi = mi[r] * w;
+                    px[r] = fma(wj, dx, px[r]);
+                    py[r] = fma(wj, dy, py[r]);
+                    pz[r] = fma(wj, dz, pz[r]);
+                    pp[r] = fma(p.w, rinv, pp[r]);
+                    rx = fma(wi, dx, rx);
+                    ry = fma(wi, dy, ry);
+                    rz = fma(wi, dz, rz);
+                    rp = fma(mi[r], rinv, rp);
+                }
+            }
+            v[4 * q + 0] = rx;
+            v[4 * q + 1] = ry;
+            v[4 * q + 2] = rz;
+            v[4 * q + 3] = rp;
+        }
+        // all four lanes of a bank store its total: a branch here makes the
+        // compiler sink sums behind it and spill
+        jp[g + slot][comp] = wave_sum4(v);
+    }
+}
+
+template <int NT>
+struct SymLds64 {
+    double4 tile[NT];
+    double jpart[NT / 64][NT][4];
+    int64_t next;
+};
+
+template <int IREG, int NT, bool EQM>
+__device__ inline void grav_sym64_body(const double* __restrict__ x, const double* __restrict__ y,
+                                       const double* __restrict__ z, const double* __restrict__ m,
+                                       const SymItem& it, const HaloDev& H, double mref,
+                                       unsigned long long* __restrict__ acc, SymLds64<NT>& L)
+{
+    constexpr int NW = NT / 64;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const double eps2 = H.eps2;
+    const int64_t il0 = it.i0 - H.offset;
+    double sa, sp;
+    sym_scales(H, mref, sa, sp);
+    double xi[IREG], yi[IREG], zi[IREG], mi[IREG];
+    double sx[IREG], sy[IREG], sz[IREG], sq[IREG];   // sums over the item's tiles
+#pragma unroll
+    for (int r = 0; r < IREG; ++r) {
+        const int64_t li = il0 + (int64_t)r * NT + t;
+        xi[r] = yi[r] = zi[r] = mi[r] = 0.0;
+        if (li < H.n) {
+            const int64_t p = H.sbase + li;
+            xi[r] = x[p]; yi[r] = y[p]; zi[r] = z[p];
+            if (!EQM) mi[r] = m[p];
+        }
+        sx[r] = sy[r] = sz[r] = sq[r] = 0.0;
+    }
+    for (int64_t j0 = it.j0; j0 < it.j1; j0 += NT) {
+        const int64_t lj0 = j0 - H.offset;
+        // padding as in the one-sided tiles (no weight on either side)
+        double4 pj = make_double4(1.0e150, 1.0e150, 1.0e150, 0.0);
+        if (j0 + t < it.j1) {
+            const int64_t p = H.sbase + lj0 + t;
+            pj = make_double4(x[p], y[p], z[p], m[p]);
+        }
+        __syncthreads();
+        L.tile[t] = pj;
+        __syncthreads();
+        const bool diag = j0 < it.i0 + (int64_t)IREG * NT;   // inside the i-block
+        const int nj = (int)(it.j1 - j0 < NT ? it.j1 - j0 : NT);
+        double px[IREG], py[IREG], pz[IREG], pp[IREG];
+#pragma unroll
+        for (int r = 0; r < IREG; ++r) px[r] = py[r] = pz[r] = pp[r] = 0.0;
+        if (diag)
+            tile_f64<IREG, NT, EQM, true>(L.tile, xi, yi, zi, eps2, j0, it.i0, t, px, py, pz, pp);
+        else
+            tile_sym64<IREG, EQM>(L.tile, (nj + 3) & ~3, xi, yi, zi, mi, eps2, px, py, pz, pp,
+                                  L.jpart[wave], lane);
+#pragma unroll
+        for (int r = 0; r < IREG; ++r) {
+            sx[r] += px[r];
+            sy[r] += py[r];
+            sz[r] += pz[r];
+            sq[r] += pp[r];
+        }
+        if (!diag) {
+            __syncthreads();
+            if (t < nj) {
+                double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    s0 += L.jpart[w][t][0];
+                    s1 += L.jpart[w][t][1];
+                    s2 += L.jpart[w][t][2];
+                    s3 += L.jpart[w][t][3];
+                }
+                unsigned long long* a = acc + 8 * (H.sbase + lj0 + t);
+                fixed_add(a + 0, -s0 * sa);
+                fixed_add(a + 2, -s1 * sa);
+                fixed_add(a + 4, -s2 * sa);
+                fixed_add(a + 6, s3 * sp);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < IREG; ++r) {
+        const int64_t li = il0 + (int64_t)r * NT + t;
+        if (li < H.n) {
+            unsigned long long* a = acc + 8 * (H.sbase + li);
+            fixed_add(a + 0, sx[r] * sa);
+            fixed_add(a + 2, sy[r] * sa);
+            fixed_add(a + 4, sz[r] * sa);
+            fixed_add(a + 6, sq[r] * sp);
+        }
+    }
+}
+
+// As k_grav_sym; halos that the fixed-point totals cannot hold (sym_ok, see
+// put_mass) are left to the one-sided tiles.
+template <int IREG, int NT, bool EQM>
+__global__ __launch_bounds__(NT, IREG >= 8 ? 2 : 3) void k_grav_sym64(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const double* __restrict__ m, const SymItem* __restrict__ items, int64_t n_items,
+    unsigned long long* __restrict__ ticket, const HaloDev* __restrict__ halos,
+    const double* __restrict__ cmass, int n_halos, unsigned long long* __restrict__ acc)
+{
+    __shared__ SymLds64<NT> L;
+    const double* __restrict__ sym_ok = cmass + 2 * n_halos;
+    auto takes = [&](int h) {
+        return (halos[h].grav_sym & kSymFp64) && sym_ok[h] != 0.0 && (cmass[h] > 0.0) == EQM;
+    };
+    int mine = 0;
+    for (int h = threadIdx.x; h < n_halos; h += NT)
+        if (takes(h)) mine = 1;
+    if (!__syncthreads_or(mine)) return;
+    for (;;) {
+        __syncthreads();   // every thread has read the previous `next`
+        if (threadIdx.x == 0) L.next = (int64_t)atomicAdd(ticket, 1ull);
+        __syncthreads();
+        const int64_t k = L.next;
+        if (k >= n_items) return;
+        const SymItem it = items[k];
+        if (!takes(it.halo)) continue;   // uniform over the block
+        grav_sym64_body<IREG, NT, EQM>(x, y, z, m, it, halos[it.halo],
+                                       EQM ? 1.0 : cmass[n_halos + it.halo], acc, L);
     }
 }
 
@@ -797,7 +1091,7 @@ __global__ __launch_bounds__(kStreamBlock) void k_grav_finalize(
     double* __restrict__ vz, double* __restrict__ svx, double* __restrict__ svy,
     double* __restrict__ svz, int kick, int8_t* __restrict__ bin, int tick, int bmax,
     const double4* __restrict__ partial_tick, const unsigned long long* __restrict__ symacc,
-    const double* __restrict__ cmass, int n_halos)
+    const double* __restrict__ cmass, int n_halos, int kind)
 {
 #pragma clang fp contract(off)
     const StreamBlock B = blocks[blockIdx.x];
@@ -820,17 +1114,25 @@ __global__ __launch_bounds__(kStreamBlock) void k_grav_finalize(
     const int64_t rbase = trow ? H.tick_part_base : H.part_base;
     const int nrow = trow ? H.tick_split : H.grav_split;
     double sx = 0, sy = 0, sz = 0, sp = 0;
-    if (symacc && H.grav_sym) {
+    if (symacc && (H.grav_sym & kind) &&
+        (kind == kSymMixed || cmass[2 * n_halos + B.halo] != 0.0)) {
         // the fixed-point totals of the symmetric tiles
         const double meq = cmass[B.halo];
         double sa, spp;
         sym_scales(H, meq > 0.0 ? 1.0 : cmass[n_halos + B.halo], sa, spp);
-        const long long* q = (const long long*)symacc + 4 * p;
+        const long long* q = (const long long*)symacc + (kind == kSymMixed ? 4 : 8) * p;
         const double ms = meq > 0.0 ? meq : 1.0;
-        sx = ms * ((double)q[0] / sa);
-        sy = ms * ((double)q[1] / sa);
-        sz = ms * ((double)q[2] / sa);
-        sp = ms * ((double)q[3] / spp);
+        if (kind == kSymMixed) {
+            sx = ms * ((double)q[0] / sa);
+            sy = ms * ((double)q[1] / sa);
+            sz = ms * ((double)q[2] / sa);
+            sp = ms * ((double)q[3] / spp);
+        } else {
+            sx = ms * (fixed_value(q + 0) / sa);
+            sy = ms * (fixed_value(q + 2) / sa);
+            sz = ms * (fixed_value(q + 4) / sa);
+            sp = ms * (fixed_value(q + 6) / spp);
+        }
     } else {
         for (int s = 0; s < nrow; ++s) {
             const double4 q = rows[rbase + (int64_t)s * H.n + li];
@@ -906,13 +1208,18 @@ int64_t gravity_slots(int device) { return gravity_slots(device, GravShape{}, tr
 // f(kernel pointer, threads) for each.  About
 // eight pairs per cross-lane reduction: j-slots per reduction 1, 2 or 4 for
 // 8, 4 or 2 i-particles per thread.
-template <class F>
+template <bool MIXED, class F>
 static bool with_sym_shape(int ireg, int nt, F f)
 {
 #define SIDM_SYM(I, T)                                                                        \
     if (ireg == I && nt == T) {                                                               \
-        f(k_grav_sym<I, T, (I >= 8 ? 1 : 8 / I), true>, T);                                   \
-        f(k_grav_sym<I, T, (I >= 8 ? 1 : 8 / I), false>, T);                                  \
+        if constexpr (MIXED) {                                                                \
+            f(k_grav_sym<I, T, (I >= 8 ? 1 : 8 / I), true>, T);                               \
+            f(k_grav_sym<I, T, (I >= 8 ? 1 : 8 / I), false>, T);                              \
+        } else {                                                                              \
+            f(k_grav_sym64<I, T, true>, T);                                                   \
+            f(k_grav_sym64<I, T, false>, T);                                                  \
+        }                                                                                     \
         return true;                                                                          \
     }
     SIDM_SYM(2, 128) SIDM_SYM(4, 128) SIDM_SYM(8, 128)
@@ -924,17 +1231,19 @@ static bool with_sym_shape(int ireg, int nt, F f)
 
 // Blocks of the symmetric tiles of a launch shape the device holds at once,
 // or 0 if unknown.
-int64_t gravity_sym_slots(int device, const GravShape& shape)
+int64_t gravity_sym_slots(int device, const GravShape& shape, bool mixed)
 {
     int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
         return 0;
     hipError_t e = hipErrorInvalidValue;
     bool first = true;   // the common-mass kernel: the one that runs the benchmark halos
-    with_sym_shape(shape.ireg, shape.nt, [&](auto kern, int threads) {
+    auto query = [&](auto kern, int threads) {
         if (first) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, 0);
         first = false;
-    });
+    };
+    if (mixed) with_sym_shape<true>(shape.ireg, shape.nt, query);
+    else with_sym_shape<false>(shape.ireg, shape.nt, query);
     return e == hipSuccess ? (int64_t)cus * per_cu : 0;
 }
 
@@ -963,37 +1272,48 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
         if (tick == 0 && P.n_items == 0 && tile_end) (void)hipEventRecord(tile_end, st);
     }
     // a tick of block steps runs the finer tick items into their own rows; any
-    // other mixed evaluation runs the symmetric tiles for the halos that take
-    // them and the one-sided tiles for the rest (their items come first in the
-    // item table).  Without tick items no direct-sum halo has block steps, so
+    // other evaluation runs the symmetric tiles for the halos that take them
+    // and the one-sided tiles for the rest (in mixed precision their items come
+    // first in the item table; the FP64 ones pass over what the symmetric tiles
+    // took, which only the device knows).  Without tick items no direct-sum halo has block steps, so
     // all of their particles are active at every tick.
     // The last tick of a cycle steps every particle of every halo: it runs the
     // whole evaluation (the symmetric tiles where they apply) instead of the
     // tick items.
     const bool full_tick = tick > 0 && tick == (1 << bmax);
     const bool tk = tick > 0 && !full_tick && !P.items_tick.empty();
-    const bool sym = mixed && !tk && P.n_sym_items > 0;
+    const bool sym = !tk && (mixed ? P.n_sym_items > 0 : P.any_sym64);
+    const int kind = mixed ? kSymMixed : kSymFp64;
     const GravItem* items = tk ? w.items_tick : w.items;
     const int64_t n_items =
-        tk ? (int64_t)P.items_tick.size() : (sym ? P.n_items_nosym : P.n_items);
+        tk ? (int64_t)P.items_tick.size() : (sym && mixed ? P.n_items_nosym : P.n_items);
     double4* rows = tk ? w.partial_tick : w.partial;
     unsigned long long* ticket = &w.counters->ticket;
     if (mixed && (n_items > 0 || sym))
         hipLaunchKernelGGL(k_pack_frames, dim3(nb), dim3(kStreamBlock), 0, st, w.sx, w.sy, w.sz,
                            w.sm, w.blocks, w.halos, w.sub, w.sub_n, w.xm32);
     if (sym) {
-        if (w.slots_sym <= 0 || !w.symacc || !w.sym_items) return hipErrorInvalidValue;
+        const int64_t slots = mixed ? w.slots_sym : w.slots_sym64;
+        if (slots <= 0 || !w.symacc || !w.sym_items) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_sym_zero, dim3(nb), dim3(kStreamBlock), 0, st, w.blocks, w.halos,
-                           w.symacc);
+                           w.symacc, kind, mixed ? 4 : 8);
         if (tile_begin) (void)hipEventRecord(tile_begin, st);
         tile_begin = nullptr;
-        const unsigned grid = (unsigned)std::min<int64_t>(w.slots_sym, P.n_sym_items);
-        const bool ok = with_sym_shape(P.shape.ireg, P.shape.nt, [&](auto kern, int threads) {
+        const unsigned grid = (unsigned)std::min<int64_t>(slots, P.n_sym_items);
+        auto launch_mixed = [&](auto kern, int threads) {
             hipLaunchKernelGGL(k_ticket_reset, dim3(1), dim3(64), 0, st, w.counters);
             hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, w.xm32, w.sub, w.sub_n,
                                w.sym_items, P.n_sym_items, ticket, w.halos, w.cref, P.n_halos,
                                w.symacc);
-        });
+        };
+        auto launch_fp64 = [&](auto kern, int threads) {
+            hipLaunchKernelGGL(k_ticket_reset, dim3(1), dim3(64), 0, st, w.counters);
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, w.sx, w.sy, w.sz, w.sm,
+                               w.sym_items, P.n_sym_items, ticket, w.halos, w.cref, P.n_halos,
+                               w.symacc);
+        };
+        const bool ok = mixed ? with_sym_shape<true>(P.shape.ireg, P.shape.nt, launch_mixed)
+                              : with_sym_shape<false>(P.shape.ireg, P.shape.nt, launch_fp64);
         if (!ok) return hipErrorInvalidValue;
         if (n_items == 0 && tile_end) (void)hipEventRecord(tile_end, st);
     }
@@ -1016,7 +1336,8 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
         auto launch_fp64 = [&](auto kern, int threads) {
             hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, w.sx, w.sy, w.sz, w.sm,
                                items, n_items, ticket, w.halos, w.cref, rows, w.bin, w.perm,
-                               tick, bmax, tk ? 1 : 0);
+                               tick, bmax, tk ? 1 : 0,
+                               sym ? w.cref + 2 * P.n_halos : (const double*)nullptr);
         };
         bool ok;
         if (mixed)
@@ -1032,7 +1353,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
                        w.partial, w.perm, s->x, s->y, s->z, s->ax, s->ay, s->az, s->pot, s->vx,
                        s->vy, s->vz, w.svx, w.svy, w.svz, kick, w.bin, tick, bmax,
                        tk ? w.partial_tick : nullptr, sym ? w.symacc : nullptr, w.cref,
-                       P.n_halos);
+                       P.n_halos, kind);
     return hipGetLastError();
 }
 

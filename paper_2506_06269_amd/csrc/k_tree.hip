@@ -77,18 +77,29 @@ __device__ inline void block_range(double (&e)[kRange], double* red)
     }
 }
 
-// The common mass of a halo (cmass[h], 0 when its masses differ) and its
-// largest (cmass[n_halos + h]).  With a status array, a halo that scatters
+// The common mass of a halo (cmass[h], 0 when its masses differ), the largest
+// magnitude of its masses (cmass[n_halos + h]), and whether the FP64 symmetric
+// tiles can sum it (cmass[2 n_halos + h]): their fixed-point totals need finite
+// values and scales, and hold a sum to 2^-104 of its bound n m 0.385 / eps^2,
+// which is below 2^-63 of n m / R^2, the least force scale of a box of side R,
+// for R up to 2^20 eps (workloads: 10^3 to 10^4).  With a status array, a halo that scatters
 // (sigma_m > 0) without a common mass is flagged: the probability of a pair
 // takes the mass of one member, which is only symmetric when the masses are
 // equal (each run of the paper's Table 1 has one particle mass), so such a
 // halo is not scattered.
-__device__ inline void put_mass(const HaloDev& H, int h, int n_halos, double lo, double hi,
+__device__ inline void put_mass(const HaloDev& H, int h, int n_halos, const double (&e)[kRange],
                                 double* __restrict__ cmass, int* __restrict__ status)
 {
+    const double lo = e[3], hi = e[7], top = fmax(fabs(lo), fabs(hi));
     const bool equal = lo == hi;
     cmass[h] = equal ? lo : 0.0;
-    cmass[n_halos + h] = hi;
+    cmass[n_halos + h] = top;
+    const double side = fmax(fmax(e[4] - e[0], e[5] - e[1]), e[6] - e[2]);
+    const double mref = equal && lo > 0.0 ? 1.0 : top;
+    cmass[2 * n_halos + h] = e[8] == 0.0 && side <= 0x1p20 * H.eps && H.eps2 > 0x1p-400 &&
+                                     H.eps2 < 0x1p400 && mref > 0x1p-400 && mref < 0x1p400
+                                 ? 1.0
+                                 : 0.0;
     if (status && !equal && H.sigma_m > 0.0) atomicOr(&status[h], SIDM_DEV_UNEQUAL_MASS);
 }
 
@@ -107,7 +118,8 @@ __global__ __launch_bounds__(kStreamBlock) void k_block_range(
         zero[i] = 0u;
     const int64_t i = B.start + (t < B.count ? t : 0);
     const double px = x[i], py = y[i], pz = z[i], mi = m[i];
-    double e[kRange] = {px, py, pz, mi, px, py, pz, mi};
+    const double nf = (px - px) + (py - py) + (pz - pz) + (mi - mi) == 0.0 ? 0.0 : 1.0;
+    double e[kRange] = {px, py, pz, mi, px, py, pz, mi, nf};
     block_range<kStreamBlock / 64>(e, red);
     if (t == 0)
         for (int c = 0; c < kRange; ++c) brange[kRange * (int64_t)blockIdx.x + c] = e[c];
@@ -122,8 +134,8 @@ __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
     const HaloDev& H = halos[blockIdx.x];
     const int t = threadIdx.x;
     const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
-    double e[kRange] = {INFINITY, INFINITY, INFINITY, INFINITY,
-                        -INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    double e[kRange] = {INFINITY,  INFINITY,  INFINITY,  INFINITY, -INFINITY,
+                        -INFINITY, -INFINITY, -INFINITY, 0.0};
     for (int64_t b = t; b < nb; b += kRangeThreads)
         for (int c = 0; c < kRange; ++c) {
             const double v = brange[kRange * (H.stream_block0 + b) + c];
@@ -135,7 +147,7 @@ __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
             bbox[6 * blockIdx.x + c] = e[c];
             bbox[6 * blockIdx.x + 3 + c] = e[4 + c];
         }
-        put_mass(H, blockIdx.x, gridDim.x, e[3], e[7], cmass, status);
+        put_mass(H, blockIdx.x, gridDim.x, e, cmass, status);
     }
 }
 
@@ -398,8 +410,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int n = (int)H.n, q0 = wv * (64 * IPT) + lane;
     double px[IPT], py[IPT], pz[IPT];
-    double e[kRange] = {INFINITY, INFINITY, INFINITY, INFINITY,
-                        -INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    double e[kRange] = {INFINITY,  INFINITY,  INFINITY,  INFINITY, -INFINITY,
+                        -INFINITY, -INFINITY, -INFINITY, 0.0};
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
         const int q = q0 + 64 * r;
@@ -412,11 +424,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
             for (int c = 0; c < 4; ++c) {
                 e[c] = fmin(e[c], v[c]);
                 e[4 + c] = fmax(e[4 + c], v[c]);
+                if (!(v[c] - v[c] == 0.0)) e[8] = 1.0;
             }
         }
     }
     block_range<kSmallWaves>(e, red);
-    if (t == 0) put_mass(H, blockIdx.x, gridDim.x, e[3], e[7], cmass, status);
+    if (t == 0) put_mass(H, blockIdx.x, gridDim.x, e, cmass, status);
     const double inv = key_scale(e, e + 4);
     unsigned long long key[IPT];
     uint32_t id[IPT], rank[IPT], dig[IPT];

@@ -46,7 +46,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
                           int bmax = 0);
 int64_t gravity_slots(int device);
 int64_t gravity_slots(int device, const GravShape& shape, bool mixed);
-int64_t gravity_sym_slots(int device, const GravShape& shape);
+int64_t gravity_sym_slots(int device, const GravShape& shape, bool mixed);
 hipError_t launch_cell_list(const Plan& plan, const sidm_state* s, Scratch& w, hipStream_t st,
                             int* status, int tick = 0, int bmax = 0);
 hipError_t launch_knn(const Plan& plan, const sidm_state* s, Scratch& w, uint32_t* nbr, int k_max,
@@ -204,7 +204,8 @@ sidm_status ensure_plan(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos, hi
     const unsigned long long* symacc = c->w.symacc;
     c->w.slots_mixed = gravity_slots(c->device, c->shape, true);
     c->w.slots_fp64 = gravity_slots(c->device, c->shape, false);
-    c->w.slots_sym = c->sym_min_n > 0 ? gravity_sym_slots(c->device, c->shape) : 0;
+    c->w.slots_sym = c->sym_min_n > 0 ? gravity_sym_slots(c->device, c->shape, true) : 0;
+    c->w.slots_sym64 = c->sym_min_n > 0 ? gravity_sym_slots(c->device, c->shape, false) : 0;
     if (!build_plan(c->plan, c->w, halos, n_halos, c->shape, c->w.slots_mixed, why, c->sym_min_n,
                     c->w.slots_sym) ||
         !ensure_tick_tables(c->w, c->plan, why) || !ensure_sym_tables(c->w, c->plan, why)) {
@@ -766,8 +767,8 @@ bool shape_supported(int ireg, int nt)
 // Key of a tuning-cache entry: device architecture and compute units,
 // precision, and the call's direct-sum size class (log2 of the particles in
 // direct-sum halos, and of the number of halos, both rounded to nearest).
-// sym_min_n: the context's threshold of the symmetric tiles; a mixed call
-// with a halo that takes them is keyed apart (":sym"), as it times them.
+// sym_min_n: the context's threshold of the symmetric tiles; a call with a
+// halo that takes them is keyed apart (":sym"), as it times them.
 std::string tune_key(int device, const sidm_halo* halos, int32_t n_halos, sidm_precision prec,
                      int64_t sym_min_n)
 {
@@ -787,16 +788,16 @@ std::string tune_key(int device, const sidm_halo* halos, int32_t n_halos, sidm_p
         if (!(halos[h].tree_alpha > 0.0)) {
             ndir += (double)halos[h].n;
             ++nh;
-            if (sym_min_n > 0 && halos[h].n >= std::max<int64_t>(sym_min_n, 2) &&
-                halos[h].eps > 0.0)
-                sym = true;
+            const int64_t least =
+                std::max<int64_t>(sym_min_n, prec == SIDM_PREC_MIXED ? 2 : kSymMinN64);
+            if (sym_min_n > 0 && halos[h].n >= least && halos[h].eps > 0.0) sym = true;
         }
     const int ln = ndir > 0.0 ? (int)std::lround(std::log2(ndir)) : 0;
     const int lh = nh > 0 ? (int)std::lround(std::log2((double)nh)) : 0;
     char buf[160];
     snprintf(buf, sizeof buf, "%s:%dcu:%s:n2^%d:h2^%d%s", arch.c_str(), cus,
              prec == SIDM_PREC_MIXED ? "mixed" : "fp64", ln, lh,
-             prec == SIDM_PREC_MIXED && sym ? ":sym" : "");
+             sym ? ":sym" : "");
     return buf;
 }
 

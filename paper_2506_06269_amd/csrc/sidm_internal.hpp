@@ -22,7 +22,7 @@ constexpr int kTickSplit = 16;       // j-splits of a block-step tick
 constexpr int kSortBits = 8;         // radix digit width
 constexpr int kSortBlock = 256;      // threads per sort tile
 constexpr int kSortMaxPasses = 8;    // 64-bit keys
-constexpr int kRange = 8;            // box and mass range: min x, y, z, m, max x, y, z, m
+constexpr int kRange = 9;            // min x, y, z, m, max x, y, z, m, whether any is not finite
 constexpr int64_t kSmallN = 8192;    // halos up to this size are sorted by one workgroup
 
 // Shape of the direct-sum gravity launch: i-particles per thread, threads per
@@ -44,6 +44,11 @@ constexpr int kShapeNt[kNumShapes] = {128, 128, 128, 256, 256, 256, 512, 512, 51
 // evaluated once) run in the launch shape of the one-sided tiles; by default
 // halos of at least kSymMinN particles take them.
 constexpr int64_t kSymMinN = 4096;
+// The FP64 sums take them from kSymMinN64 particles on (4 x 256, symmetric and
+// one-sided: 0.42 and 0.30 ms at 16384, 0.84 and 0.81 at 32768, 2.1 and 2.8 at
+// 65536); no less than kSymMinN.
+constexpr int64_t kSymMinN64 = 40960;
+constexpr int kSymMixed = 1, kSymFp64 = 2;   // HaloDev::grav_sym
 constexpr int kSymFold = 4;           // j-tiles per flush of the i-side sums
 constexpr int kSymWaves = 4;          // waves per SIMD the symmetric tiles are compiled for
 
@@ -72,7 +77,7 @@ struct HaloDev {
     int64_t stream_block0;                // first streaming block of this halo
     int64_t sbase;                        // first position in the sorted (compact) order
     int32_t rank;                         // halo rank by offset (high bits of the sort key)
-    int32_t grav_sym;                     // mixed direct sums run the symmetric tiles
+    int32_t grav_sym;                     // kSym* bits: direct sums run the symmetric tiles
     int32_t win_lo, win_hi;               // kNN bound window, in buckets around b
     int32_t pad;
 };

@@ -105,7 +105,7 @@ struct Scratch {
     // gravity
     double* bsum = nullptr;       // 7 doubles per streaming block
     double* brange = nullptr;     // kRange doubles per streaming block
-    double* cref = nullptr;       // per halo: the common mass if all are equal, else 0
+    double* cref = nullptr;       // masses of the halos (put_mass), by kind then halo
     double* radius = nullptr;     // per halo: radius of the central density
     sidm_center* center = nullptr;    // per halo: centre of the tidal-radius search
     double* tidal = nullptr;          // per halo: 8 doubles of bisection state
@@ -120,13 +120,13 @@ struct Scratch {
     int64_t partial_tick_rows = 0;
     int64_t grav_slots = 0;       // resident blocks of the gravity tiles on the whole device
     int64_t slots_mixed = 0, slots_fp64 = 0;   // of the plan's shape, per precision
-    // symmetric tiles: work items, fixed-point totals (4 per sorted particle),
-    // resident blocks
+    // symmetric tiles: work items, fixed-point totals (4 words per sorted
+    // particle, FP64 8), resident blocks
     SymItem* sym_items = nullptr;
     int64_t sym_items_cap = 0;
     unsigned long long* symacc = nullptr;
-    int64_t symacc_n = 0;
-    int64_t slots_sym = 0;
+    int64_t symacc_n = 0;             // words
+    int64_t slots_sym = 0, slots_sym64 = 0;
     // cell list
     unsigned long long* keys[2] = {nullptr, nullptr};
     uint32_t* vals[2] = {nullptr, nullptr};
@@ -176,8 +176,9 @@ struct Plan {
     std::vector<StreamBlock> blocks;
     std::vector<GravItem> items;          // one-sided: the halos without symmetric tiles first
     int64_t n_items_nosym = 0;            // items of the halos without symmetric tiles
-    std::vector<SymItem> sym_items;       // symmetric tiles (mixed precision)
+    std::vector<SymItem> sym_items;       // symmetric tiles
     int64_t n_sym_items = 0;
+    bool any_sym64 = false;               // some halo's FP64 sums take them
     std::vector<GravItem> items_tick;     // block-step ticks (empty without block steps)
     int64_t tick_rows = 0;                // partial rows the tick items need
     std::vector<BucketInfo> buckets;
@@ -550,7 +551,8 @@ inline void choose_splits(std::vector<HaloDev>& hd, int64_t partial_rows, int64_
 }
 
 // Symmetric tiles: marks the halos large enough for them (softened, direct
-// sum, at least sym_min_n particles; none for sym_min_n = 0) and cuts their
+// sum, at least sym_min_n particles; none for sym_min_n = 0; the FP64 sums from
+// kSymMinN64 on) and cuts their
 // work: each i-block of ireg * nt against the j from its own start to the
 // halo's end, in ranges of L, about 32 items per resident block over all such
 // halos, largest first.  L is a multiple of nt; below four i-blocks a multiple
@@ -568,7 +570,7 @@ inline void make_sym_items(std::vector<HaloDev>& halos, const GravShape& shape,
     double pairs = 0.0;
     for (auto& H : halos)
         if (!(H.tree_alpha > 0.0) && H.n >= std::max<int64_t>(sym_min_n, 2) && H.eps > 0.0) {
-            H.grav_sym = 1;
+            H.grav_sym = kSymMixed | (H.n >= kSymMinN64 ? kSymFp64 : 0);
             pairs += 0.5 * (double)H.n * (double)H.n;
         }
     const double target = pairs / (32.0 * (double)sym_slots * (double)sym_i);
@@ -729,11 +731,13 @@ inline bool build_plan(Plan& P, const Scratch& w, const sidm_halo* halos, int32_
     }
     make_sym_items(P.halos, shape, sym_min_n, sym_slots, P.sym_items);
     P.n_sym_items = (int64_t)P.sym_items.size();
+    for (const auto& H : P.halos)
+        if (H.grav_sym & kSymFp64) P.any_sym64 = true;
     // largest items first so that the uneven tail is short, those of the halos
     // without symmetric tiles ahead of the others; a tick's active i-blocks
     // come first, so its items are ordered by i-block within a j size
     std::stable_sort(P.items.begin(), P.items.end(), [&](const GravItem& a, const GravItem& b) {
-        const int sa = P.halos[a.halo].grav_sym, sb = P.halos[b.halo].grav_sym;
+        const bool sa = P.halos[a.halo].grav_sym != 0, sb = P.halos[b.halo].grav_sym != 0;
         if (sa != sb) return sa < sb;
         return (a.j1 - a.j0) > (b.j1 - b.j0);
     });
@@ -797,14 +801,15 @@ inline bool ensure_sym_tables(Scratch& w, const Plan& P, std::string& why)
         }
         w.sym_items_cap = P.n_sym_items;
     }
-    if (P.n_sorted > w.symacc_n) {
+    const int64_t words = (P.any_sym64 ? 8 : 4) * P.n_sorted;
+    if (words > w.symacc_n) {
         dfree(w.symacc);
         w.symacc_n = 0;
-        if (!dalloc(w.symacc, 4 * P.n_sorted)) {
+        if (!dalloc(w.symacc, words)) {
             why = "out of device memory for the symmetric tiles' totals";
             return false;
         }
-        w.symacc_n = P.n_sorted;
+        w.symacc_n = words;
     }
     return true;
 }
