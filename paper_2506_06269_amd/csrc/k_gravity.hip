@@ -796,22 +796,22 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
 //
 // The totals are 128-bit fixed point in two words that never carry into each
 // other: x = v 2^s is cut into its nearest integer and the remainder times
-// 2^kSymLow, each summed with integer atomics, so that the result does not
+// kSymLow, each summed with integer atomics, so that the result does not
 // depend on the order in which items finish and keeps what FP64 holds of
 // every partial sum (a single word of 64 bits would round them at 2^-61 of the
 // bound, 10^-10 of the force on a particle at a halo's edge).
-constexpr int kSymLow = 44;
+constexpr double kSymLow = 0x1p44;
 
 __device__ inline void fixed_add(unsigned long long* a, double x)
 {
     const double hi = rint(x);
     atomicAdd(a + 0, (unsigned long long)(long long)hi);
-    atomicAdd(a + 1, (unsigned long long)(long long)rint((x - hi) * 0x1p44));
+    atomicAdd(a + 1, (unsigned long long)(long long)rint((x - hi) * kSymLow));
 }
 
 __device__ inline double fixed_value(const long long* q)
 {
-    return (double)q[0] + (double)q[1] * 0x1p-44;
+    return (double)q[0] + (double)q[1] / kSymLow;
 }
 
 struct Words {
@@ -1045,7 +1045,7 @@ __device__ inline void grav_sym64_body(const double* __restrict__ x, const doubl
 // As k_grav_sym; halos that the fixed-point totals cannot hold (sym_ok, see
 // put_mass) are left to the one-sided tiles.
 template <int IREG, int NT, bool EQM>
-__global__ __launch_bounds__(NT, IREG >= 8 ? 2 : 3) void k_grav_sym64(
+__global__ __launch_bounds__(NT, IREG >= 8 || NT >= 512 ? 2 : 3) void k_grav_sym64(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
     const double* __restrict__ m, const SymItem* __restrict__ items, int64_t n_items,
     unsigned long long* __restrict__ ticket, const HaloDev* __restrict__ halos,

@@ -373,7 +373,7 @@ hipError_t launch_center(const StreamBlock* d_blocks, int64_t n_blocks, const Ha
 // ---------------------------------------------------------------- tidal radius
 // Eq. tidal_radius: G M(<= r) / r^2 = |grad Phi_host(c + r n) - grad Phi_host(c - r n)|,
 // bisection in log r.  Per-halo state in `tid` (8 doubles): n (3), lo, hi,
-// the initial hi, mid.
+// the initial hi, the mass within hi, whether that is known.
 
 // Per streaming block: the largest squared distance from the halo's centre.
 __global__ __launch_bounds__(kStreamBlock) void k_tidal_extent(
@@ -431,100 +431,236 @@ __global__ __launch_bounds__(kStreamBlock) void k_tidal_init(
         T[4] = hi;
         T[3] = ldexp(hi, -40);
         T[5] = hi;
-        T[6] = sqrt(T[3] * T[4]);
+        T[6] = 0.0;
+        T[7] = 0.0;
     }
 }
 
-// Per streaming block: mass within the radius r of the halo's centre, with
-// r the current midpoint (tid[6]) or, with `final_pass`, the upper bracket.
-__global__ __launch_bounds__(kStreamBlock) void k_tidal_mass(
-    const StreamBlock* __restrict__ blocks, const double* __restrict__ x,
-    const double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ m,
-    const sidm_center* __restrict__ cen, const double* __restrict__ tid, int final_pass,
-    double* __restrict__ bsum)
+// The bisection takes kTidalLevels steps per launch.  The midpoints that those
+// steps can reach are known before any of them is taken (a tree of 2^levels - 1
+// radii below the bracket, node q's children 2q and 2q + 1), so one pass over
+// the particles sums the mass within each of them and within the upper
+// bracket; the next launch adds the workgroups' sums, decides every node at
+// once and follows the decisions down.  Every workgroup of a halo does that for
+// itself, in the same order, so nothing is exchanged within a launch.  60
+// launches of a mass pass and 60 of a one-workgroup sum and decision, 6 and 11
+// us each at 2^20 particles, became 13 of 15 us (a chain of loads, square roots
+// and fields; the sums themselves take 3).
+constexpr int kTidalLevels = 5;
+constexpr int kTidalSums = 1 << kTidalLevels;   // 31 nodes (entry q - 1) and the upper bracket
+constexpr int kTidalSteps = 60;
+constexpr int kTidalThreads = 512;
+constexpr int kTidalBlocks = 256;               // workgroups per halo at most
+static_assert(kTidalSteps % kTidalLevels == 0, "whole launches");
+
+struct Bracket {
+    double lo, hi;
+};
+
+// The bracket of node q of the tree below b, whose midpoint is the node's
+// radius: the steps of the bisection on the way down.
+__device__ inline Bracket tidal_node(Bracket b, int q)
 {
-    __shared__ double red[kStreamBlock];
-    const StreamBlock B = blocks[blockIdx.x];
-    const sidm_center C = cen[B.halo];
-    const double r = tid[8 * B.halo + (final_pass ? 4 : 6)];
-    const int t = threadIdx.x;
-    double w = 0.0;
-    if (t < B.count && C.index >= 0) {
 #pragma clang fp contract(off)
-        const int64_t p = B.start + t;
-        const double dx = x[p] - C.x, dy = y[p] - C.y, dz = z[p] - C.z;
-        if ((dx * dx + dy * dy) + dz * dz <= r * r) w = m[p];
+    for (int l = 30 - __clz(q); l >= 0; --l) {
+        const double r = sqrt(b.lo * b.hi);
+        if ((q >> l) & 1) b.lo = r;
+        else b.hi = r;
     }
-    red[t] = w;
-    __syncthreads();
-    for (int s = kStreamBlock / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
-        __syncthreads();
-    }
-    if (t == 0) bsum[7 * blockIdx.x + 5] = red[0];
+    return b;
 }
 
-__device__ inline double halo_block_sum(const HaloDev& H, const double* bsum, int slot,
-                                        double* red)
+// The acceleration of one component of the host at the node's radius on either
+// side of the centre (the wave's index: the component; lanes 0 to 31 outwards,
+// 32 to 63 inwards).  The fields' square roots, divisions and logarithms are a
+// serial chain of 10 us when one lane evaluates all components of both sides.
+__device__ inline void tidal_part(const HaloDev& H, const sidm_center& C, const double* T,
+                                  const Bracket& b, int part, int lane, double (*field)[64][3])
 {
-    const int t = threadIdx.x;
+#pragma clang fp contract(off)
+    const int q = lane % kTidalSums + 1;
+    if (q == kTidalSums) return;
+    const Bracket n = tidal_node(b, q);
+    const double r = sqrt(n.lo * n.hi), s = lane < kTidalSums ? r : -r;
+    const double px = C.x + s * T[0], py = C.y + s * T[1], pz = C.z + s * T[2];
+    double phi;
+    double* a = field[part][lane];
+    host_part(H, part, px - H.host_c[0], py - H.host_c[1], pz - H.host_c[2], a[0], a[1], a[2],
+              phi);
+}
+
+// Whether the halo's own gravity at r wins over the host's tide there, for the
+// node of thread t (the components of its two sides added as host_field does).
+__device__ inline bool tidal_inside(const HaloDev& H, const double (*field)[64][3], int t,
+                                    double r, double M)
+{
+#pragma clang fp contract(off)
+    double g[3];
+    for (int c = 0; c < 3; ++c) {
+        double out = field[0][t][c], in = field[0][t + kTidalSums][c];
+        for (int k = 1; k < kHostParts; ++k) {
+            out += field[k][t][c];
+            in += field[k][t + kTidalSums][c];
+        }
+        g[c] = out - in;
+    }
+    const double tide = sqrt((g[0] * g[0] + g[1] * g[1]) + g[2] * g[2]);
+    return H.G * M / (r * r) > tide;
+}
+
+// Workgroups of a halo's passes.
+__device__ inline int tidal_groups(const HaloDev& H)
+{
     const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
-    double v = 0.0;
-    for (int64_t b = t; b < nb; b += kStreamBlock) v += bsum[7 * (H.stream_block0 + b) + slot];
-    red[t] = v;
-    __syncthreads();
-    for (int s = kStreamBlock / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
-        __syncthreads();
-    }
-    return red[0];
+    return (int)(nb < kTidalBlocks ? nb : kTidalBlocks);
 }
 
-// One bisection step or the final record (thread 0 of the halo's block).
-__device__ inline void tidal_update(const HaloDev& H, double M, const sidm_center C, double* T,
-                                    int final_pass, sidm_tidal* o_ptr)
-{
-#pragma clang fp contract(off)
-    if (final_pass) {
-        sidm_tidal o;
-        o.r_tidal = T[4];
-        o.mass = M;
-        o.x = C.x; o.y = C.y; o.z = C.z;
-        o.index = C.index;
-        o.status = T[4] == T[5] ? 1 : 0;
-        o.reserved = 0;
-        *o_ptr = o;
-        return;
-    }
-    const double r = T[6];
-    double ax1, ay1, az1, p1, ax2, ay2, az2, p2;
-    host_field(H, C.x + r * T[0], C.y + r * T[1], C.z + r * T[2], ax1, ay1, az1, p1);
-    host_field(H, C.x - r * T[0], C.y - r * T[1], C.z - r * T[2], ax2, ay2, az2, p2);
-    const double gx = ax1 - ax2, gy = ay1 - ay2, gz = az1 - az2;
-    const double tide = sqrt((gx * gx + gy * gy) + gz * gz);
-    if (H.G * M / (r * r) > tide) T[3] = r;
-    else T[4] = r;
-    T[6] = sqrt(T[3] * T[4]);
-}
-
-// Per halo: one bisection step (self gravity at the midpoint against the
-// host's tidal acceleration there), or the final record.
-__global__ __launch_bounds__(kStreamBlock) void k_tidal_step(
-    const HaloDev* __restrict__ halos, const double* __restrict__ bsum,
-    const sidm_center* __restrict__ cen, double* __restrict__ tid, int final_pass,
+// per_halo workgroups for each halo (those past its own leave).  tid_in / tid_out: the state before and after the
+// decisions on sums_in (none in the first launch); sums_out: this launch's sums
+// (kTidalSums per workgroup).  The last launch writes the record instead.
+__global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
+    const HaloDev* __restrict__ halos, const double* __restrict__ x, const double* __restrict__ y,
+    const double* __restrict__ z, const double* __restrict__ m,
+    const sidm_center* __restrict__ cen, const double* __restrict__ tid_in,
+    double* __restrict__ tid_out, const double* __restrict__ sums_in,
+    double* __restrict__ sums_out, int per_halo, int first, int last,
     sidm_tidal* __restrict__ out)
 {
-    __shared__ double red[kStreamBlock];
-    const HaloDev& H = halos[blockIdx.x];
-    const double M = halo_block_sum(H, bsum, 5, red);
-    if (threadIdx.x != 0) return;
-    tidal_update(H, M, cen[blockIdx.x], tid + 8 * blockIdx.x, final_pass, out + blockIdx.x);
+    constexpr int NW = kTidalThreads / 64, NG = kTidalThreads / kTidalSums;
+    __shared__ double red[NG][kTidalSums];
+    __shared__ double rad2[kTidalSums];
+    __shared__ int inside[kTidalSums];
+    __shared__ double field[kHostParts][64][3];
+    static_assert(kHostParts <= NW && 2 * kTidalSums == 64, "a wave per component, a lane per side");
+    const int h = blockIdx.x / per_halo, g = blockIdx.x % per_halo, t = threadIdx.x;
+    const HaloDev& H = halos[h];
+    const int groups = tidal_groups(H);
+    if (g >= (last ? 1 : groups)) return;
+    const sidm_center C = cen[h];
+    double T[8];
+    for (int q = 0; q < 8; ++q) T[q] = tid_in[8 * h + q];
+    Bracket b{T[3], T[4]};
+    double M_hi = T[6];   // mass within the upper bracket
+    if (!first) {
+        // the sums of the previous pass, in workgroup order
+        const int c = t % kTidalSums, part = t / kTidalSums;
+        constexpr int kRows = kTidalBlocks / NG;
+        double w[kRows], v = 0.0;
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int q = part + u * NG;
+            w[u] = q < groups ? sums_in[(H.stream_block0 + q) * kTidalSums + c] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) v += w[u];
+        red[part][c] = v;
+        if (t / 64 < kHostParts) tidal_part(H, C, T, b, t / 64, t & 63, field);
+        __syncthreads();
+        if (t < kTidalSums) {
+            double M = 0.0;
+            for (int q = 0; q < NG; ++q) M += red[q][t];
+            red[0][t] = M;
+            if (t + 1 < kTidalSums) {
+                const Bracket n = tidal_node(b, t + 1);
+                inside[t] = tidal_inside(H, field, t, sqrt(n.lo * n.hi), M);
+            }
+        }
+        __syncthreads();
+        if (T[7] == 0.0) M_hi = red[0][kTidalSums - 1];   // the initial bracket's
+        for (int l = 0, q = 1; l < kTidalLevels; ++l) {
+#pragma clang fp contract(off)
+            const double r = sqrt(b.lo * b.hi);
+            const bool in = inside[q - 1];
+            if (in) {
+                b.lo = r;
+            } else {
+                b.hi = r;
+                M_hi = red[0][q - 1];
+            }
+            q = 2 * q + (in ? 1 : 0);
+        }
+    }
+    if (last) {
+        if (t == 0) {
+            sidm_tidal o;
+            o.r_tidal = b.hi;
+            o.mass = M_hi;
+            o.x = C.x; o.y = C.y; o.z = C.z;
+            o.index = C.index;
+            o.status = b.hi == T[5] ? 1 : 0;
+            o.reserved = 0;
+            out[h] = o;
+        }
+        return;
+    }
+    if (g == 0 && t < 8)
+        tid_out[8 * h + t] = t == 3   ? b.lo
+                             : t == 4 ? b.hi
+                             : t == 6 ? M_hi
+                             : t == 7 ? (first ? 0.0 : 1.0)
+                                      : T[t];
+    __syncthreads();   // the previous sums are read before red is reused
+    if (t < kTidalSums) {
+#pragma clang fp contract(off)
+        double r = b.hi;
+        if (t + 1 < kTidalSums) {
+            const Bracket n = tidal_node(b, t + 1);
+            r = sqrt(n.lo * n.hi);
+        }
+        rad2[t] = r * r;
+    }
+    __syncthreads();
+    double v[kTidalSums];
+#pragma unroll
+    for (int c = 0; c < kTidalSums; ++c) v[c] = 0.0;
+    if (C.index >= 0) {
+        // four particles' loads in flight
+        constexpr int kLoads = 4;
+        const int64_t step = (int64_t)groups * kTidalThreads;
+        for (int64_t i = (int64_t)g * kTidalThreads + t; i < H.n; i += kLoads * step) {
+#pragma clang fp contract(off)
+            double d2[kLoads], mp[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const bool on = i + u * step < H.n;
+                const int64_t p = H.offset + (on ? i + u * step : i);
+                const double dx = x[p] - C.x, dy = y[p] - C.y, dz = z[p] - C.z;
+                d2[u] = (dx * dx + dy * dy) + dz * dz;
+                mp[u] = on ? m[p] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u)
+#pragma unroll
+                for (int c = 0; c < kTidalSums; ++c) v[c] += d2[u] <= rad2[c] ? mp[u] : 0.0;
+        }
+    }
+    // over the wave: every exchange halves the sums a lane holds; lane l ends
+    // with sum l / 2
+    const int lane = t & 63;
+#pragma unroll
+    for (int k = kTidalSums / 2; k > 0; k /= 2) {
+        const int o = 2 * k;
+        const bool up = lane & o;
+#pragma unroll
+        for (int c = 0; c < k; ++c) {
+            const double keep = up ? v[c + k] : v[c], give = up ? v[c] : v[c + k];
+            v[c] = keep + __shfl_xor(give, o, 64);
+        }
+    }
+    v[0] += __shfl_xor(v[0], 1, 64);
+    if (!(lane & 1)) red[t >> 6][lane >> 1] = v[0];
+    __syncthreads();
+    if (t < kTidalSums) {
+        double M = 0.0;
+        for (int w = 0; w < NW; ++w) M += red[w][t];
+        sums_out[(H.stream_block0 + g) * kTidalSums + t] = M;
+    }
 }
 
 hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const HaloDev* d_halos,
-                        int n_halos, const double* x, const double* y, const double* z,
+                        int n_halos, int64_t n_max, const double* x, const double* y, const double* z,
                         const double* m, const double* pot, double* bsum, sidm_center* cen,
-                        double* tid, sidm_tidal* out, hipStream_t st)
+                        double* tid, double* sums, sidm_tidal* out, hipStream_t st)
 {
     hipLaunchKernelGGL(k_center_block, dim3((unsigned)n_blocks), dim3(kStreamBlock), 0, st,
                        d_blocks, d_halos, x, y, z, pot, bsum);
@@ -534,12 +670,17 @@ hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const Hal
                        d_blocks, x, y, z, cen, bsum);
     hipLaunchKernelGGL(k_tidal_init, dim3(n_halos), dim3(kStreamBlock), 0, st, d_halos, bsum, cen,
                        tid);
-    for (int it = 0; it <= 60; ++it) {
-        const int fin = it == 60 ? 1 : 0;
-        hipLaunchKernelGGL(k_tidal_mass, dim3((unsigned)n_blocks), dim3(kStreamBlock), 0, st,
-                           d_blocks, x, y, z, m, cen, tid, fin, bsum);
-        hipLaunchKernelGGL(k_tidal_step, dim3(n_halos), dim3(kStreamBlock), 0, st, d_halos, bsum,
-                           cen, tid, fin, out);
+    constexpr int kPasses = kTidalSteps / kTidalLevels;
+    double* state[2] = {tid, tid + 8 * (int64_t)n_halos};
+    double* sum[2] = {sums, sums + n_blocks * kTidalSums};
+    const int64_t nb = (n_max + kStreamBlock - 1) / kStreamBlock;
+    const int groups = (int)(nb < kTidalBlocks ? nb : kTidalBlocks);
+    for (int it = 0; it <= kPasses; ++it) {
+        const int per_halo = it == kPasses ? 1 : groups;
+        hipLaunchKernelGGL(k_tidal_pass, dim3((unsigned)per_halo * (unsigned)n_halos),
+                           dim3(kTidalThreads), 0, st, d_halos, x, y, z, m, cen, state[it & 1],
+                           state[(it & 1) ^ 1], sum[(it & 1) ^ 1], sum[it & 1], per_halo, it == 0,
+                           it == kPasses, out);
     }
     return hipGetLastError();
 }

@@ -61,23 +61,41 @@ __device__ inline void disk_field(double GM, double a, double b, double dx, doub
     az = zeta > 0.0 ? f * dz * s / zeta : 0.0;
 }
 
+// The host's components in the order host_field adds them: the NFW halo, the
+// bulge, the discs.  False (and zeros) when the host has no component k.
+constexpr int kHostParts = 6;
+__device__ inline bool host_part(const HaloDev& H, int k, double dx, double dy, double dz,
+                                 double& ax, double& ay, double& az, double& phi)
+{
+    ax = ay = az = phi = 0.0;
+    if (H.host_kind == 0) return false;
+    if (k == 0) {
+        if (H.host_K == 0.0) return false;
+        nfw_field(H, dx, dy, dz, ax, ay, az, phi);
+        return true;
+    }
+    if (H.host_kind != 2) return false;
+    if (k == 1) {
+        if (H.hern_GM == 0.0) return false;
+        hernquist_field(H.hern_GM, H.hern_a, dx, dy, dz, ax, ay, az, phi);
+        return true;
+    }
+    const int d = k - 2;
+    if (H.disk_GM[d] == 0.0) return false;
+    disk_field(H.disk_GM[d], H.disk_a[d], H.disk_b[d], dx, dy, dz, ax, ay, az, phi);
+    return true;
+}
+
 // Total host acceleration and potential at p.
 __device__ inline void host_field(const HaloDev& H, double px, double py, double pz, double& ax,
                                   double& ay, double& az, double& phi)
 {
     const double dx = px - H.host_c[0], dy = py - H.host_c[1], dz = pz - H.host_c[2];
-    ax = ay = az = phi = 0.0;
-    if (H.host_kind == 0) return;
-    if (H.host_K != 0.0) nfw_field(H, dx, dy, dz, ax, ay, az, phi);
+    host_part(H, 0, dx, dy, dz, ax, ay, az, phi);
     if (H.host_kind != 2) return;
-    double gx, gy, gz, gp;
-    if (H.hern_GM != 0.0) {
-        hernquist_field(H.hern_GM, H.hern_a, dx, dy, dz, gx, gy, gz, gp);
-        ax += gx; ay += gy; az += gz; phi += gp;
-    }
-    for (int d = 0; d < 4; ++d) {
-        if (H.disk_GM[d] == 0.0) continue;
-        disk_field(H.disk_GM[d], H.disk_a[d], H.disk_b[d], dx, dy, dz, gx, gy, gz, gp);
+    for (int k = 1; k < kHostParts; ++k) {
+        double gx, gy, gz, gp;
+        if (!host_part(H, k, dx, dy, dz, gx, gy, gz, gp)) continue;
         ax += gx; ay += gy; az += gz; phi += gp;
     }
 }

@@ -108,7 +108,8 @@ struct Scratch {
     double* cref = nullptr;       // masses of the halos (put_mass), by kind then halo
     double* radius = nullptr;     // per halo: radius of the central density
     sidm_center* center = nullptr;    // per halo: centre of the tidal-radius search
-    double* tidal = nullptr;          // per halo: 8 doubles of bisection state
+    double* tidal = nullptr;          // per halo: 8 doubles of bisection state, twice
+    double* tidal_sums = nullptr;     // per streaming block: 32 mass sums, twice
     double* bbox = nullptr;       // 6 per halo (min xyz, max xyz)
     float4* xm32 = nullptr;       // FP32 positions relative to their tile centre, mass
     double4* partial = nullptr;
@@ -308,7 +309,7 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
     bool ok = dalloc(w.halos, H) && dalloc(w.blocks, nb) && dalloc(w.items, w.items_cap) &&
               dalloc(w.buckets, w.buckets_cap) && dalloc(w.node_tasks, w.nodes_cap) && dalloc(w.nodes, w.nodes_cap) &&
               dalloc(w.bsum, 7 * nb) && dalloc(w.brange, kRange * nb) && dalloc(w.cref, 4 * H) && dalloc(w.radius, H) && dalloc(w.center, H) &&
-              dalloc(w.tidal, 8 * H) && dalloc(w.bbox, 6 * H) &&
+              dalloc(w.tidal, 16 * H) && dalloc(w.tidal_sums, 64 * nb) && dalloc(w.bbox, 6 * H) &&
               dalloc(w.xm32, N) &&  dalloc(w.partial, w.partial_rows) && dalloc(w.keys[0], 2 * N) &&
               dalloc(w.vals[0], N) && dalloc(w.vals[1], N) &&
               dalloc(w.sort_ws, w.sort_ws_n) && dalloc(w.sx, N) && dalloc(w.sy, N) &&
@@ -356,7 +357,7 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
 inline void free_scratch(Scratch& w)
 {
     dfree(w.halos); dfree(w.blocks); dfree(w.items); dfree(w.buckets); dfree(w.node_tasks); dfree(w.nodes);
-    dfree(w.bsum); dfree(w.brange); dfree(w.cref); dfree(w.radius); dfree(w.center); dfree(w.tidal); dfree(w.bbox); dfree(w.xm32);  dfree(w.partial);
+    dfree(w.bsum); dfree(w.brange); dfree(w.cref); dfree(w.radius); dfree(w.center); dfree(w.tidal); dfree(w.tidal_sums); dfree(w.bbox); dfree(w.xm32);  dfree(w.partial);
     dfree(w.keys[0]); w.keys[1] = nullptr; dfree(w.vals[0]); dfree(w.vals[1]); dfree(w.sort_ws);
     dfree(w.sx); dfree(w.sy); dfree(w.sz); dfree(w.sp4); dfree(w.svx); dfree(w.svy); dfree(w.svz);
     dfree(w.items_tick); dfree(w.partial_tick);
