@@ -374,9 +374,12 @@ __global__ __launch_bounds__(kBucket) void k_knn(
         // volume, and taken by all 64 lanes it cost four times the warm
         // candidate stream; taken by the few representatives it costs one
         // such stream.
-        const bool rep = in_bucket && lane == go;
+        // (Where a bucket is split over waves, the first of the wave's own
+        // members: without one the others would start from the estimate.)
+        const int first = max(go, part * (kBucket / split));
+        const bool rep = in_bucket && lane == first;
         const double d2r = resolve(rep, warm ? u2 : 0.25 * e2);
-        const double c2 = kKnnWarm * __shfl(d2r, go);
+        const double c2 = kKnnWarm * __shfl(d2r, first);
         if (!warm) u2 = (isfinite(c2) && c2 > 0.0) ? fmin(c2, e2) : e2;
     }
     double d2k = NAN;
