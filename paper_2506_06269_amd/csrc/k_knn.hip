@@ -3,36 +3,39 @@
 // neighbours).
 //
 // One wavefront per bucket of 64 Morton-consecutive particles, one particle
-// per lane, all lanes resolved together (each with its own search sphere).
-// Candidates are read with wave-uniform loads (every lane evaluates the same
-// candidate), and a candidate sub-range is visited only if
-// it intersects the search sphere of at least one lane.
+// per lane, all lanes resolved together (each with its own search sphere).  A
+// visit collects the particles that can lie within some lane's sphere
+// (sidm_search.hpp); every lane then evaluates each of them.
 // Selection works on values only.  When the particle's kernel size before
 // the call is a usable value h0 (a warm start: the result does not depend on
 // it), one visit of the sphere of radius (1 + d) h0 counts the candidates
-// closer than (1 - d) h0 and keeps the distances in between (the band: its
-// kKnnBand smallest values, in an LDS column of the lane); if the k-th
-// distance lies in the band and among the kept values, it is read off them.
+// closer than (1 - d) h0 and lists those in between (the band) in an LDS column
+// of the lane; if the k-th distance lies in the band and among its kKnnBand
+// smallest, it is read off the listed ones.
 // In a step h changes by a few tenths of a per cent (a few per cent at the
 // tail), so almost every lane ends here.  The other lanes, and lanes without
 // a usable h0, take the general search, with a private 32-bin histogram per
 // lane (an LDS column, written with LDS atomics that return nothing):
 //   1. a histogram of the distances within a starting radius: 1.15 times h0
-//      when it is usable; otherwise the first member of the particle's
-//      compact sub-range is resolved first, from an estimate out of the
-//      nearest members of that sub-range, and the particle starts from 1.15
-//      times that member's h; the radius grows until the sphere holds k
-//      others;
+//      when it is usable, else an estimate out of the nearest members of the
+//      particle's compact sub-range; the radius grows until the sphere holds
+//      k others;
 //   2. a visit restricted to the shell of the bin that holds the k-th
 //      collects that bin's members (at most 16, kept sorted in registers) or,
 //      if it holds more, records their min..max, whose histogram (step 1 over
 //      that range) refines the choice; equal values end the refinement.
-// Typical cost: one visit of the candidates around the bucket when warm; two
-// visits for the general search, restricted to the sub-ranges that its
-// lanes' spheres reach.
+// Typical cost: one visit when warm; three for the general search.
+//
+// Bound by vector issue: about 75 cycles per candidate and wave (eight FP64
+// operations of four cycles, three comparisons, four LDS reads shared by four
+// candidates), most of the rest the tests that select them.  A call of 2^20
+// particles (k 64) takes 1.73 ms warm and 5.6 ms without previous sizes, the
+// neighbour lists 2.8 ms more (2.6, 9.6 and 18 ms with the lane-by-lane search,
+// single row stores and a distance per band slot); 8192 particles (k 32) 0.14
+// and 0.27 ms (0.25 and 2.4).
 // Distances d2 = (dx*dx + dy*dy) + dz*dz are evaluated in FP64 without fused
 // multiply-add, the same expression the oracle uses, so h matches bit for bit.
-#include "sidm_tree.hpp"
+#include "sidm_search.hpp"
 
 namespace sidm {
 
@@ -41,30 +44,24 @@ constexpr int kKnnSurv = 16;
 constexpr int kKnnLevels = 4;
 constexpr int kKnnGrow = 80;
 constexpr double kKnnWarm = 1.15 * 1.15;   // squared margin on the previous kernel size
-constexpr int kKnnBand = 16;               // band distances kept per lane
+// squared margin on the estimate without one (calls without previous sizes at
+// N = 2^20 with 0.35, 0.5, 0.7, 1 and 2: 5.5, 5.3, 5.5, 5.9 and 8.5 ms; 8192: 0.29,
+// 0.29, 0.28, 0.27)
+constexpr double kKnnCold = 0.7;
+constexpr int kKnnBand = 16;               // smallest distances of the band kept per lane
+constexpr int kKnnGroup = 4;               // candidates evaluated at once
 constexpr int kKnnSplitMax = 16;           // waves per bucket for calls with few buckets
 
-// The band pass and the general search never run at once: the band's values
-// live in the histogram columns, value q of a lane in words 2q (low half) and
-// 2q + 1 (high half) of its column (a barrier separates the two uses).
-static_assert(2 * kKnnBand <= kKnnBins, "band values fit the histogram columns");
+// The band pass and the general search never run at once: the band's
+// candidates (sorted indices) are listed in the lane's histogram column (a
+// barrier separates the two uses).
 struct KnnLds {
     uint32_t hist[kKnnBins][kBucket];
-    int64_t stack[kStackMax];
+    SearchLds S;
+    // candidates within reach of some lane: position and sorted index
+    double x[2 * kBucket + kKnnGroup], y[2 * kBucket + kKnnGroup], z[2 * kBucket + kKnnGroup];
+    uint32_t p[2 * kBucket + kKnnGroup];
 };
-
-__device__ inline double band_get(const KnnLds& L, int q, int lane)
-{
-    const uint64_t lo = L.hist[2 * q][lane], hi = L.hist[2 * q + 1][lane];
-    return __longlong_as_double((long long)((hi << 32) | lo));
-}
-
-__device__ inline void band_put(KnnLds& L, int q, int lane, double v)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    L.hist[2 * q][lane] = (uint32_t)u;
-    L.hist[2 * q + 1][lane] = (uint32_t)(u >> 32);
-}
 
 __device__ inline double dist2_exact(double ax, double ay, double az, double bx, double by,
                                      double bz)
@@ -104,9 +101,9 @@ template <bool LIST>
 __global__ __launch_bounds__(kBucket) void k_knn(
     const HaloDev* __restrict__ halos, const BucketInfo* __restrict__ buckets,
     const NodeChild* __restrict__ nodes, const double* __restrict__ box,
-    const SubRange* __restrict__ sub, const int* __restrict__ sub_n,
-    const double* __restrict__ cbox, int64_t n_buckets,
-    const double4* __restrict__ sp4, const uint32_t* __restrict__ perm,
+    const SubRange* __restrict__ sub, const int* __restrict__ sub_n, int64_t n_buckets,
+    const double* __restrict__ sx, const double* __restrict__ sy, const double* __restrict__ sz,
+    const uint32_t* __restrict__ perm,
     double* __restrict__ sh, double* __restrict__ h_out, int* __restrict__ status,
     const uint32_t* __restrict__ sid, uint32_t* __restrict__ nbr, int k_max, int split)
 {
@@ -122,61 +119,118 @@ __global__ __launch_bounds__(kBucket) void k_knn(
     const HaloDev& H = halos[B.halo];
     const int k = H.k;
     const bool in_bucket = lane < B.count && lane / (kBucket / split) == part;
-    const int64_t mypos = B.start + (in_bucket ? lane : 0);
-    const double4 me = sp4[mypos];
-    const double xi = me.x, yi = me.y, zi = me.z;
+    const uint32_t mypos = (uint32_t)(B.start + (in_bucket ? lane : 0));
+    const double xi = sx[mypos], yi = sy[mypos], zi = sz[mypos];
     const double hint = sh[mypos];   // the kernel size before the call
     const double diag2 = box_diag2_k(box + 6 * H.level_off[H.n_levels - 1]);
-    auto all_nodes = [](int64_t) { return true; };
+    const int sid_l = lane_sub(sub + kSubMax * b, sub_n[b], lane);
 
-    // every candidate of the sub-ranges within reach of a lane's sphere
-    // (radius^2 r2 of the lane, ignored when `off` is true for the lane);
-    // body(p, c) runs on every lane for candidate p at c = (x, y, z, .)
+    // every candidate within reach of a lane's sphere (radius^2 r2 of the lane;
+    // lanes with `off` set do not search); body(p, d2) runs on every lane for
+    // kKnnGroup candidates p at once and their squared distances d2 (infinite
+    // past the last one): their LDS reads and arithmetic overlap, and one
+    // branch serves them all
     auto visit = [&](double r2, bool off, auto body) __attribute__((always_inline)) {
-        tree_visit(H, nodes, n_buckets, L.stack,
-                   [&](int64_t c) { return !off && point_box_dist2(xi, yi, zi, box + 6 * c) <= r2; },
-                   all_nodes, [&](int64_t c) {
-                       const int64_t c0 = buckets[c].start;
-                       const int ns = sub_n[c];
-                       for (int q = 0; q < ns; ++q) {
-                           const SubRange& R = sub[kSubMax * c + q];
-                           if (!__ballot(!off && point_box_dist2(xi, yi, zi, R.box) <= r2)) continue;
-                           // a long sub-range is taken by chunks, those that
-                           // some sphere reaches
-                           const int j1 = R.off + R.cnt;
-                           const bool chunked = R.cnt > kChunk;
-                           for (int a0 = R.off; a0 < j1;) {
-                               const int g = a0 / kChunk;
-                               const int a1 = chunked ? min(j1, (g + 1) * kChunk) : j1;
-                               const bool reach =
-                                   !chunked ||
-                                   __ballot(!off && point_box_dist2(xi, yi, zi,
-                                                                    cbox + 6 * (kChunks * c + g)) <= r2);
-                               // candidates [a0, a1), four loads in flight
-                               // before the first use
-                               int j = reach ? a0 : a1;
-                               for (; j + 4 <= a1; j += 4) {
-                                   double4 v[4];
+        const int nq = search_groups(L.S, lane, sid_l, !off, xi, yi, zi, r2);
+        if (nq == 0) return;
+        const bool singles = nq == __popcll(__ballot(!off));   // every group one lane
+        int bn = 0;   // candidates in LDS
+        auto process = [&](int n) {
+            if (lane < kKnnGroup) {   // at most 2 kBucket - 1 entries are in use
+                L.x[n + lane] = INFINITY;
+                L.p[n + lane] = ~0u;
+            }
+            __syncthreads();
+            for (int j = 0; j < n; j += kKnnGroup) {
+                uint32_t p[kKnnGroup];
+                double d2[kKnnGroup];
 #pragma unroll
-                                   for (int u = 0; u < 4; ++u) v[u] = sp4[c0 + j + u];
+                for (int u = 0; u < kKnnGroup; ++u) {
+                    p[u] = L.p[j + u];
+                    d2[u] = dist2_exact(xi, yi, zi, L.x[j + u], L.y[j + u], L.z[j + u]);
+                }
+                body(p, d2);
+            }
+            __syncthreads();
+        };
+        auto drain = [&](int ln) {
+            // the buckets whose box some lane reaches (the groups' boxes can
+            // hold the dense centre without any lane near it)
+            int kept = singles ? ln : 0;
+            for (int i = 0; i < ln && !singles; i += 4) {
+                uint32_t c[4];
+                unsigned long long m[4];
 #pragma unroll
-                                   for (int u = 0; u < 4; ++u) body(c0 + j + u, v[u]);
-                               }
-                               for (; j < a1; ++j) body(c0 + j, sp4[c0 + j]);
-                               a0 = a1;
-                           }
-                       }
-                   });
+                for (int u = 0; u < 4; ++u)
+                    c[u] = __builtin_amdgcn_readfirstlane(L.S.list[min(i + u, ln - 1)]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    m[u] = __ballot(!off &&
+                                    point_box_dist2(xi, yi, zi, box + 6 * (int64_t)c[u]) <= r2);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (m[u] && i + u < ln) {
+                        if (lane == 0) L.S.list[kept] = c[u];
+                        ++kept;
+                    }
+            }
+            __syncthreads();
+            if (kept == 0) return;
+            // the next bucket's particles are in flight while one is tested
+            int cnt;
+            int64_t p0 = bucket_start(H, __builtin_amdgcn_readfirstlane(L.S.list[0]), cnt);
+            bool on = lane < cnt;
+            int64_t p = p0 + (on ? lane : 0);
+            double x = sx[p], y = sy[p], z = sz[p];
+            for (int i = 0; i < kept; ++i) {
+                const double cx = x, cy = y, cz = z;
+                const uint32_t cp = (uint32_t)p;
+                const bool con = on;
+                if (i + 1 < kept) {
+                    p0 = bucket_start(H, __builtin_amdgcn_readfirstlane(L.S.list[i + 1]), cnt);
+                    on = lane < cnt;
+                    p = p0 + (on ? lane : 0);
+                    x = sx[p]; y = sy[p]; z = sz[p];
+                }
+                bool keep = false;
+                for (int q = 0; q < nq; ++q)
+                    keep |= group_point_dist2(L.S.group[q], cx, cy, cz) <= L.S.group[q][6];
+                const unsigned long long m = __ballot(con && keep);
+                if (con && keep) {
+                    const int at = bn + __popcll(m & ((1ull << lane) - 1ull));
+                    L.x[at] = cx;
+                    L.y[at] = cy;
+                    L.z[at] = cz;
+                    L.p[at] = cp;
+                }
+                bn += __popcll(m);
+                if (bn >= kBucket) {
+                    process(bn);
+                    bn = 0;
+                }
+            }
+        };
+        search_walk(H, nodes, n_buckets, L.S,
+                    [&](int64_t c) {
+                        bool in = false;
+                        for (int q = 0; q < nq; ++q)
+                            in |= group_box_dist2(L.S.group[q], box + 6 * c) <= L.S.group[q][6];
+                        return in;
+                    },
+                    drain);
+        if (bn > 0) process(bn);
     };
     // histogram of the distances in [a, z] over kKnnBins bins from lo
     auto histogram = [&](bool on, double a, double z, double lo, double inv)
         __attribute__((always_inline)) {
         if (on)
             for (int q = 0; q < kKnnBins; ++q) L.hist[q][lane] = 0u;
-        visit(z * (1.0 + 1e-9), !on, [&](int64_t p, const double4& c) {
-            const double d2 = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-            if (on && p != mypos && d2 >= a && d2 <= z)
-                atomicAdd(&L.hist[bin_of(d2, lo, inv)][lane], 1u);
+        visit(z * (1.0 + 1e-9), !on, [&](const uint32_t (&p)[kKnnGroup],
+                                         const double (&d2)[kKnnGroup]) {
+#pragma unroll
+            for (int u = 0; u < kKnnGroup; ++u)
+                if (on && p[u] != mypos && d2[u] >= a && d2[u] <= z)
+                    atomicAdd(&L.hist[bin_of(d2[u], lo, inv)][lane], 1u);
         });
         __syncthreads();
     };
@@ -235,12 +289,23 @@ __global__ __launch_bounds__(kBucket) void k_knn(
             for (int q = 0; q < kKnnSurv; ++q) best[q] = INFINITY;
             double mn = INFINITY, mxv = -INFINITY;
             const bool collect = !done && inb <= kKnnSurv;
-            visit(shell2 * (1.0 + 1e-9), done, [&](int64_t p, const double4& c) {
-                const double d2 = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-                if (!done && p != mypos && d2 >= a && d2 <= z && bin_of(d2, lo, inv) == sel) {
-                    mn = fmin(mn, d2);
-                    mxv = fmax(mxv, d2);
-                    if (collect) insert_sorted(best, d2);
+            visit(shell2 * (1.0 + 1e-9), done, [&](const uint32_t (&p)[kKnnGroup],
+                                                   const double (&d2)[kKnnGroup]) {
+                bool hit[kKnnGroup], any = false;
+#pragma unroll
+                for (int u = 0; u < kKnnGroup; ++u) {
+                    hit[u] = !done & (p[u] != mypos) & (d2[u] >= a) & (d2[u] <= z) &
+                             (bin_of(d2[u], lo, inv) == sel);
+                    any |= hit[u];
+                }
+                if (!__ballot(any)) return;
+                for (int u = 0; u < kKnnGroup; ++u) {
+                    if (!__ballot(hit[u])) continue;
+                    if (hit[u]) {
+                        mn = fmin(mn, d2[u]);
+                        mxv = fmax(mxv, d2[u]);
+                        if (collect) insert_sorted(best, d2[u]);
+                    }
                 }
             });
             bool refine = false;
@@ -280,42 +345,45 @@ __global__ __launch_bounds__(kBucket) void k_knn(
         const double d = fmin(fmax(2.0 / (double)k, 0.01), 0.06);
         const double rlo = h0 * (1.0 - d), rhi = h0 * (1.0 + d);
         const double blo = rlo * rlo, bhi = rhi * rhi;
-        // below the band; kept band values (the band's smallest when it holds
-        // more than kKnnBand); the slot of the largest kept value when full
-        int nlo = 0, kept = 0, imax = 0;
-        auto find_max = [&]() {
-            imax = 0;
-            for (int q = 1; q < kKnnBand; ++q)
-                if (band_get(L, q, lane) > band_get(L, imax, lane)) imax = q;
-        };
-        visit(bhi * (1.0 + 1e-9), !act, [&](int64_t p, const double4& c) {
-            const double d2 = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-            if (!act || p == mypos || d2 > bhi) return;
-            if (d2 < blo) {
-                ++nlo;
-            } else if (kept < kKnnBand) {
-                band_put(L, kept, lane, d2);
-                if (++kept == kKnnBand) find_max();
-            } else if (d2 < band_get(L, imax, lane)) {
-                band_put(L, imax, lane, d2);
-                find_max();
+        // below the band; candidates in the band, listed in the lane's column
+        int nlo = 0, kept = 0;
+        visit(bhi * (1.0 + 1e-9), !act, [&](const uint32_t (&p)[kKnnGroup],
+                                            const double (&d2)[kKnnGroup]) {
+#pragma unroll
+            for (int u = 0; u < kKnnGroup; ++u) {
+                const bool other = act & (p[u] != mypos), lo = d2[u] < blo;
+                nlo += other & lo;
+                if (other & !lo & (d2[u] <= bhi)) {
+                    L.hist[min(kept, kKnnBins - 1)][lane] = p[u];
+                    ++kept;
+                }
             }
         });
-        // the k-th distance has rank r (0-based) in the band; it is a kept
-        // value iff 0 <= r < kept
+        // the k-th distance has rank r (0-based) in the band: the r-th of the
+        // listed candidates' distances (evaluated again) when the list holds
+        // the whole band
         const int r = k - nlo - 1;
-        if (!act || r < 0 || r >= kept) kept = 0;
-        double d2k = NAN;
-        for (int q = 0; q < kept; ++q) {   // the kept value with r below it and r + 1 up to it
-            const double v = band_get(L, q, lane);
-            int less = 0, upto = 0;
-            for (int t = 0; t < kept; ++t) {
-                const double w = band_get(L, t, lane);
-                less += w < v;
-                upto += w <= v;
+        const bool ok = act && r >= 0 && r < kept && r < kKnnBand && kept <= kKnnBins;
+        if (!ok) kept = 0;
+        __syncthreads();
+        double best[kKnnBand];
+#pragma unroll
+        for (int q = 0; q < kKnnBand; ++q) best[q] = INFINITY;
+        for (int q = 0; __ballot(q < kept); q += kKnnGroup) {
+            double v[kKnnGroup];
+#pragma unroll
+            for (int u = 0; u < kKnnGroup; ++u) {
+                const uint32_t p = q + u < kept ? L.hist[q + u][lane] : mypos;
+                v[u] = dist2_exact(xi, yi, zi, sx[p], sy[p], sz[p]);
             }
-            if (less <= r && r < upto) d2k = v;
+#pragma unroll
+            for (int u = 0; u < kKnnGroup; ++u)
+                insert_sorted(best, q + u < kept ? v[u] : INFINITY);
         }
+        double d2k = NAN;
+#pragma unroll
+        for (int q = 0; q < kKnnBand; ++q)
+            if (ok && q == r) d2k = best[q];
         __syncthreads();   // the band columns are read before the histograms reuse them
         return d2k;
     };
@@ -324,63 +392,32 @@ __global__ __launch_bounds__(kBucket) void k_knn(
     const bool warm = isfinite(hint) && hint > 0.0 && hint * hint <= diag2;
     double u2 = kKnnWarm * hint * hint;
     if (__ballot(in_bucket && !warm)) {
-        // the lane's own compact sub-range (members of another sub-range of
-        // the bucket can be far away)
-        int go = 0, gc = B.count;
-        for (int g = 0; g < sub_n[b]; ++g) {
-            const SubRange R = sub[kSubMax * b + g];
-            if (lane >= R.off && lane < R.off + R.cnt) {
-                go = R.off;
-                gc = R.cnt;
-            }
-        }
-        // an estimate: the m-th nearest member of that sub-range (m <= 8),
-        // scaled to k neighbours
+        // an estimate: the m-th nearest (m <= 8) of the particles up to a bucket
+        // before and after this one in sorted order, scaled to k neighbours
         constexpr int kM = 8;
         double best[kM];
 #pragma unroll
         for (int q = 0; q < kM; ++q) best[q] = INFINITY;
-        const int64_t p0 = B.start;
-        for (int j = 0; j < B.count; ++j) {
-            const double4 c = sp4[p0 + j];
-            if (p0 + j == mypos || j < go || j >= go + gc) continue;
-            double v = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-#pragma unroll
-            for (int q = 0; q < kM; ++q) {
-                const double lo = fmin(best[q], v);
-                v = fmax(best[q], v);
-                best[q] = lo;
-            }
+        const int64_t q0 = max(B.start - kBucket, H.sbase);
+        const int64_t q1 = min(B.start + 2 * kBucket, H.sbase + H.n);
+        for (int64_t q = q0; q < q1; ++q) {
+            const double v = dist2_exact(xi, yi, zi, sx[q], sy[q], sz[q]);
+            const bool nearer = (uint32_t)q != mypos && v < best[kM - 1];
+            if (!__ballot(nearer)) continue;
+            insert_sorted(best, nearer ? v : INFINITY);
         }
-        const int m = min(min(kM, k), gc - 1);
+        const int m = min(min(kM, k), (int)(q1 - q0) - 1);
         double rm2 = 0.0;
 #pragma unroll
         for (int q = 0; q < kM; ++q)
             if (q == m - 1) rm2 = best[q];
-        // With fewer than four members to go by (a sub-range cut off by a
-        // jump of the Morton curve) an estimate can exceed the true radius
-        // many times, and in the dense centre such a sphere holds a large
-        // part of the halo (one wave then streams most of it); those
-        // representatives start instead from the halo's diagonal / N, far
-        // below any neighbour distance, and grow.
-        double e2 = (m >= 4 && rm2 > 0.0 && rm2 < INFINITY)
-                        ? 1.44 * rm2 * pow((double)k / (double)m, 2.0 / 3.0)
+        // (from the halo's diagonal / N, far below any neighbour distance, where
+        // there are too few to go by)
+        double e2 = m >= 1 && rm2 > 0.0 && rm2 < INFINITY
+                        ? kKnnCold * rm2 * pow((double)k / (double)m, 2.0 / 3.0)
                         : diag2 / ((double)H.n * (double)H.n);
         if (!(e2 > 0.0)) e2 = 1.0;
-        // The first member of each sub-range is resolved from the estimate
-        // alone; every other member then starts as if warm, from 1.15 times
-        // that representative's h (the kernel size varies slowly across a
-        // compact sub-range).  The estimate errs by a factor of a few in
-        // volume, and taken by all 64 lanes it cost four times the warm
-        // candidate stream; taken by the few representatives it costs one
-        // such stream.
-        // (Where a bucket is split over waves, the first of the wave's own
-        // members: without one the others would start from the estimate.)
-        const int first = max(go, part * (kBucket / split));
-        const bool rep = in_bucket && lane == first;
-        const double d2r = resolve(rep, warm ? u2 : 0.25 * e2);
-        const double c2 = kKnnWarm * __shfl(d2r, first);
-        if (!warm) u2 = (isfinite(c2) && c2 > 0.0) ? fmin(c2, e2) : e2;
+        if (!warm) u2 = e2;
     }
     double d2k = NAN;
     bool todo = in_bucket;
@@ -399,89 +436,147 @@ __global__ __launch_bounds__(kBucket) void k_knn(
 
     // Neighbour lists: the members of the sphere of the k-th distance, as
     // sorted positions in the particle's row (k_knn_list_order puts them in
-    // (d2, id) order and turns them into ids): first every candidate strictly
-    // closer than the k-th (fewer than k), then the candidates at exactly that
-    // distance, keeping the smallest ids when they are more than the rest.
-    uint32_t* row = nbr + (int64_t)(in_bucket ? perm[mypos] : 0) * k_max;
+    // (d2, id) order and turns them into ids).  The candidates strictly closer
+    // than the k-th (fewer than k) are staged in the lane's LDS column, entry q
+    // in column (lane + q) mod 64, and written out row by row (stores of
+    // single entries, each lane to a row of its own, took 18 of the 21 ms of a
+    // warm call at N = 2^20).  Candidates at exactly the k-th distance fill
+    // the rest: one as a rule; when they are more than the rest, those with the
+    // smallest ids, in a visit of their own.
+    const uint32_t my_row = in_bucket ? perm[mypos] : 0u;
     const bool on = in_bucket && isfinite(d2k);
-    int cnt = 0;
-    visit(d2k * (1.0 + 1e-9), !on, [&](int64_t p, const double4& c) {
-        const double d2 = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-        if (on && p != mypos && d2 < d2k && cnt < k) row[cnt++] = (uint32_t)p;
-    });
-    const int need = k - cnt;
-    int nt = 0;
-    visit(d2k * (1.0 + 1e-9), !on, [&](int64_t p, const double4& c) {
-        const double d2 = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-        if (!(on && p != mypos && d2 == d2k && need > 0)) return;
-        if (nt < need) {
-            row[cnt + nt++] = (uint32_t)p;
-            return;
+    int cnt = 0, staged = 0, ties = 0;
+    uint32_t tie = 0u;
+    auto flush = [&]() {
+        __syncthreads();
+        unsigned long long act = __ballot(staged > 0);
+        while (act) {
+            const int r = __ffsll((long long)act) - 1;
+            act &= act - 1ull;
+            const int n = __shfl(staged, r, 64), base = __shfl(cnt, r, 64);
+            const uint32_t row = __shfl(my_row, r, 64);
+            if (lane < n)
+                nbr[(int64_t)row * k_max + base + lane] = L.hist[lane][(r + lane) & 63];
         }
-        int worst = 0;
-        uint32_t wid = 0;
-        for (int q = 0; q < need; ++q) {
-            const uint32_t iq = sid[row[cnt + q]];
-            if (iq >= wid) {
-                wid = iq;
-                worst = q;
+        cnt += staged;
+        staged = 0;
+        __syncthreads();
+    };
+    visit(d2k * (1.0 + 1e-9), !on, [&](const uint32_t (&p)[kKnnGroup],
+                                       const double (&d2)[kKnnGroup]) {
+#pragma unroll
+        for (int u = 0; u < kKnnGroup; ++u) {
+            const bool other = on & (p[u] != mypos);
+            if (other & (d2[u] < d2k)) {
+                L.hist[staged][(lane + staged) & 63] = p[u];
+                ++staged;
             }
+            const bool same = other & (d2[u] == d2k);
+            tie = same ? p[u] : tie;
+            ties += same;
         }
-        if (sid[p] < wid) row[cnt + worst] = (uint32_t)p;
+        if (__ballot(staged > kKnnBins - kKnnGroup)) flush();
+    });
+    flush();
+    const int need = on ? k - cnt : 0;
+    if (on && ties == 1 && need == 1) nbr[(int64_t)my_row * k_max + cnt] = tie;
+    const bool more = on && !(ties == 1 && need == 1);
+    if (!__ballot(more)) return;
+    uint32_t* row = nbr + (int64_t)my_row * k_max;
+    int nt = 0;
+    visit(d2k * (1.0 + 1e-9), !more, [&](const uint32_t (&p)[kKnnGroup],
+                                         const double (&d2)[kKnnGroup]) {
+        for (int u = 0; u < kKnnGroup; ++u) {
+            if (!(more && p[u] != mypos && d2[u] == d2k && need > 0)) continue;
+            if (nt < need) {
+                row[cnt + nt++] = p[u];
+                continue;
+            }
+            int worst = 0;
+            uint32_t wid = 0;
+            for (int q = 0; q < need; ++q) {
+                const uint32_t iq = sid[row[cnt + q]];
+                if (iq >= wid) {
+                    wid = iq;
+                    worst = q;
+                }
+            }
+            if (sid[p[u]] < wid) row[cnt + worst] = p[u];
+        }
     });
 }
 
-// The rows k_knn collected, in (d2, id) order, as ids: one thread per
-// particle, the distances recomputed with the same expression.
-__global__ __launch_bounds__(kStreamBlock) void k_knn_list_order(
-    const StreamBlock* __restrict__ blocks, const HaloDev* __restrict__ halos,
-    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const double4* __restrict__ sp4, const uint32_t* __restrict__ sid, int k_max,
-    uint32_t* __restrict__ nbr)
+// The rows k_knn collected, in (d2, id) order, as ids: one wave per particle,
+// two entries per lane, each entry's place the number of entries before it (the
+// distances recomputed with the same expression).  One thread per particle
+// with an insertion sort in scratch memory took 0.80 ms for 200003 rows of 32.
+constexpr int kListWaves = 4;
+static_assert(SIDM_MAX_K <= 128, "two entries per lane");
+__global__ __launch_bounds__(64 * kListWaves) void k_knn_list_order(
+    const uint32_t* __restrict__ perm, const BucketInfo* __restrict__ buckets,
+    const HaloDev* __restrict__ halos, const double* __restrict__ sx,
+    const double* __restrict__ sy, const double* __restrict__ sz, const double* __restrict__ sh,
+    const uint32_t* __restrict__ sid, int k_max, uint32_t* __restrict__ nbr)
 {
-    const StreamBlock B = blocks[blockIdx.x];
-    const int t = threadIdx.x;
-    if (t >= B.count) return;
-    const HaloDev& H = halos[B.halo];
-    const int64_t i = B.start + t;
-    const int k = H.k;
-    uint32_t* row = nbr + i * (int64_t)k_max;
-    const double xi = x[i], yi = y[i], zi = z[i];
-    double d[SIDM_MAX_K];
-    uint32_t id[SIDM_MAX_K];
-    for (int q = 0; q < k; ++q) {
-        const uint32_t p = row[q];
-        const double4 c = sp4[p];
-        const double d2 = dist2_exact(xi, yi, zi, c.x, c.y, c.z);
-        const uint32_t iq = sid[p];
-        int pos = q;
-        while (pos > 0 && (d2 < d[pos - 1] || (d2 == d[pos - 1] && iq < id[pos - 1]))) {
-            d[pos] = d[pos - 1];
-            id[pos] = id[pos - 1];
-            --pos;
+    __shared__ double d2s[kListWaves][SIDM_MAX_K];
+    __shared__ uint32_t ids[kListWaves][SIDM_MAX_K];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const BucketInfo B = buckets[blockIdx.x];
+    const int k = halos[B.halo].k;
+    for (int i = wv; i < B.count; i += kListWaves) {
+        const int64_t me = B.start + i;
+        if (!isfinite(sh[me])) continue;   // a failed search has no row
+        uint32_t* row = nbr + (int64_t)perm[me] * k_max;
+        const double xi = sx[me], yi = sy[me], zi = sz[me];
+        double d[2];
+        uint32_t id[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int q = lane + 64 * u;
+            d[u] = INFINITY;
+            id[u] = 0u;
+            if (q < k) {
+                const uint32_t p = row[q];
+                d[u] = dist2_exact(xi, yi, zi, sx[p], sy[p], sz[p]);
+                id[u] = sid[p];
+                d2s[wv][q] = d[u];
+                ids[wv][q] = id[u];
+            }
         }
-        d[pos] = d2;
-        id[pos] = iq;
+        // a wave's own LDS rows, read back in program order
+        __builtin_amdgcn_wave_barrier();
+        int at[2] = {0, 0};
+        for (int q = 0; q < k; ++q) {
+            const double dq = d2s[wv][q];
+            const uint32_t iq = ids[wv][q];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                at[u] += dq < d[u] || (dq == d[u] && iq < id[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (lane + 64 * u < k) row[at[u]] = id[u];
+        __builtin_amdgcn_wave_barrier();
     }
-    for (int q = 0; q < k; ++q) row[q] = id[q];
 }
 
 hipError_t launch_knn(const Plan& P, const sidm_state* s, Scratch& w, uint32_t* nbr, int k_max,
                       hipStream_t st)
 {
     const int split = search_split(P.n_buckets, kKnnSplitMax);
-    const dim3 grid((unsigned)(P.n_buckets * split));
+    auto search = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(P.n_buckets * split)), dim3(kBucket), 0, st,
+                           w.halos, w.buckets, w.nodes, w.box, w.sub, w.sub_n, P.n_buckets, w.sx,
+                           w.sy, w.sz, w.perm, w.sh, s->h, w.status, w.sid, nbr, k_max, split);
+    };
     if (!nbr) {
-        hipLaunchKernelGGL(k_knn<false>, grid, dim3(kBucket), 0, st,
-                           w.halos, w.buckets, w.nodes, w.box, w.sub, w.sub_n, w.cbox, P.n_buckets,
-                           w.sp4, w.perm, w.sh, s->h, w.status, w.sid, nbr, k_max, split);
+        search(k_knn<false>);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_knn<true>, grid, dim3(kBucket), 0, st, w.halos,
-                       w.buckets, w.nodes, w.box, w.sub, w.sub_n, w.cbox, P.n_buckets, w.sp4, w.perm,
-                       w.sh, s->h, w.status, w.sid, nbr, k_max, split);
-    hipLaunchKernelGGL(k_knn_list_order, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0,
-                           st, w.blocks, w.halos, s->x, s->y, s->z, w.sp4, w.sid, k_max, nbr);
+    search(k_knn<true>);
+    hipLaunchKernelGGL(k_knn_list_order, dim3((unsigned)P.n_buckets), dim3(64 * kListWaves), 0,
+                       st, w.perm, w.buckets, w.halos, w.sx, w.sy, w.sz, w.sh, w.sid, k_max,
+                       nbr);
     return hipGetLastError();
 }
 

@@ -11,49 +11,9 @@
 // radix digit (k_sort_pass).
 #include "sidm_plan.hpp"
 #include "sidm_steps.hpp"
+#include "sidm_wave.hpp"
 
 namespace sidm {
-
-// ---------------------------------------------------------------- wave reductions
-// v moved by a DPP control (rotations within rows of 16 lanes)
-template <int CTRL>
-__device__ inline double dpp_f64(double v)
-{
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// Minimum / maximum over each row of 16 lanes, on every lane of the row.
-__device__ inline double row_min(double v)
-{
-    v = fmin(v, dpp_f64<0x128>(v));   // row_ror:8
-    v = fmin(v, dpp_f64<0x124>(v));
-    v = fmin(v, dpp_f64<0x122>(v));
-    return fmin(v, dpp_f64<0x121>(v));
-}
-
-__device__ inline double row_max(double v)
-{
-    v = fmax(v, dpp_f64<0x128>(v));
-    v = fmax(v, dpp_f64<0x124>(v));
-    v = fmax(v, dpp_f64<0x122>(v));
-    return fmax(v, dpp_f64<0x121>(v));
-}
-
-// ... and over the rows of the wave (v uniform within each row).
-__device__ inline double rows_min(double v)
-{
-    v = fmin(v, __shfl_xor(v, 16, 64));
-    return fmin(v, __shfl_xor(v, 32, 64));
-}
-
-__device__ inline double rows_max(double v)
-{
-    v = fmax(v, __shfl_xor(v, 16, 64));
-    return fmax(v, __shfl_xor(v, 32, 64));
-}
 
 // ---------------------------------------------------------------- bounding boxes
 // Box and mass range of a workgroup's particles: per-thread extrema e (min x,
@@ -483,19 +443,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
 }
 
 // ---------------------------------------------------------------- permute and boxes
-// Box of the lanes [lo, hi) of the wave, on every lane.
-__device__ inline void range_box(int lo, int hi, int lane, double px, double py, double pz,
-                                 double* o)
-{
-    const bool in = lane >= lo && lane < hi;
-    o[0] = rows_min(row_min(in ? px : INFINITY));
-    o[1] = rows_min(row_min(in ? py : INFINITY));
-    o[2] = rows_min(row_min(in ? pz : INFINITY));
-    o[3] = rows_max(row_max(in ? px : -INFINITY));
-    o[4] = rows_max(row_max(in ? py : -INFINITY));
-    o[5] = rows_max(row_max(in ? pz : -INFINITY));
-}
-
 __device__ inline double box_diag2(const double* b)
 {
     const double ex = b[3] - b[0], ey = b[4] - b[1], ez = b[5] - b[2];
@@ -517,8 +464,8 @@ __device__ inline int split_range(int lo, int hi, int lane, unsigned long long k
     const bool low = lane >= lo && lane < hi && !(((key ^ kf) >> hb) & 1ull);
     const int s = lo + __popcll(__ballot(low));
     if (s <= lo || s >= hi) return -1;
-    range_box(lo, s, lane, px, py, pz, ba);
-    range_box(s, hi, lane, px, py, pz, bb);
+    lanes_box(lane >= lo && lane < s, px, py, pz, ba);
+    lanes_box(lane >= s && lane < hi, px, py, pz, bb);
     const double before = (hi - lo) * sqrt(box_diag2(full));
     const double after = (s - lo) * sqrt(box_diag2(ba)) + (hi - s) * sqrt(box_diag2(bb));
     return after < 0.5 * before ? s : -1;

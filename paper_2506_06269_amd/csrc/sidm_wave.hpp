@@ -1,0 +1,61 @@
+// sidm_wave.hpp -- reductions over the lanes of a wave.
+#pragma once
+
+#include "sidm_internal.hpp"
+
+namespace sidm {
+
+#ifdef __HIPCC__
+// v moved by a DPP control (rotations within rows of 16 lanes)
+template <int CTRL>
+__device__ inline double dpp_f64(double v)
+{
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Minimum / maximum over each row of 16 lanes, on every lane of the row.
+__device__ inline double row_min(double v)
+{
+    v = fmin(v, dpp_f64<0x128>(v));   // row_ror:8
+    v = fmin(v, dpp_f64<0x124>(v));
+    v = fmin(v, dpp_f64<0x122>(v));
+    return fmin(v, dpp_f64<0x121>(v));
+}
+
+__device__ inline double row_max(double v)
+{
+    v = fmax(v, dpp_f64<0x128>(v));
+    v = fmax(v, dpp_f64<0x124>(v));
+    v = fmax(v, dpp_f64<0x122>(v));
+    return fmax(v, dpp_f64<0x121>(v));
+}
+
+// ... and over the rows of the wave (v uniform within each row).
+__device__ inline double rows_min(double v)
+{
+    v = fmin(v, __shfl_xor(v, 16, 64));
+    return fmin(v, __shfl_xor(v, 32, 64));
+}
+
+__device__ inline double rows_max(double v)
+{
+    v = fmax(v, __shfl_xor(v, 16, 64));
+    return fmax(v, __shfl_xor(v, 32, 64));
+}
+
+// Box (lo xyz, hi xyz) of the positions of the lanes with `in` set.
+__device__ inline void lanes_box(bool in, double px, double py, double pz, double* o)
+{
+    o[0] = rows_min(row_min(in ? px : INFINITY));
+    o[1] = rows_min(row_min(in ? py : INFINITY));
+    o[2] = rows_min(row_min(in ? pz : INFINITY));
+    o[3] = rows_max(row_max(in ? px : -INFINITY));
+    o[4] = rows_max(row_max(in ? py : -INFINITY));
+    o[5] = rows_max(row_max(in ? pz : -INFINITY));
+}
+#endif
+
+}  // namespace sidm
