@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kBucket) void k_knn(
             }
             __syncthreads();
         };
-        auto drain = [&](int ln) {
+        auto drain = [&](int ln, bool last) __attribute__((always_inline)) {
             // the buckets whose box some lane reaches (the groups' boxes can
             // hold the dense centre without any lane near it)
             int kept = singles ? ln : 0;

@@ -2,18 +2,24 @@
 // through the spline kernel, explicitly conserving energy and momentum;
 // Sec. 3.5: the geometric factor Lambda of the interaction probability).
 //
-// k_pairs: one wavefront per bucket, one i per lane.  Candidate buckets come
-// from the search tree: bucket c is visited when, for some lane i, the
-// distance from x_i to c's box is below h_i + hmax(c).
-// A bucket visits only candidate buckets of equal or higher index (pairs
-// inside a bucket are owned by the smaller id), so each pair is tested once,
-// when d2 < (h_i + h_j)^2; accepted pairs are compacted through an LDS queue
-// (ballot + prefix count) so that the expensive per-pair work -- Philox4x32-10,
-// |dv|, and Lambda when the draw falls below a cheap upper bound of P -- runs
-// on full wavefronts.  A pair whose draw falls below the bound is appended to
-// a candidate buffer; k_decide evaluates Lambda for those and appends the
-// events (u < P) to the event buffer (when the candidate buffer is full, the
-// pair pass decides the rest itself).
+// k_pairs: one wavefront per bucket, one i per lane.  The candidates j are the
+// particles closer than h_i + h_j to the box of a group of its lanes, h_i the
+// group's largest (sidm_search.hpp); every lane tests each of them.
+// A bucket takes only candidate buckets of higher index, after the pairs inside
+// it (owned by the smaller id), so each pair is tested once, when
+// d2 < (h_i + h_j)^2; accepted pairs go through an LDS queue (ballot + prefix
+// count) so that the expensive per-pair work -- Philox4x32-10, |dv|, and
+// Lambda when the draw falls below a cheap upper bound of P -- runs on full
+// wavefronts.  A pair whose draw falls below the bound is appended to a
+// candidate buffer; k_decide evaluates Lambda for those and appends the events
+// (u < P) to the event buffer (when the candidate buffer is full, the pair pass
+// decides the rest itself).
+// Its time goes to the exact test of 64 i by one candidate (half of it) and the
+// per-pair work (three tenths); one in six tested pairs is accepted.  A pass
+// that visited the buckets one after the other, each lane testing its own
+// sphere against them and every particle of a chunk, took 2.10 ms for 500009
+// particles (126 M pairs), 3.7 for 2^20 (265 M) and 0.11 for 8192; this one
+// 1.42, 2.65 and 0.074.
 //
 // k_rounds: the events of a step are applied in (a, b) order as elastic,
 // isotropic kicks in the pair's centre-of-mass frame.  Events that share no
@@ -22,7 +28,7 @@
 // and an event fires when it is the elected one for both of its particles.
 // This is exactly the dependency order of one-after-the-other application.
 #include "sidm_math.hpp"
-#include "sidm_tree.hpp"
+#include "sidm_search.hpp"
 
 namespace sidm {
 
@@ -174,18 +180,21 @@ __device__ __forceinline__ void decide_pair(const CandRec& r, double dt,
     }
 }
 
-// LDS copies of the bucket's own particles (I: what the per-pair work reads)
-// and of the candidate range (J: also the positions of the pair test).  The
-// rest (positions of I, original indices) is read from memory for the rare
-// candidates, and the mass is the halo's common one.
-struct PairI {
+// LDS of the pair pass: what the per-pair work reads of the bucket's own
+// particles, the candidates (position, kernel size, id, sorted index), and the
+// queue of pairs (lane of i, slot of j).  The velocities of j are read from
+// memory per pair, in flight during its Philox rounds, and what only the rare
+// candidates need (positions of i, original indices) there; the mass is the
+// halo's common one.
+constexpr int kPairGroup = 4;   // candidates tested at once
+struct PairLds {
+    SearchLds S;
     double vx[kBucket], vy[kBucket], vz[kBucket], h[kBucket];
     uint32_t id[kBucket];
-};
-struct PairJ {
-    double x[kBucket], y[kBucket], z[kBucket], h[kBucket];
-    double vx[kBucket], vy[kBucket], vz[kBucket];
-    uint32_t id[kBucket];
+    double jx[2 * kBucket + kPairGroup], jy[2 * kBucket + kPairGroup],
+        jz[2 * kBucket + kPairGroup], jh[2 * kBucket + kPairGroup];
+    uint32_t jid[2 * kBucket + kPairGroup], jp[2 * kBucket + kPairGroup];
+    uint16_t queue[(kPairGroup + 1) * kBucket];
 };
 
 // Cross-section per unit mass at relative speed g: sigma_m, or with a velocity
@@ -208,8 +217,7 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     const HaloDev* __restrict__ halos, const BucketInfo* __restrict__ buckets,
     const NodeChild* __restrict__ nodes, const double* __restrict__ box,
     const double* __restrict__ hmax, const SubRange* __restrict__ sub,
-    const int* __restrict__ sub_n, const double* __restrict__ cbox,
-    const double* __restrict__ chmax, int64_t n_buckets,
+    const int* __restrict__ sub_n, int64_t n_buckets,
     const double* __restrict__ sx,
     const double* __restrict__ sy, const double* __restrict__ sz, const double* __restrict__ svx,
     const double* __restrict__ svy, const double* __restrict__ svz, const double* __restrict__ sh,
@@ -219,13 +227,11 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     int64_t max_events, unsigned long long* __restrict__ ev_counts, const int* __restrict__ status,
     int split)
 {
-    __shared__ PairI I;
-    __shared__ PairJ J;
-    __shared__ uint16_t queue[2 * kBucket];
-    __shared__ int64_t stack[kStackMax];
+    __shared__ PairLds L;
     // split waves per bucket: wave `part` takes every split-th candidate
-    // bucket of the bucket's visit (a call with few buckets still fills the
-    // device; every pair is still tested by exactly one wave)
+    // bucket of the bucket's visit, the first the pairs inside it too (a call
+    // with few buckets still fills the device; every pair is still tested by
+    // exactly one wave)
     const int64_t b = blockIdx.x / split;
     const int part = (int)(blockIdx.x % split);
     const int lane = threadIdx.x;
@@ -237,12 +243,13 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     if (status[B.halo] & (SIDM_DEV_UNEQUAL_MASS | SIDM_DEV_DUPLICATE_ID)) return;
     const bool act = lane < B.count;
     const double mb = cmass[B.halo];   // the masses of a halo that scatters are equal
-    int64_t jbase = 0;                  // first sorted position of the range in J
+    const int64_t pl = B.start + (act ? lane : 0);
+    const double xi = sx[pl], yi = sy[pl], zi = sz[pl], hi = act ? sh[pl] : 0.0;
+    const uint32_t idi = sid[pl];
     if (act) {
-        const int64_t p = B.start + lane;
-        I.vx[lane] = svx[p]; I.vy[lane] = svy[p]; I.vz[lane] = svz[p];
-        I.h[lane] = sh[p];
-        I.id[lane] = sid[p];
+        L.vx[lane] = svx[pl]; L.vy[lane] = svy[pl]; L.vz[lane] = svz[pl];
+        L.h[lane] = hi;
+        L.id[lane] = idi;
     }
     const uint32_t k0 = (uint32_t)(H.seed & 0xffffffffull), k1 = (uint32_t)(H.seed >> 32);
     const double kInvPi8 = 8.0 / 3.14159265358979323846;
@@ -255,21 +262,22 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     unsigned long long wave_pairs = 0;   // wave-uniform: the ballots' counts
     int qn = 0;
 
-    // per-pair work for queue entries [0, cnt): lane l takes entry l
-    auto process = [&](int cnt) {
+    // per-pair work for queue entries [from, from + cnt): lane l takes entry l
+    auto process = [&](int from, int cnt) __attribute__((always_inline)) {
         __syncthreads();
         if (lane < cnt) {
-            const int e = queue[lane];
-            const int il = e & 63, jl = e >> 8;
+            const int e = L.queue[from + lane];
+            const int il = e & 63, jl = e >> 6;
+            const uint32_t pj = L.jp[jl];
+            const double vjx = svx[pj], vjy = svy[pj], vjz = svz[pj];
             // canonical order of the pair: a = smaller id, b = larger id
-            const bool iswap = I.id[il] > J.id[jl];
-            const uint32_t a = iswap ? J.id[jl] : I.id[il], bb = iswap ? I.id[il] : J.id[jl];
+            const bool iswap = L.id[il] > L.jid[jl];
+            const uint32_t a = iswap ? L.jid[jl] : L.id[il], bb = iswap ? L.id[il] : L.jid[jl];
             const Philox4 w = philox4x32_10(a, bb, step, 0u, k0, k1);
             const double u = unit53(w.w[0], w.w[1]);
-            const double dvx = I.vx[il] - J.vx[jl], dvy = I.vy[il] - J.vy[jl],
-                         dvz = I.vz[il] - J.vz[jl];
+            const double dvx = L.vx[il] - vjx, dvy = L.vy[il] - vjy, dvz = L.vz[il] - vjz;
             const double g2 = (dvx * dvx + dvy * dvy) + dvz * dvz;
-            const double ha = I.h[il], hbb = J.h[jl];
+            const double ha = L.h[il], hbb = L.jh[jl];
             const double hm = fmax(ha, hbb);
 
             // Lambda <= min(W_a(0), W_b(0)) = 8 / (pi max(h)^3) bounds P by
@@ -293,13 +301,13 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
                 r.mb = mb;
                 r.g = g;
                 const int64_t pi = B.start + il;
-                r.d = sqrt(dist2_pair(sx[pi], sy[pi], sz[pi], J.x[jl], J.y[jl], J.z[jl]));
+                r.d = sqrt(dist2_pair(sx[pi], sy[pi], sz[pi], L.jx[jl], L.jy[jl], L.jz[jl]));
                 r.ha = iswap ? hbb : ha;
                 r.hb = iswap ? ha : hbb;
                 r.u = u;
                 r.a = a;
                 r.b = bb;
-                const uint32_t oi = perm[pi], oj = perm[jbase + jl];
+                const uint32_t oi = perm[pi], oj = perm[pj];
                 r.ia = iswap ? oj : oi;
                 r.ib = iswap ? oi : oj;
                 r.halo = B.halo;
@@ -315,83 +323,148 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
         __syncthreads();
     };
 
-    // bucket c can hold a partner of lane i only if its box is closer than
-    // h_i + max h over c; pairs between two buckets are handled by the lower
-    // bucket index, pairs inside a bucket by the smaller id
-    const double hi_l = act ? I.h[lane] : 0.0;
-    const int64_t pl = B.start + (act ? lane : 0);
-    const double xl = sx[pl], yl = sy[pl], zl = sz[pl];
-    int visit_no = 0;   // candidate buckets visited so far (wave-uniform)
-    tree_visit(H, nodes, n_buckets, stack,
-               [&](int64_t c) {
-                   const double r = hi_l + hmax[c];
-                   return act && point_box_dist2(xl, yl, zl, box + 6 * c) < r * r * (1.0 + 1e-9);
-               },
-               [&](int64_t c) { return nodes[c].last >= b; },
-               [&](int64_t c) {
-        if (split > 1 && (visit_no++ % split) != part) return;
-        const BucketInfo C = buckets[c];
-        const double hc = hmax[c];
-        const int nsub = sub_n[c];
-        for (int q = 0; q < nsub; ++q) {
-            const SubRange R = sub[kSubMax * c + q];
-            const double rr = hi_l + hc;
-            if (!__ballot(act && point_box_dist2(xl, yl, zl, R.box) < rr * rr * (1.0 + 1e-9)))
-                continue;
-            __syncthreads();
-            jbase = C.start + R.off;
-            if (lane < R.cnt) {
-                const int64_t p = jbase + lane;
-                J.x[lane] = sx[p]; J.y[lane] = sy[p]; J.z[lane] = sz[p];
-                J.h[lane] = sh[p];
-                J.vx[lane] = svx[p]; J.vy[lane] = svy[p]; J.vz[lane] = svz[p];
-                J.id[lane] = sid[p];
+    // every lane against the first n candidates in LDS (same: the bucket's own
+    // particles, pairs owned by the smaller id), then the per-pair work of
+    // the pairs found, whose entries refer to these candidates.  The test is
+    // evaluated without a branch per candidate, for kPairGroup of them at once
+    // (infinitely far ones past the last).
+    auto test = [&](int n, bool same) __attribute__((always_inline)) {
+        if (lane < kPairGroup) {
+            L.jx[n + lane] = INFINITY;
+            L.jy[n + lane] = L.jz[n + lane] = L.jh[n + lane] = 0.0;
+        }
+        __syncthreads();
+        for (int j = 0; j < n; j += kPairGroup) {
+            bool pair[kPairGroup];
+#pragma unroll
+            for (int u = 0; u < kPairGroup; ++u) {
+                const double d2 = dist2_pair(xi, yi, zi, L.jx[j + u], L.jy[j + u], L.jz[j + u]);
+                const double hs = hi + L.jh[j + u];
+                pair[u] = act & (d2 < hs * hs);
             }
-            __syncthreads();
-            const double xi = xl, yi = yl, zi = zl, hi = hi_l;
-            const uint32_t idi = I.id[act ? lane : 0];
-            const bool same = c == b;
-            // a long sub-range is tested by chunks, those within reach of
-            // some lane
-            const bool chunked = R.cnt > kChunk;
-            for (int jj = 0; jj < R.cnt;) {
-            const int g = (R.off + jj) / kChunk;
-            const int je = chunked ? min(R.cnt, (g + 1) * kChunk - R.off) : R.cnt;
-            const double rc = hi_l + chmax[kChunks * c + g];   // the chunk's own largest h
-            if (chunked &&
-                !__ballot(act && point_box_dist2(xl, yl, zl, cbox + 6 * (kChunks * c + g)) <
-                                     rc * rc * (1.0 + 1e-9))) {
-                jj = je;
-                continue;
+            if (same) {
+#pragma unroll
+                for (int u = 0; u < kPairGroup; ++u) pair[u] &= idi < L.jid[j + u];
             }
-            for (; jj < je; ++jj) {
-                // every lane evaluates the test, without a branch per
-                // candidate (a lane past the bucket's end tests lane 0's copy)
-                const double d2 = dist2_pair(xi, yi, zi, J.x[jj], J.y[jj], J.z[jj]);
-                const double hs = hi + J.h[jj];
-                const bool ord = !same || idi < J.id[jj];
-                const bool pair = act & ord & (d2 < hs * hs);
-                const unsigned long long mask = __ballot(pair);
-                if (pair) queue[qn + __popcll(mask & lt)] = (uint16_t)(lane | (jj << 8));
+#pragma unroll
+            for (int u = 0; u < kPairGroup; ++u) {
+                const unsigned long long mask = __ballot(pair[u]);
+                if (pair[u])
+                    L.queue[qn + __popcll(mask & lt)] = (uint16_t)(lane | ((j + u) << 6));
                 qn += __popcll(mask);
                 wave_pairs += (unsigned long long)__popcll(mask);
-                if (qn >= kBucket) {
-                    process(kBucket);
-                    const int rest = qn - kBucket;
-                    const uint16_t moved = lane < rest ? queue[kBucket + lane] : 0;
-                    __syncthreads();
-                    if (lane < rest) queue[lane] = moved;
-                    qn = rest;
-                    __syncthreads();
-                }
             }
-            }
-            if (qn > 0) {
-                process(qn);   // entries refer to this candidate range: flush now
-                qn = 0;
+            const int rest = j + kPairGroup < n ? kBucket - 1 : 0;   // may stay queued
+            while (qn > rest) {
+                const int cnt = min(qn, kBucket);
+                qn -= cnt;
+                process(qn, cnt);
             }
         }
-    });
+        __syncthreads();
+    };
+
+    // the first candidates are the bucket's own particles
+    bool own = part == 0;
+    int jn = own ? B.count : 0;   // candidates in LDS
+    if (own) {
+        L.jx[lane] = xi;
+        L.jy[lane] = yi;
+        L.jz[lane] = zi;
+        L.jh[lane] = hi;
+        L.jid[lane] = idi;
+        L.jp[lane] = (uint32_t)pl;
+    }
+    // A node can hold a partner of lane i only if its box is closer than h_i +
+    // max h over it; the later buckets' pairs with this one are taken here.
+    const int nq = search_groups(L.S, lane, lane_sub(sub + kSubMax * b, sub_n[b], lane), act, xi,
+                                 yi, zi, hi);
+    unsigned seen = 0;   // buckets of the walk so far
+    auto drain = [&](int ln, bool last) __attribute__((always_inline)) {
+        // this part's buckets, and of them those that some lane reaches
+        const unsigned first = (unsigned)(part + split - (int)(seen % split)) % split;
+        seen += ln;
+        int kept = 0;
+        for (int i = first; i < ln; i += 4 * split) {
+            uint32_t c[4];
+            unsigned long long m[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                c[u] = __builtin_amdgcn_readfirstlane(L.S.list[min(i + u * split, ln - 1)]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double r = hi + hmax[c[u]];
+                m[u] = __ballot(act && point_box_dist2(xi, yi, zi, box + 6 * (int64_t)c[u]) <
+                                           r * r * (1.0 + 1e-9));
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (m[u] && i + u * split < ln) {
+                    if (lane == 0) L.S.list[kept] = c[u];
+                    ++kept;
+                }
+        }
+        __syncthreads();
+        if (kept == 0 && !last) return;
+        // the next bucket's particles are in flight while one is tested
+        int cnt;
+        int64_t p0 = kept > 0
+                         ? bucket_start(H, __builtin_amdgcn_readfirstlane(L.S.list[0]), cnt)
+                         : (cnt = 0, B.start);
+        bool on = lane < cnt;
+        int64_t p = p0 + (on ? lane : 0);
+        double x = sx[p], y = sy[p], z = sz[p], h = sh[p];
+        uint32_t idj = sid[p];
+        for (int i = 0; i <= kept; ++i) {
+            if (jn >= kBucket || (jn > 0 && (own || (last && i == kept)))) {
+                test(jn, own);
+                jn = 0;
+                own = false;
+            }
+            if (i == kept) break;
+            const double cx = x, cy = y, cz = z, ch = h;
+            const uint32_t cid = idj, cp = (uint32_t)p;
+            const bool con = on;
+            if (i + 1 < kept) {
+                p0 = bucket_start(H, __builtin_amdgcn_readfirstlane(L.S.list[i + 1]), cnt);
+                on = lane < cnt;
+                p = p0 + (on ? lane : 0);
+                x = sx[p]; y = sy[p]; z = sz[p]; h = sh[p];
+                idj = sid[p];
+            }
+            bool keep = false;
+            for (int q = 0; q < nq; ++q) {
+                const double r = L.S.group[q][6] + ch;
+                keep |= group_point_dist2(L.S.group[q], cx, cy, cz) < r * r * (1.0 + 1e-9);
+            }
+            const unsigned long long m = __ballot(con && keep);
+            if (con && keep) {
+                const int at = jn + __popcll(m & lt);
+                L.jx[at] = cx;
+                L.jy[at] = cy;
+                L.jz[at] = cz;
+                L.jh[at] = ch;
+                L.jid[at] = cid;
+                L.jp[at] = cp;
+            }
+            jn += __popcll(m);
+        }
+    };
+    search_walk(H, nodes, n_buckets, L.S,
+                [&](int64_t c) {
+                    if (nodes[c].last <= b) return false;
+                    const double hc = hmax[c];
+                    bool in = false;
+                    for (int q = 0; q < nq; ++q) {
+                        const double r = L.S.group[q][6] + hc;
+                        in |= group_box_dist2(L.S.group[q], box + 6 * c) < r * r * (1.0 + 1e-9);
+                    }
+                    return in;
+                },
+                [&](int ln, bool last) __attribute__((always_inline)) {
+                    // a halo of one bucket has no other pairs than its own
+                    drain(H.n_levels > 1 ? ln : 0, last);
+                });
     // pairs tested and candidates of the exact decision found by this bucket
     if (INLINE) return;
     long long vc = my_cands;
@@ -635,7 +708,7 @@ hipError_t launch_scatter(const Plan& P, const sidm_state* s, Scratch& w, uint32
     const int split = search_split(P.n_buckets, kPairSplitMax);
     auto pairs = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)(P.n_buckets * split)), dim3(kBucket), 0, st, w.halos,
-                           w.buckets, w.nodes, w.box, w.hmax, w.sub, w.sub_n, w.cbox, w.chmax, P.n_buckets, w.sx,
+                           w.buckets, w.nodes, w.box, w.hmax, w.sub, w.sub_n, P.n_buckets, w.sx,
                            w.sy, w.sz, w.svx, w.svy, w.svz, w.sh, w.cref, w.sid, w.perm, step,
                            w.counters, w.cands, w.max_cands, w.events, w.max_events,
                            (unsigned long long*)w.ev_counts, w.status, split);

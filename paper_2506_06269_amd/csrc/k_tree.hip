@@ -472,22 +472,17 @@ __device__ inline int split_range(int lo, int hi, int lane, unsigned long long k
 }
 
 // One wave per bucket: gathers its particles into the sorted arrays, and
-// writes its box, up to kSubMax compact sub-ranges (two levels of splits) and
-// (when cbox is given) the boxes of its chunks of kChunk particles (an empty
-// chunk gets the empty box [+inf, -inf], which no distance test passes).  A
-// chunk is a row of 16 lanes: its box is what the row reduction leaves.
-static_assert(kChunk == 16, "a chunk is a row of lanes");
+// writes its box and up to kSubMax compact sub-ranges (two levels of splits).
 __global__ __launch_bounds__(256) void k_bucket_fill(
     const BucketInfo* __restrict__ buckets, int64_t nb, const uint32_t* __restrict__ order,
     const unsigned long long* __restrict__ skeys, const double* __restrict__ x,
     const double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ vx,
     const double* __restrict__ vy, const double* __restrict__ vz, const double* __restrict__ m,
     const uint32_t* __restrict__ id, const double* __restrict__ h, double* __restrict__ sx,
-    double* __restrict__ sy, double* __restrict__ sz, double4* __restrict__ sp4,
-    double* __restrict__ svx, double* __restrict__ svy, double* __restrict__ svz,
+    double* __restrict__ sy, double* __restrict__ sz, double* __restrict__ svx, double* __restrict__ svy, double* __restrict__ svz,
     double* __restrict__ sm, uint32_t* __restrict__ sid, double* __restrict__ sh,
     uint32_t* __restrict__ perm, double* __restrict__ box, SubRange* __restrict__ sub,
-    int* __restrict__ sub_n, double* __restrict__ cbox)
+    int* __restrict__ sub_n)
 {
     const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= nb) return;
@@ -500,20 +495,14 @@ __global__ __launch_bounds__(256) void k_bucket_fill(
     const double px = x[o], py = y[o], pz = z[o];
     if (live) {
         sx[p] = px; sy[p] = py; sz[p] = pz;
-        sp4[p] = make_double4(px, py, pz, 0.0);
         if (vx) { svx[p] = vx[o]; svy[p] = vy[o]; svz[p] = vz[o]; }
         sm[p] = m[o];
         if (id) sid[p] = id[o];
         sh[p] = h ? h[o] : 0.0;
         perm[p] = o;
     }
-    double e[6] = {row_min(live ? px : INFINITY),  row_min(live ? py : INFINITY),
-                   row_min(live ? pz : INFINITY),  row_max(live ? px : -INFINITY),
-                   row_max(live ? py : -INFINITY), row_max(live ? pz : -INFINITY)};
-    if (cbox && (lane & 15) == 0)
-        for (int q = 0; q < 6; ++q) cbox[6 * (kChunks * b + (lane >> 4)) + q] = e[q];
-#pragma unroll
-    for (int q = 0; q < 6; ++q) e[q] = q < 3 ? rows_min(e[q]) : rows_max(e[q]);
+    double e[6];
+    lanes_box(live, px, py, pz, e);
     if (lane == 0)
         for (int q = 0; q < 6; ++q) box[6 * b + q] = e[q];
     int n = 0;
@@ -548,11 +537,10 @@ __global__ __launch_bounds__(256) void k_bucket_fill(
     if (lane == 0) sub_n[b] = n;
 }
 
-// The largest kernel size of every bucket and (when chmax is given) of each of
-// its chunks of kChunk particles (0 for an empty chunk).
+// The largest kernel size of every bucket.
 __global__ __launch_bounds__(256) void k_bucket_hmax(
     const BucketInfo* __restrict__ buckets, int64_t nb, const double* __restrict__ sh,
-    double* __restrict__ hmax, double* __restrict__ chmax)
+    double* __restrict__ hmax)
 {
     const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= nb) return;
@@ -561,9 +549,6 @@ __global__ __launch_bounds__(256) void k_bucket_hmax(
     const double h = sh[B.start + (lane < B.count ? lane : 0)];
     const double v = rows_max(row_max(h));
     if (lane == 0) hmax[b] = v;
-    if (!chmax) return;
-    const double c = fmax(row_max(lane < B.count ? h : 0.0), 0.0);
-    if ((lane & 15) == 0) chmax[kChunks * b + (lane >> 4)] = c;
 }
 
 // ---------------------------------------------------------------- tree nodes
@@ -694,8 +679,8 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
     }
     hipLaunchKernelGGL(k_bucket_fill, dim3(grid_of(P.n_buckets, 4)), dim3(256), 0, st, w.buckets,
                        P.n_buckets, w.vals[cur], w.keys[cur], s->x, s->y, s->z, s->vx, s->vy,
-                       s->vz, s->m, s->id, s->h, w.sx, w.sy, w.sz, w.sp4, w.svx, w.svy, w.svz,
-                       w.sm, w.sid, w.sh, w.perm, w.box, w.sub, w.sub_n, w.cbox);
+                       s->vz, s->m, s->id, s->h, w.sx, w.sy, w.sz, w.svx, w.svy, w.svz,
+                       w.sm, w.sid, w.sh, w.perm, w.box, w.sub, w.sub_n);
     launch_nodes<false>(P, w, w.box, st);
     return hipGetLastError();
 }
@@ -703,7 +688,7 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
 hipError_t launch_tree_hmax(const Plan& P, Scratch& w, hipStream_t st)
 {
     hipLaunchKernelGGL(k_bucket_hmax, dim3(grid_of(P.n_buckets, 4)), dim3(256), 0, st, w.buckets,
-                       P.n_buckets, w.sh, w.hmax, w.chmax);
+                       P.n_buckets, w.sh, w.hmax);
     launch_nodes<true>(P, w, w.hmax, st);
     return hipGetLastError();
 }

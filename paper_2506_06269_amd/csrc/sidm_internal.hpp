@@ -78,7 +78,6 @@ struct HaloDev {
     int64_t sbase;                        // first position in the sorted (compact) order
     int32_t rank;                         // halo rank by offset (high bits of the sort key)
     int32_t grav_sym;                     // kSym* bits: direct sums run the symmetric tiles
-    int32_t win_lo, win_hi;               // kNN bound window, in buckets around b
     int32_t pad;
 };
 
@@ -148,20 +147,6 @@ __device__ inline int64_t xcd_contiguous(int64_t id, int64_t n)
 {
     const int64_t q = n >> 3, r = n & 7, x = id & 7;
     return x * q + (x < r ? x : r) + (id >> 3);
-}
-
-// Between the two: runs of C consecutive items go to the XCDs in turn, so an
-// XCD keeps C neighbouring buckets under its L2 while every XCD still samples
-// the whole curve (the tree walk, whose lists grow towards the centre).  Items
-// past the last whole round of 8 C keep their own number.  A bijection on
-// [0, n).
-template <int64_t C>
-__device__ inline int64_t xcd_chunked(int64_t id, int64_t n)
-{
-    const int64_t full = n / (8 * C) * (8 * C);
-    if (id >= full) return id;
-    const int64_t x = id & 7, j = id >> 3;
-    return (j / C * 8 + x) * C + j % C;
 }
 #endif
 

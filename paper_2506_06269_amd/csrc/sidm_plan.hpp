@@ -78,10 +78,6 @@ inline int32_t tree_parts(const HaloDev& H)
 {
     return tree_front_level(H.level_n, H.n_levels, kTreeSplit) >= 0 ? kTreeSplit : 1;
 }
-// The searches also skip chunks of kChunk consecutive particles of a bucket
-// (aligned to the bucket start) that no lane's sphere reaches.
-constexpr int kChunk = 16;
-constexpr int kChunks = kBucket / kChunk;
 struct SubRange {
     int32_t off;                  // first particle, relative to the bucket start
     int32_t cnt;
@@ -134,7 +130,6 @@ struct Scratch {
     uint32_t* sort_ws = nullptr;  // digit counts, tickets and tile words of the sort
     int64_t sort_ws_n = 0;
     double *sx = nullptr, *sy = nullptr, *sz = nullptr;
-    double4* sp4 = nullptr;       // sorted positions as (x, y, z, 0): one load per candidate
     double *svx = nullptr, *svy = nullptr, *svz = nullptr;
     double *sh = nullptr, *sm = nullptr;
     int8_t* bin = nullptr;        // block time-step bin per particle (caller's order)
@@ -146,8 +141,6 @@ struct Scratch {
     double* box = nullptr;        // 6 per node (buckets first)
     SubRange* sub = nullptr;      // kSubMax per bucket
     int* sub_n = nullptr;         // sub-ranges per bucket
-    double* cbox = nullptr;       // 6 per chunk, kChunks per bucket (searches only)
-    double* chmax = nullptr;      // largest h per chunk, kChunks per bucket (pair search)
     double* hmax = nullptr;       // 1 per node
     // scattering
     unsigned long long* owner = nullptr;
@@ -313,12 +306,11 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
               dalloc(w.xm32, N) &&  dalloc(w.partial, w.partial_rows) && dalloc(w.keys[0], 2 * N) &&
               dalloc(w.vals[0], N) && dalloc(w.vals[1], N) &&
               dalloc(w.sort_ws, w.sort_ws_n) && dalloc(w.sx, N) && dalloc(w.sy, N) &&
-              dalloc(w.sz, N) && dalloc(w.sp4, N) && dalloc(w.svx, N) && dalloc(w.svy, N) && dalloc(w.svz, N) &&
+              dalloc(w.sz, N) && dalloc(w.svx, N) && dalloc(w.svy, N) && dalloc(w.svz, N) &&
               dalloc(w.sh, N) && dalloc(w.sm, N) && dalloc(w.bin, N) &&
               dalloc(w.mom, w.nodes_cap) && dalloc(w.mom2, 6 * w.nodes_cap) && dalloc(w.tree_terms, H) && dalloc(w.sid, N) && dalloc(w.perm, N) &&
               dalloc(w.box, 6 * w.nodes_cap) && dalloc(w.hmax, w.nodes_cap) &&
               dalloc(w.sub, kSubMax * w.buckets_cap) && dalloc(w.sub_n, w.buckets_cap) &&
-              dalloc(w.cbox, 6 * kChunks * w.buckets_cap) && dalloc(w.chmax, kChunks * w.buckets_cap) &&
               dalloc(w.owner, N) && dalloc(w.counters, 1) && dalloc(w.ev_counts, kEvCounts * H) &&
               dalloc(w.status, H) && dalloc(w.sticky, 1) && dalloc(w.fp_dev, 1);
     if (!ok) {
@@ -359,11 +351,11 @@ inline void free_scratch(Scratch& w)
     dfree(w.halos); dfree(w.blocks); dfree(w.items); dfree(w.buckets); dfree(w.node_tasks); dfree(w.nodes);
     dfree(w.bsum); dfree(w.brange); dfree(w.cref); dfree(w.radius); dfree(w.center); dfree(w.tidal); dfree(w.tidal_sums); dfree(w.bbox); dfree(w.xm32);  dfree(w.partial);
     dfree(w.keys[0]); w.keys[1] = nullptr; dfree(w.vals[0]); dfree(w.vals[1]); dfree(w.sort_ws);
-    dfree(w.sx); dfree(w.sy); dfree(w.sz); dfree(w.sp4); dfree(w.svx); dfree(w.svy); dfree(w.svz);
+    dfree(w.sx); dfree(w.sy); dfree(w.sz); dfree(w.svx); dfree(w.svy); dfree(w.svz);
     dfree(w.items_tick); dfree(w.partial_tick);
     w.items_tick_cap = w.partial_tick_rows = 0;
     dfree(w.sh); dfree(w.sm); dfree(w.bin); dfree(w.mom); dfree(w.mom2); dfree(w.tree_terms); dfree(w.sid); dfree(w.perm); dfree(w.box); dfree(w.hmax);
-    dfree(w.sub); dfree(w.sub_n); dfree(w.cbox); dfree(w.chmax);
+    dfree(w.sub); dfree(w.sub_n);
     dfree(w.owner); dfree(w.events); dfree(w.cands); dfree(w.counters); dfree(w.ev_counts); dfree(w.status);
     dfree(w.sticky); dfree(w.fp_dev);
     dfree(w.sym_items); dfree(w.symacc);
@@ -639,11 +631,6 @@ inline bool build_plan(Plan& P, const Scratch& w, const sidm_halo* halos, int32_
         for (int64_t b = 0; b < nbk; ++b)
             P.buckets.push_back({H.sbase + b * kBucket,
                                  (int32_t)std::min<int64_t>(kBucket, S.n - b * kBucket), h});
-        // kNN bound window: buckets around b holding at least 2(k+1) particles
-        const int64_t want = 2 * ((int64_t)std::max(S.k, 1) + 1);
-        const int64_t wb = std::min<int64_t>(nbk, (want + kBucket - 1) / kBucket + 1);
-        H.win_lo = (int32_t)(wb / 2);
-        H.win_hi = (int32_t)(wb - 1 - wb / 2);
     }
     // tree levels (nodes after all buckets)
     P.n_buckets = (int64_t)P.buckets.size();

@@ -173,7 +173,8 @@ __device__ inline double group_point_dist2(const double* g, double px, double py
 
 // The buckets of the halo for which test(node) holds; internal nodes are entered
 // on the same condition (it must be monotone).  test runs on lanes with a
-// different node each.  drain(n) takes the first n entries of L.list (uniform).
+// different node each.  drain(n, last) takes the first n entries of L.list (uniform); the call
+// with `last` set ends the walk (n may be 0).
 template <class Test, class Drain>
 __device__ inline void search_walk(const HaloDev& H, const NodeChild* __restrict__ nodes,
                                    int64_t n_buckets, SearchLds& L, Test test, Drain drain)
@@ -184,12 +185,9 @@ __device__ inline void search_walk(const HaloDev& H, const NodeChild* __restrict
     __syncthreads();
     if (lane == 0) L.stack[0] = L.list[0] = root;
     __syncthreads();
-    if (H.n_levels == 1) {   // one bucket
-        drain(1);
-        return;
-    }
-    int sp = 1, ln = 0;
-    while (sp > 0) {
+    const bool one = H.n_levels == 1;   // one bucket
+    int sp = one ? 0 : 1, ln = one ? 1 : 0;
+    for (;;) {
         const int npop = sp < kSearchPop ? sp : kSearchPop;
         const int slot = lane / kFanout;
         bool hit = false, leaf = false;
@@ -211,13 +209,13 @@ __device__ inline void search_walk(const HaloDev& H, const NodeChild* __restrict
         ln += __popcll(ml);
         sp += __popcll(mi);
         __syncthreads();
-        if (ln > kSearchList - 64) {
-            drain(ln);
+        if (sp == 0 || ln > kSearchList - 64) {
+            drain(ln, sp == 0);
             ln = 0;
             __syncthreads();
+            if (sp == 0) return;
         }
     }
-    if (ln > 0) drain(ln);
 }
 
 // First particle (sorted position) and number of particles of bucket c.

@@ -32,7 +32,7 @@ constexpr int64_t kItemsMax = kMaxSplit * (kMaxN / kIBlock + 1);
 // Byte offsets of the buffers inside the array (each aligned to 256 bytes).
 struct Layout {
     size_t halos, blocks, items, buckets, node_tasks, nodes, brange, cref, bbox, xm32, partial;
-    size_t keys0, keys1, vals0, vals1, sort_ws, sx, sy, sz, sp4, sh, sm, perm, box, sub,
+    size_t keys0, keys1, vals0, vals1, sort_ws, sx, sy, sz, sh, sm, perm, box, sub,
         sub_n, total;
 };
 
@@ -66,7 +66,6 @@ constexpr Layout make_layout()
     L.sx = take(off, sizeof(double) * kMaxN);
     L.sy = take(off, sizeof(double) * kMaxN);
     L.sz = take(off, sizeof(double) * kMaxN);
-    L.sp4 = take(off, sizeof(double) * 4 * kMaxN);
     L.sh = take(off, sizeof(double) * kMaxN);
     L.sm = take(off, sizeof(double) * kMaxN);
     L.perm = take(off, sizeof(uint32_t) * kMaxN);
@@ -136,7 +135,6 @@ void carve(Scratch& w, unsigned char* base)
     w.sx = (double*)(base + L.sx);
     w.sy = (double*)(base + L.sy);
     w.sz = (double*)(base + L.sz);
-    w.sp4 = (double4*)(base + L.sp4);
     w.sh = (double*)(base + L.sh);
     w.sm = (double*)(base + L.sm);
     w.perm = (uint32_t*)(base + L.perm);
@@ -261,10 +259,6 @@ extern "C" sidm_status sidm_gravity_static(const sidm_halo* halo, const sidm_sta
     H.n_levels = l + 1;
     P.n_levels = H.n_levels;
     P.n_nodes = count;
-    const int64_t want = 2 * ((int64_t)std::max(halo->k, 1) + 1);
-    const int64_t wb = std::min<int64_t>(P.n_buckets, (want + kBucket - 1) / kBucket + 1);
-    H.win_lo = (int32_t)(wb / 2);
-    H.win_hi = (int32_t)(wb - 1 - wb / 2);
     // j-splits: with all items resident at once (at most 256 items here), the
     // split that choose_splits takes is the smallest with the shortest longest
     // j-range; without an occupancy figure, the largest
