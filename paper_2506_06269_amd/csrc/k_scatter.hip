@@ -6,20 +6,25 @@
 // particles closer than h_i + h_j to the box of a group of its lanes, h_i the
 // group's largest (sidm_search.hpp); every lane tests each of them.
 // A bucket takes only candidate buckets of higher index, after the pairs inside
-// it (owned by the smaller id), so each pair is tested once, when
-// d2 < (h_i + h_j)^2; accepted pairs go through an LDS queue (ballot + prefix
-// count) so that the expensive per-pair work -- Philox4x32-10, |dv|, and
-// Lambda when the draw falls below a cheap upper bound of P -- runs on full
-// wavefronts.  A pair whose draw falls below the bound is appended to a
-// candidate buffer; k_decide evaluates Lambda for those and appends the events
-// (u < P) to the event buffer (when the candidate buffer is full, the pair pass
-// decides the rest itself).
-// Its time goes to the exact test of 64 i by one candidate (half of it) and the
-// per-pair work (three tenths); one in six tested pairs is accepted.  A pass
-// that visited the buckets one after the other, each lane testing its own
-// sphere against them and every particle of a chunk, took 2.10 ms for 500009
-// particles (126 M pairs), 3.7 for 2^20 (265 M) and 0.11 for 8192; this one
-// 1.42, 2.65 and 0.074.
+// it, so each pair is tested once, when d2 < (h_i + h_j)^2: first on the matrix
+// cores, 32 i by 32 j at once, to within a rounding bound; the pairs that pass
+// go through an LDS queue (prefix count) so that the exact test and the
+// expensive per-pair work -- Philox4x32-10, |dv|, and Lambda when the draw falls
+// below a cheap upper bound of P -- run on full wavefronts.  A pair whose draw
+// falls below the bound is appended to a candidate buffer; k_decide evaluates
+// Lambda for those and appends the events (u < P) to the event buffer (when the
+// candidate buffer is full, the pair pass decides the rest itself).
+//
+// What bounds it: half of the time is per-pair work, a chain of LDS reads,
+// gathered velocities and ten dependent rounds of the generator at three waves
+// per SIMD (145 registers), so each lane takes two pairs at once (64 halos: 5.4
+// -> 4.9 ms; four waves with fewer registers: 6.0); a quarter is the search,
+// a quarter the screen and the queue.  One in six screened pairs is accepted; in
+// double precision on the vector unit they took half of the pass.
+//            N = 500009 (126 M pairs)   2^20 (265 M)   64 x 32768 (571 M)   8192
+//   bucket after bucket, chunk boxes   2.10 ms   3.7   7.4   0.110
+//   candidates a lane each             1.42      2.65  5.9   0.074
+//   and the screen                     1.17      2.2   4.9   0.058
 //
 // k_rounds: the events of a step are applied in (a, b) order as elastic,
 // isotropic kicks in the pair's centre-of-mass frame.  Events that share no
@@ -180,21 +185,66 @@ __device__ __forceinline__ void decide_pair(const CandRec& r, double dt,
     }
 }
 
-// LDS of the pair pass: what the per-pair work reads of the bucket's own
-// particles, the candidates (position, kernel size, id, sorted index), and the
-// queue of pairs (lane of i, slot of j).  The velocities of j are read from
-// memory per pair, in flight during its Philox rounds, and what only the rare
-// candidates need (positions of i, original indices) there; the mass is the
-// halo's common one.
-constexpr int kPairGroup = 4;   // candidates tested at once
+// The pair test runs on the matrix cores first.  With positions from the
+// bucket's centre, d2 - (h_i + h_j)^2 = q_i + q_j - 2 (r_i . r_j + h_i h_j),
+// q = r^2 - h^2: a product over 16 terms when every factor is the sum of two
+// halves, one 32x32x16 instruction for 1024 pairs.  Lengths are scaled by a
+// power of two to at most 1 over the lanes and 64 candidates.  A factor is then
+// good to 2^-23 (FP32 difference, two halves), a product without the term of
+// two low halves to 2^-21, the four of them doubled to 2^-18, both q to 2^-19
+// (at most 4, FP32 from FP32, two halves), and the sum of 16 terms of at most
+// 16 in all to 2^-17: less than 2^-16 in total.  Pairs with a value below
+// kScreenTol are tested exactly, as they were before; no others can be pairs.
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+constexpr float kScreenTol = 0x1p-15f;
+constexpr int kScreen = 32;   // rows (i) and columns (j) of one instruction
+
+// the factors of i (left operand) and j (right operand), halves of 8 terms
+__device__ inline void screen_factors(float x, float y, float z, float h, bool left, half8* f)
+{
+    float q = ((x * x + y * y) + z * z) - h * h;
+    if (left) q -= kScreenTol;   // the sign of the sum is the test
+    // q as rounded to FP32, for both halves: an FMA that rounds to FP16 at once
+    // in the place of one of its uses gives a high half that the low one does
+    // not belong to
+    asm("" : "+v"(q));
+    const _Float16 xh = (_Float16)x, yh = (_Float16)y, zh = (_Float16)z, hh = (_Float16)h;
+    const _Float16 xl = (_Float16)(x - (float)xh), yl = (_Float16)(y - (float)yh),
+                   zl = (_Float16)(z - (float)zh), hl = (_Float16)(h - (float)hh);
+    const _Float16 qh = (_Float16)q, ql = (_Float16)(q - (float)qh), one = (_Float16)1.0f,
+                   m2 = (_Float16)-2.0f;
+    if (left) {
+        f[0] = half8{m2 * xh, m2 * yh, m2 * zh, m2 * hh, m2 * xh, m2 * yh, m2 * zh, m2 * hh};
+        f[1] = half8{m2 * xl, m2 * yl, m2 * zl, m2 * hl, qh, ql, one, one};
+    } else {
+        f[0] = half8{xh, yh, zh, hh, xl, yl, zl, hl};
+        f[1] = half8{xh, yh, zh, hh, one, one, qh, ql};
+    }
+}
+
+// row of accumulator register r, 32 lanes `half`
+__device__ inline int screen_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
+
+// bucket lane of a queue entry: register 15 - (bits 0-3), tile of 32 rows (bit
+// 4), 32 lanes (bit 5); the rest is the candidate
+__device__ inline int screen_entry(int e)
+{
+    return kScreen * ((e >> 4) & 1) + screen_row(15 - (e & 15), (e >> 5) & 1);
+}
+constexpr int kPairEach = 2;   // queue entries per lane and round of the per-pair work
+
+// LDS of the pair pass: the candidates (position, kernel size, id, sorted
+// index), the factors of 64 of them, and the queue of pairs (place in the
+// accumulators, slot of j).  What the per-pair work reads of the bucket's own
+// particles, and the velocities of j, come from memory, in flight during its
+// Philox rounds; the mass is the halo's common one.
 struct PairLds {
     SearchLds S;
-    double vx[kBucket], vy[kBucket], vz[kBucket], h[kBucket];
-    uint32_t id[kBucket];
-    double jx[2 * kBucket + kPairGroup], jy[2 * kBucket + kPairGroup],
-        jz[2 * kBucket + kPairGroup], jh[2 * kBucket + kPairGroup];
-    uint32_t jid[2 * kBucket + kPairGroup], jp[2 * kBucket + kPairGroup];
-    uint16_t queue[(kPairGroup + 1) * kBucket];
+    double jx[2 * kBucket], jy[2 * kBucket], jz[2 * kBucket], jh[2 * kBucket];
+    uint32_t jid[2 * kBucket], jp[2 * kBucket];
+    half8 factor[2][kBucket];
+    uint16_t queue[kScreen * kScreen + kPairEach * kBucket];
 };
 
 // Cross-section per unit mass at relative speed g: sigma_m, or with a velocity
@@ -246,11 +296,16 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     const int64_t pl = B.start + (act ? lane : 0);
     const double xi = sx[pl], yi = sy[pl], zi = sz[pl], hi = act ? sh[pl] : 0.0;
     const uint32_t idi = sid[pl];
-    if (act) {
-        L.vx[lane] = svx[pl]; L.vy[lane] = svy[pl]; L.vz[lane] = svz[pl];
-        L.h[lane] = hi;
-        L.id[lane] = idi;
-    }
+    // the lane's particle from the centre of the bucket's box, in FP32
+    const double ctr[3] = {0.5 * (box[6 * b] + box[6 * b + 3]), 0.5 * (box[6 * b + 1] + box[6 * b + 4]),
+                           0.5 * (box[6 * b + 2] + box[6 * b + 5])};
+    const float fx = act ? (float)(xi - ctr[0]) : 0.0f, fy = act ? (float)(yi - ctr[1]) : 0.0f,
+                fz = act ? (float)(zi - ctr[2]) : 0.0f, fh = (float)hi;
+    // the rows of the accumulators that hold a particle (bit 15 - r)
+    uint32_t rows[2] = {0, 0};
+    for (int r = 0; r < 16; ++r)
+        for (int t = 0; t < 2; ++t)
+            if (kScreen * t + screen_row(r, lane >> 5) < B.count) rows[t] |= 1u << (15 - r);
     const uint32_t k0 = (uint32_t)(H.seed & 0xffffffffull), k1 = (uint32_t)(H.seed >> 32);
     const double kInvPi8 = 8.0 / 3.14159265358979323846;
     const double cbound = H.sigma_m * mb * kInvPi8 * H.dt;
@@ -262,22 +317,35 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     unsigned long long wave_pairs = 0;   // wave-uniform: the ballots' counts
     int qn = 0;
 
-    // per-pair work for queue entries [from, from + cnt): lane l takes entry l
+    // the exact test and the per-pair work for queue entries [from, from + cnt):
+    // lane l takes entries l and l + 64, two chains of loads and draws at once.
+    // Entries past the last one are the pair of lane 0 and slot 0, not counted.
     auto process = [&](int from, int cnt) __attribute__((always_inline)) {
         __syncthreads();
-        if (lane < cnt) {
-            const int e = L.queue[from + lane];
-            const int il = e & 63, jl = e >> 6;
+        int e[kPairEach];
+        double u[kPairEach];
+        unsigned hit = 0;   // entries below the bound
+#pragma unroll
+        for (int k = 0; k < kPairEach; ++k)
+            e[k] = lane + k * kBucket < cnt ? L.queue[from + lane + k * kBucket] : 15;
+#pragma unroll
+        for (int k = 0; k < kPairEach; ++k) {
+            const int il = screen_entry(e[k]), jl = e[k] >> 6;
+            const double ha = __shfl(hi, il, 64), hbb = L.jh[jl];
+            const double d2 = dist2_pair(__shfl(xi, il, 64), __shfl(yi, il, 64),
+                                         __shfl(zi, il, 64), L.jx[jl], L.jy[jl], L.jz[jl]);
+            const double hs = ha + hbb;
+            const bool pair = lane + k * kBucket < cnt && d2 < hs * hs;
+            wave_pairs += (unsigned long long)__popcll(__ballot(pair));
+            const int64_t pi = B.start + il;
             const uint32_t pj = L.jp[jl];
-            const double vjx = svx[pj], vjy = svy[pj], vjz = svz[pj];
-            // canonical order of the pair: a = smaller id, b = larger id
-            const bool iswap = L.id[il] > L.jid[jl];
-            const uint32_t a = iswap ? L.jid[jl] : L.id[il], bb = iswap ? L.id[il] : L.jid[jl];
-            const Philox4 w = philox4x32_10(a, bb, step, 0u, k0, k1);
-            const double u = unit53(w.w[0], w.w[1]);
-            const double dvx = L.vx[il] - vjx, dvy = L.vy[il] - vjy, dvz = L.vz[il] - vjz;
+            const double dvx = svx[pi] - svx[pj], dvy = svy[pi] - svy[pj],
+                         dvz = svz[pi] - svz[pj];
+            // the draw of the pair: smaller id first
+            const uint32_t ii = __shfl(idi, il, 64), ij = L.jid[jl];
+            const Philox4 w = philox4x32_10(min(ii, ij), max(ii, ij), step, 0u, k0, k1);
+            u[k] = unit53(w.w[0], w.w[1]);
             const double g2 = (dvx * dvx + dvy * dvy) + dvz * dvz;
-            const double ha = L.h[il], hbb = L.jh[jl];
             const double hm = fmax(ha, hbb);
 
             // Lambda <= min(W_a(0), W_b(0)) = 8 / (pi max(h)^3) bounds P by
@@ -286,79 +354,114 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
             // both sides are non-negative, so it is taken squared (no square
             // root, no division), with a relative slack of 1e-12 so that the
             // candidates include every pair whose rounded P exceeds u.
-            double lhs = u * (hm * hm * hm);
+            double lhs = u[k] * (hm * hm * hm);
             if (sw) {
                 const double q = 1.0 + g2 * inv_w2;
                 lhs *= q * q;
             }
-            if (lhs * lhs < cbound2 * g2) {
-                // the exact decision needs Lambda: k_decide takes it from here
-                // (after an overflow of its buffer, the INLINE pass)
-                ++my_cands;
-                const double g = norm3(dvx, dvy, dvz);
-                CandRec r;
-                r.sg = sigma_at(H, g);
-                r.mb = mb;
-                r.g = g;
-                const int64_t pi = B.start + il;
-                r.d = sqrt(dist2_pair(sx[pi], sy[pi], sz[pi], L.jx[jl], L.jy[jl], L.jz[jl]));
-                r.ha = iswap ? hbb : ha;
-                r.hb = iswap ? ha : hbb;
-                r.u = u;
-                r.a = a;
-                r.b = bb;
-                const uint32_t oi = perm[pi], oj = perm[pj];
-                r.ia = iswap ? oj : oi;
-                r.ib = iswap ? oi : oj;
-                r.halo = B.halo;
-                r.pad = 0;
-                if (INLINE) {
-                    decide_pair(r, H.dt, counters, events, max_events, ev_counts);
-                } else {
-                    const unsigned long long slot = atomicAdd(&counters->n_cands, 1ull);
-                    if ((int64_t)slot < max_cands) cands[slot] = r;
-                }
+            hit |= (unsigned)(pair && lhs * lhs < cbound2 * g2) << k;
+        }
+        while (hit) {
+            // the exact decision needs Lambda: k_decide takes it from here
+            // (after an overflow of its buffer, the INLINE pass)
+            const int k = __ffs(hit) - 1;
+            hit &= hit - 1;
+            ++my_cands;
+            const int ek = k == 0 ? e[0] : e[1];
+            const int jl = ek >> 6;
+            const int64_t pi = B.start + screen_entry(ek);
+            const uint32_t pj = L.jp[jl], ii = sid[pi], ij = L.jid[jl];
+            const bool iswap = ii > ij;   // canonical order of the pair: a = smaller id
+            const double ha = sh[pi], hbb = L.jh[jl];
+            const double g =
+                norm3(svx[pi] - svx[pj], svy[pi] - svy[pj], svz[pi] - svz[pj]);
+            CandRec r;
+            r.sg = sigma_at(H, g);
+            r.mb = mb;
+            r.g = g;
+            r.d = sqrt(dist2_pair(sx[pi], sy[pi], sz[pi], L.jx[jl], L.jy[jl], L.jz[jl]));
+            r.ha = iswap ? hbb : ha;
+            r.hb = iswap ? ha : hbb;
+            r.u = k == 0 ? u[0] : u[1];
+            r.a = iswap ? ij : ii;
+            r.b = iswap ? ii : ij;
+            const uint32_t oi = perm[pi], oj = perm[pj];
+            r.ia = iswap ? oj : oi;
+            r.ib = iswap ? oi : oj;
+            r.halo = B.halo;
+            r.pad = 0;
+            if (INLINE) {
+                decide_pair(r, H.dt, counters, events, max_events, ev_counts);
+            } else {
+                const unsigned long long slot = atomicAdd(&counters->n_cands, 1ull);
+                if ((int64_t)slot < max_cands) cands[slot] = r;
             }
         }
         __syncthreads();
     };
 
-    // every lane against the first n candidates in LDS (same: the bucket's own
-    // particles, pairs owned by the smaller id), then the per-pair work of
-    // the pairs found, whose entries refer to these candidates.  The test is
-    // evaluated without a branch per candidate, for kPairGroup of them at once
-    // (infinitely far ones past the last).
+    // the bucket against the first n candidates in LDS (same: its own
+    // particles, a pair taken by the earlier one), and the per-pair work of
+    // what passes, whose entries refer to these candidates
     auto test = [&](int n, bool same) __attribute__((always_inline)) {
-        if (lane < kPairGroup) {
-            L.jx[n + lane] = INFINITY;
-            L.jy[n + lane] = L.jz[n + lane] = L.jh[n + lane] = 0.0;
-        }
+        half8 fi[2];
+        bool wide = false;
+        const int steps = 2 * ((n + kScreen - 1) / kScreen);
         __syncthreads();
-        for (int j = 0; j < n; j += kPairGroup) {
-            bool pair[kPairGroup];
-#pragma unroll
-            for (int u = 0; u < kPairGroup; ++u) {
-                const double d2 = dist2_pair(xi, yi, zi, L.jx[j + u], L.jy[j + u], L.jz[j + u]);
-                const double hs = hi + L.jh[j + u];
-                pair[u] = act & (d2 < hs * hs);
+        for (int u = 0; u < steps; ++u) {
+            const int j0 = kScreen * (u >> 1), jc = j0 + (lane & (kScreen - 1));
+            if ((u & 3) == 0) {   // the factors for the next 64 candidates
+                const int j = j0 + lane;
+                const bool in = j < n;
+                const float gx = in ? (float)(L.jx[j] - ctr[0]) : 0.0f,
+                            gy = in ? (float)(L.jy[j] - ctr[1]) : 0.0f,
+                            gz = in ? (float)(L.jz[j] - ctr[2]) : 0.0f,
+                            gh = in ? (float)L.jh[j] : 0.0f;
+                float m = fmaxf(fmaxf(fabsf(fx), fabsf(fy)), fmaxf(fabsf(fz), fabsf(fh)));
+                m = fmaxf(m, fmaxf(fmaxf(fabsf(gx), fabsf(gy)), fmaxf(fabsf(gz), fabsf(gh))));
+                m = lanes_max(m);
+                // lengths that FP32 does not hold: every pair is tested exactly
+                const float sum = ((fx + fy) + (fz + fh)) + ((gx + gy) + (gz + gh));
+                wide = !(m > 0x1p-100f && m < 0x1p100f) || __any(!(fabsf(sum) < INFINITY));
+                const float s = ldexpf(1.0f, -__builtin_amdgcn_frexp_expf(m));
+                half8 f[2];
+                screen_factors(fx * s, fy * s, fz * s, fh * s, true, f);
+                L.factor[0][lane] = f[0];
+                L.factor[1][lane] = f[1];
+                __syncthreads();
+                fi[0] = L.factor[lane >> 5][lane & (kScreen - 1)];
+                fi[1] = L.factor[lane >> 5][kScreen + (lane & (kScreen - 1))];
+                __syncthreads();
+                screen_factors(gx * s, gy * s, gz * s, gh * s, false, f);
+                L.factor[0][lane] = f[0];
+                L.factor[1][lane] = f[1];
+                __syncthreads();
             }
-            if (same) {
+            const half8 fj = L.factor[lane >> 5][jc & (kBucket - 1)];
+            const float16v acc = __builtin_amdgcn_mfma_f32_32x32x16_f16((u & 1) ? fi[1] : fi[0], fj,
+                                                                        float16v{}, 0, 0, 0);
+            uint32_t m = 0;   // the lane's pairs: signs, register r in bit 15 - r
 #pragma unroll
-                for (int u = 0; u < kPairGroup; ++u) pair[u] &= idi < L.jid[j + u];
+            for (int r = 0; r < 16; ++r)
+                m = __builtin_amdgcn_alignbit(m, __float_as_uint(acc[r]), 31);
+            if (wide) m = 0xffffu;
+            m &= jc < n ? ((u & 1) ? rows[1] : rows[0]) : 0u;
+            if (same)
+                for (int r = 0; r < 16; ++r)
+                    if (kScreen * (u & 1) + screen_row(r, lane >> 5) >= jc) m &= ~(1u << (15 - r));
+            const int cnt = __popc(m), upto = lanes_scan(cnt);
+            int at = qn + upto - cnt;
+            const uint32_t tag = (uint32_t)((u & 1) << 4 | (lane >> 5) << 5 | jc << 6);
+            while (m) {
+                L.queue[at++] = (uint16_t)(tag | (31 - __clz(m)));
+                m &= ~(1u << (31 - __clz(m)));
             }
-#pragma unroll
-            for (int u = 0; u < kPairGroup; ++u) {
-                const unsigned long long mask = __ballot(pair[u]);
-                if (pair[u])
-                    L.queue[qn + __popcll(mask & lt)] = (uint16_t)(lane | ((j + u) << 6));
-                qn += __popcll(mask);
-                wave_pairs += (unsigned long long)__popcll(mask);
-            }
-            const int rest = j + kPairGroup < n ? kBucket - 1 : 0;   // may stay queued
+            qn += __builtin_amdgcn_readlane(upto, 63);
+            const int rest = u + 1 < steps ? kPairEach * kBucket - 1 : 0;   // may stay queued
             while (qn > rest) {
-                const int cnt = min(qn, kBucket);
-                qn -= cnt;
-                process(qn, cnt);
+                const int c = min(qn, kPairEach * kBucket);
+                qn -= c;
+                process(qn, c);
             }
         }
         __syncthreads();
