@@ -1134,6 +1134,8 @@ __global__ __launch_bounds__(kStreamBlock) void k_grav_finalize(
             sp = ms * (fixed_value(q + 6) / spp);
         }
     } else {
+        // rows in flight together (1500 particles, 24 rows: 9.7 us one by one)
+#pragma unroll 8
         for (int s = 0; s < nrow; ++s) {
             const double4 q = rows[rbase + (int64_t)s * H.n + li];
             sx += q.x; sy += q.y; sz += q.z; sp += q.w;
@@ -1182,6 +1184,9 @@ static bool with_shape(int ireg, int nt, F f)
     SIDM_SHAPE(2, 128) SIDM_SHAPE(4, 128) SIDM_SHAPE(8, 128)
     SIDM_SHAPE(2, 256) SIDM_SHAPE(4, 256) SIDM_SHAPE(8, 256)
     SIDM_SHAPE(2, 512) SIDM_SHAPE(4, 512) SIDM_SHAPE(8, 512)
+    if constexpr (!MIXED && !PERSIST) {
+        SIDM_SHAPE(1, 64)   // small calls without a context
+    }
 #undef SIDM_SHAPE
     return false;
 }

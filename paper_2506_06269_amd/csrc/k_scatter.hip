@@ -21,7 +21,7 @@
 // -> 4.9 ms; four waves with fewer registers: 6.0); a quarter is the search,
 // a quarter the screen and the queue.  One in six screened pairs is accepted; in
 // double precision on the vector unit they took half of the pass.
-//            N = 500009 (126 M pairs)   2^20 (265 M)   64 x 32768 (571 M)   8192
+//            N = 500009 (126 M pairs)   2^20 (265 M)   64 halos (571 M)   8192
 //   bucket after bucket, chunk boxes   2.10 ms   3.7   7.4   0.110
 //   candidates a lane each             1.42      2.65  5.9   0.074
 //   and the screen                     1.17      2.2   4.9   0.058

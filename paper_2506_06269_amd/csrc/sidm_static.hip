@@ -24,10 +24,27 @@ namespace {
 constexpr int64_t kMaxN = SIDM_STATIC_MAX_N;
 constexpr int64_t kMaxSplit = 4;
 constexpr int64_t kIBlock = kGravThreads * 4;
+// FP64 items: 64 i each, one per thread of a wave, and j-ranges of whole tiles
+// of 64 until kWaves64 waves are in the grid (four per SIMD).  Items of 1024 i
+// in at most four j-ranges, as in mixed precision, leave a call of 1500
+// particles 8 of the 256 compute units: 99 us of tiles, where these take 8.
+// The whole call (us), one after the other on a stream:
+//   n                    1500   4096   8192   16384   32768   65536
+//   4 x 256, four ranges  142    251    442     774    1454    2792
+//   1 x 64, 2048 waves     55     81    133     279     830    3103
+//   1 x 64, 4096 waves     56     91    136     261     779    2878
+//   2 x 64, 4096 waves     58     90    136     260     765    2827
+// From as many of the large items as compute units on, those are taken.  Mixed
+// precision keeps them throughout: where its FP32 sums are cut is part of the
+// result.
+constexpr int64_t kComputeUnits = 256;
+constexpr int64_t kIBlock64 = 64;
+constexpr int64_t kWaves64 = 4096;
 constexpr int64_t kBlocksMax = kMaxN / kStreamBlock + 1;
 constexpr int64_t kBucketsMax = kMaxN / kBucket + 1;
 constexpr int64_t kNodesMax = 2 * kBucketsMax + kMaxLevels + 1;
-constexpr int64_t kItemsMax = kMaxSplit * (kMaxN / kIBlock + 1);
+constexpr int64_t kItemsMax = kWaves64 + kMaxN / kIBlock64 + 1;
+static_assert(kItemsMax >= kMaxSplit * (kMaxN / kIBlock + 1), "items of the mixed tiles");
 
 // Byte offsets of the buffers inside the array (each aligned to 256 bytes).
 struct Layout {
@@ -151,8 +168,8 @@ void carve(Scratch& w, unsigned char* base)
 // buckets, tree nodes and their tasks, gravity work items.
 __global__ __launch_bounds__(256) void k_static_plan(HaloDev H, int64_t n_blocks, int64_t n_buckets,
                                                      int64_t n_nodes, int64_t n_items,
-                                                     int64_t n_plan,
-                                                     HaloDev* __restrict__ halos,
+                                                     int64_t n_plan, int64_t i_block,
+                                                     int64_t tile_j, HaloDev* __restrict__ halos,
                                                      StreamBlock* __restrict__ blocks,
                                                      BucketInfo* __restrict__ buckets,
                                                      NodeChild* __restrict__ nodes,
@@ -187,13 +204,13 @@ __global__ __launch_bounds__(256) void k_static_plan(HaloDev H, int64_t n_blocks
         tasks[task] = NodeTask{t, child0, nchild, 0};
     }
     if (t < n_items) {
-        const int64_t n_ib = (n + kIBlock - 1) / kIBlock;
+        const int64_t n_ib = (n + i_block - 1) / i_block;
         const int64_t s = t / n_ib, ib = t % n_ib;
-        const int64_t tiles = (n + kGravTileJ - 1) / kGravTileJ;
+        const int64_t tiles = (n + tile_j - 1) / tile_j;
         const int64_t t0 = tiles * s / H.grav_split, t1 = tiles * (s + 1) / H.grav_split;
-        const int64_t j0 = H.offset + t0 * kGravTileJ;
-        const int64_t j1 = min(H.offset + n, H.offset + t1 * kGravTileJ);
-        items[t] = GravItem{H.offset + ib * kIBlock, j0, j1, 0, (int32_t)s};
+        const int64_t j0 = H.offset + t0 * tile_j;
+        const int64_t j1 = min(H.offset + n, H.offset + t1 * tile_j);
+        items[t] = GravItem{H.offset + ib * i_block, j0, j1, 0, (int32_t)s};
     }
 }
 
@@ -259,13 +276,25 @@ extern "C" sidm_status sidm_gravity_static(const sidm_halo* halo, const sidm_sta
     H.n_levels = l + 1;
     P.n_levels = H.n_levels;
     P.n_nodes = count;
+    int64_t i_block = kIBlock, tile_j = kGravTileJ;
+    const bool fine = prec == SIDM_PREC_FP64 &&
+                      kMaxSplit * ((n + kIBlock - 1) / kIBlock) < kComputeUnits;
+    if (fine) {
+        P.shape.ireg = 1;
+        P.shape.nt = (int32_t)kIBlock64;
+        i_block = tile_j = kIBlock64;
+    }
+    const int64_t n_ib = (n + i_block - 1) / i_block;
     // j-splits: with all items resident at once (at most 256 items here), the
     // split that choose_splits takes is the smallest with the shortest longest
     // j-range; without an occupancy figure, the largest
-    const int64_t tiles = (n + kGravTileJ - 1) / kGravTileJ;
+    const int64_t tiles = (n + tile_j - 1) / tile_j;
     const int64_t smax = std::min<int64_t>(kMaxSplit, tiles);
     int64_t split = smax;
-    if (D.slots > 0) {
+    if (fine) {
+        const int64_t rows = kMaxSplit * kMaxN / n;   // partial rows per particle
+        split = std::min(std::min(tiles, rows), (kWaves64 + n_ib - 1) / n_ib);
+    } else if (D.slots > 0) {
         int64_t best = tiles;
         split = 1;
         for (int64_t sp = 2; sp <= smax; ++sp)
@@ -275,7 +304,6 @@ extern "C" sidm_status sidm_gravity_static(const sidm_halo* halo, const sidm_sta
             }
     }
     H.grav_split = (int32_t)split;
-    const int64_t n_ib = (n + kIBlock - 1) / kIBlock;
     P.n_items = split * n_ib;
     P.key_bits = 48;
     P.rank_shift = 48;
@@ -287,8 +315,8 @@ extern "C" sidm_status sidm_gravity_static(const sidm_halo* halo, const sidm_sta
     hipStream_t st = (hipStream_t)stream;
     const int64_t n_plan = std::max(P.n_nodes, P.n_items);
     hipLaunchKernelGGL(k_static_plan, dim3((unsigned)((n_plan + 255) / 256)), dim3(256), 0, st,
-                       H, P.n_blocks, P.n_buckets, P.n_nodes, P.n_items, n_plan, w.halos, w.blocks,
-                       w.buckets, w.nodes, w.node_tasks, w.items);
+                       H, P.n_blocks, P.n_buckets, P.n_nodes, P.n_items, n_plan, i_block, tile_j,
+                       w.halos, w.blocks, w.buckets, w.nodes, w.node_tasks, w.items);
     e = hipGetLastError();
     // the passes read positions and masses only
     sidm_state local = *s;
