@@ -178,10 +178,11 @@ typedef struct {
 /* ---- context ---------------------------------------------------------------
  * Creates a context on HIP device `device` with scratch memory for up to
  * `max_particles` particles in total and `max_halos` halos per call, and room
- * for max(4096, max_particles / 8) scattering events per call (and four times
- * as many candidates: pairs whose draw falls below the cheap bound of P and
- * whose decision needs the overlap integral; when they are more, a second
- * pair pass decides them all, with the same result).  Allocates
+ * for max(4096, max_particles / 8) scattering events per call and for
+ * four times as many candidates, or two per particle if that is more (pairs
+ * whose draw falls below the cheap bound of P and whose decision needs the
+ * overlap integral; when they are more, a second pair pass decides them all,
+ * with the same result).  Allocates
  * device memory (SIDM_ERR_NOMEM on failure).  *out is NULL on error. */
 sidm_status sidm_create(sidm_ctx **out, int device, int64_t max_particles, int32_t max_halos);
 

@@ -245,12 +245,14 @@ inline void dfree(T*& p)
 // benchmark's density a pair's draw falls below the bound some 70 times as
 // often as below P, and the default event buffer, N/8, holds about 50 times
 // a step's events; an overflow only costs a second pair pass).
-inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why)
+// Room for max_events events and, unless given, four times as many candidates.
+inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why,
+                           int64_t max_cands = 0)
 {
     dfree(w.events);
     dfree(w.cands);
     w.max_events = max_events;
-    w.max_cands = 4 * max_events;
+    w.max_cands = std::max<int64_t>(4 * max_events, max_cands);
     if (!dalloc(w.events, max_events) || !dalloc(w.cands, w.max_cands)) {
         why = "cannot allocate the event buffers";
         w.max_events = w.max_cands = 0;
@@ -320,7 +322,11 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
     // the two key buffers of the radix sort are one allocation: outside the
     // sort its 2 N words serve as the hash table of the id check
     w.keys[1] = w.keys[0] + N;
-    if (!realloc_events(w, max_events, why)) return false;
+    // Some 60 pairs fall below the cheap bound of P for one that scatters, so
+    // that a cycle over long steps passes four candidates per event slot early,
+    // and the second pair pass costs more than the first (65536 particles, 0.9
+    // candidates each: 1.4 ms after 0.5): two per particle, 80 bytes each.
+    if (!realloc_events(w, max_events, why, 2 * N)) return false;
     // the counters, per-halo event counts, status words and tree term counts
     // read by the diagnostics start at zero (a context that has not stepped
     // yet reports no events and a clean status); the passes reset them later
