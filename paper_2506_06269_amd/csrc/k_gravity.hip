@@ -48,8 +48,10 @@ __global__ __launch_bounds__(kStreamBlock) void k_pack_frames(
     const double* __restrict__ sx, const double* __restrict__ sy, const double* __restrict__ sz,
     const double* __restrict__ sm, const StreamBlock* __restrict__ blocks,
     const HaloDev* __restrict__ halos, const SubRange* __restrict__ sub,
-    const int* __restrict__ sub_n, float4* __restrict__ xm32)
+    const int* __restrict__ sub_n, float4* __restrict__ xm32, const int* __restrict__ active,
+    int tick)
 {
+    if (tick_idle(active, tick)) return;
     const StreamBlock B = blocks[blockIdx.x];
     const int t = threadIdx.x;
     if (t >= B.count) return;
@@ -224,8 +226,9 @@ __global__ __launch_bounds__(NT) void k_grav_mixed(
     unsigned long long* __restrict__ ticket, const HaloDev* __restrict__ halos,
     const double* __restrict__ cmass, double4* __restrict__ partial,
     const int8_t* __restrict__ bin, const uint32_t* __restrict__ perm, int tick, int bmax,
-    int tick_rows)
+    int tick_rows, const int* __restrict__ active)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ float4 tile[NT];
     __shared__ int64_t next;
     int64_t k = blockIdx.x;
@@ -752,8 +755,9 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
     unsigned long long* __restrict__ ticket, const HaloDev* __restrict__ halos,
     const double* __restrict__ cmass, double4* __restrict__ partial,
     const int8_t* __restrict__ bin, const uint32_t* __restrict__ perm, int tick, int bmax,
-    int tick_rows, const double* __restrict__ sym_ok)
+    int tick_rows, const double* __restrict__ sym_ok, const int* __restrict__ active)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ double4 tile[NT];
     __shared__ int64_t next;
     int64_t k = blockIdx.x;
@@ -1091,9 +1095,10 @@ __global__ __launch_bounds__(kStreamBlock) void k_grav_finalize(
     double* __restrict__ vz, double* __restrict__ svx, double* __restrict__ svy,
     double* __restrict__ svz, int kick, int8_t* __restrict__ bin, int tick, int bmax,
     const double4* __restrict__ partial_tick, const unsigned long long* __restrict__ symacc,
-    const double* __restrict__ cmass, int n_halos, int kind)
+    const double* __restrict__ cmass, int n_halos, int kind, const int* __restrict__ active)
 {
 #pragma clang fp contract(off)
+    if (tick_idle(active, tick)) return;
     const StreamBlock B = blocks[blockIdx.x];
     const int t = threadIdx.x;
     if (t >= B.count) return;
@@ -1286,6 +1291,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
     // whole evaluation (the symmetric tiles where they apply) instead of the
     // tick items.
     const bool full_tick = tick > 0 && tick == (1 << bmax);
+    const int* active = idle_word(P, w, tick, bmax);
     const bool tk = tick > 0 && !full_tick && !P.items_tick.empty();
     const bool sym = !tk && (mixed ? P.n_sym_items > 0 : P.any_sym64);
     const int kind = mixed ? kSymMixed : kSymFp64;
@@ -1296,7 +1302,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
     unsigned long long* ticket = &w.counters->ticket;
     if (mixed && (n_items > 0 || sym))
         hipLaunchKernelGGL(k_pack_frames, dim3(nb), dim3(kStreamBlock), 0, st, w.sx, w.sy, w.sz,
-                           w.sm, w.blocks, w.halos, w.sub, w.sub_n, w.xm32);
+                           w.sm, w.blocks, w.halos, w.sub, w.sub_n, w.xm32, active, tick);
     if (sym) {
         const int64_t slots = mixed ? w.slots_sym : w.slots_sym64;
         if (slots <= 0 || !w.symacc || !w.sym_items) return hipErrorInvalidValue;
@@ -1336,13 +1342,13 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
         auto launch_mixed = [&](auto kern, int threads) {
             hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, w.xm32, w.sub, w.sub_n,
                                items, n_items, ticket, w.halos, w.cref, rows, w.bin, w.perm,
-                               tick, bmax, tk ? 1 : 0);
+                               tick, bmax, tk ? 1 : 0, active);
         };
         auto launch_fp64 = [&](auto kern, int threads) {
             hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, w.sx, w.sy, w.sz, w.sm,
                                items, n_items, ticket, w.halos, w.cref, rows, w.bin, w.perm,
                                tick, bmax, tk ? 1 : 0,
-                               sym ? w.cref + 2 * P.n_halos : (const double*)nullptr);
+                               sym ? w.cref + 2 * P.n_halos : (const double*)nullptr, active);
         };
         bool ok;
         if (mixed)
@@ -1358,7 +1364,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
                        w.partial, w.perm, s->x, s->y, s->z, s->ax, s->ay, s->az, s->pot, s->vx,
                        s->vy, s->vz, w.svx, w.svy, w.svz, kick, w.bin, tick, bmax,
                        tk ? w.partial_tick : nullptr, sym ? w.symacc : nullptr, w.cref,
-                       P.n_halos, kind);
+                       P.n_halos, kind, active);
     return hipGetLastError();
 }
 

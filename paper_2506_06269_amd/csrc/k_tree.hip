@@ -68,8 +68,10 @@ __device__ inline void put_mass(const HaloDev& H, int h, int n_halos, const doub
 __global__ __launch_bounds__(kStreamBlock) void k_block_range(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
     const double* __restrict__ m, const StreamBlock* __restrict__ blocks,
-    double* __restrict__ brange, uint32_t* __restrict__ zero, int64_t n_zero)
+    double* __restrict__ brange, uint32_t* __restrict__ zero, int64_t n_zero,
+    const int* __restrict__ active, int tick)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ double red[kRange * (kStreamBlock / 64)];
     const StreamBlock B = blocks[blockIdx.x];
     const int t = threadIdx.x;
@@ -88,8 +90,10 @@ __global__ __launch_bounds__(kStreamBlock) void k_block_range(
 constexpr int kRangeThreads = 1024;
 __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
     const HaloDev* __restrict__ halos, const double* __restrict__ brange,
-    double* __restrict__ bbox, double* __restrict__ cmass, int* __restrict__ status)
+    double* __restrict__ bbox, double* __restrict__ cmass, int* __restrict__ status,
+    const int* __restrict__ active, int tick)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ double red[kRange * (kRangeThreads / 64)];
     const HaloDev& H = halos[blockIdx.x];
     const int t = threadIdx.x;
@@ -166,8 +170,9 @@ __global__ __launch_bounds__(kStreamBlock) void k_morton_keys(
     const HaloDev* __restrict__ halos, const double* __restrict__ bbox,
     unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
     const int8_t* __restrict__ bin, int tick, int bmax, int rank_shift, int passes,
-    uint32_t* __restrict__ hist)
+    uint32_t* __restrict__ hist, const int* __restrict__ active)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ uint32_t cnt[kSortMaxPasses][kDigits];
     const int t = threadIdx.x;
     for (int p = 0; p < passes; ++p) cnt[p][t] = 0u;
@@ -272,8 +277,10 @@ template <int IPT>
 __global__ __launch_bounds__(kSortBlock) void k_sort_pass(
     const unsigned long long* __restrict__ kin, const uint32_t* __restrict__ vin,
     unsigned long long* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift,
-    const uint32_t* __restrict__ hist, uint32_t* __restrict__ ticket, uint32_t* __restrict__ tiles)
+    const uint32_t* __restrict__ hist, uint32_t* __restrict__ ticket, uint32_t* __restrict__ tiles,
+    const int* __restrict__ active, int tick)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ uint32_t cnt[kSortWaves][kDigits];
     __shared__ uint32_t sw[kDigits / 64];
     __shared__ uint32_t tile_s;
@@ -359,8 +366,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
     const double* __restrict__ m, const HaloDev* __restrict__ halos, double* __restrict__ cmass,
     int* __restrict__ status, unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
-    const int8_t* __restrict__ bin, int tick, int bmax, int rank_shift)
+    const int8_t* __restrict__ bin, int tick, int bmax, int rank_shift,
+    const int* __restrict__ active)
 {
+    if (tick_idle(active, tick)) return;
     __shared__ unsigned long long skey[kSmallThreads * IPT];
     __shared__ uint16_t sidx[kSmallThreads * IPT];
     __shared__ uint32_t cnt[kSmallWaves][kDigits];
@@ -482,8 +491,9 @@ __global__ __launch_bounds__(256) void k_bucket_fill(
     double* __restrict__ sy, double* __restrict__ sz, double* __restrict__ svx, double* __restrict__ svy, double* __restrict__ svz,
     double* __restrict__ sm, uint32_t* __restrict__ sid, double* __restrict__ sh,
     uint32_t* __restrict__ perm, double* __restrict__ box, SubRange* __restrict__ sub,
-    int* __restrict__ sub_n)
+    int* __restrict__ sub_n, const int* __restrict__ active, int tick)
 {
+    if (tick_idle(active, tick)) return;
     const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= nb) return;
     const int lane = threadIdx.x & 63;
@@ -575,8 +585,10 @@ __device__ inline void node_hmax(const NodeTask T, double* __restrict__ hmax)
 // One wide level of nodes: their boxes, or (HMAX) their largest kernel sizes.
 template <bool HMAX>
 __global__ __launch_bounds__(256) void k_node_level(const NodeTask* __restrict__ tasks, int64_t nt,
-                                                    double* __restrict__ a)
+                                                    double* __restrict__ a,
+                                                    const int* __restrict__ active, int tick)
 {
+    if (tick_idle(active, tick)) return;
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k >= nt) return;
     if (HMAX) node_hmax(tasks[k], a);
@@ -587,8 +599,10 @@ __global__ __launch_bounds__(256) void k_node_level(const NodeTask* __restrict__
 // cost more than the work).
 template <bool HMAX>
 __global__ __launch_bounds__(kTopThreads) void k_node_top(const NodeTask* __restrict__ tasks,
-                                                          TopLevels L, double* a)
+                                                          TopLevels L, double* a,
+                                                          const int* __restrict__ active, int tick)
 {
+    if (tick_idle(active, tick)) return;
     for (int l = L.first; l < L.n_levels; ++l) {
         for (int64_t k = L.off[l - 1] + threadIdx.x; k < L.off[l]; k += kTopThreads) {
             if (HMAX) node_hmax(tasks[k], a);
@@ -605,7 +619,8 @@ static unsigned grid_of(int64_t n, int per) { return (unsigned)((n + per - 1) / 
 // Stable LSD radix sort of keys[0] (with vals[0]) over their low key_bits bits,
 // n keys (digit counts in w.sort_ws); returns the index of the buffer pair
 // that holds the result.
-static int launch_sort(Scratch& w, int64_t n, int passes, hipStream_t st)
+static int launch_sort(Scratch& w, int64_t n, int passes, hipStream_t st, const int* active,
+                       int tick)
 {
     int cur = 0;
     const int ipt = sort_items(n);
@@ -617,7 +632,7 @@ static int launch_sort(Scratch& w, int64_t n, int passes, hipStream_t st)
         auto pass = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3((unsigned)ntile), dim3(kSortBlock), 0, st, w.keys[cur],
                                w.vals[cur], w.keys[cur ^ 1], w.vals[cur ^ 1], n, p * kSortBits,
-                               hist, ticket, tiles);
+                               hist, ticket, tiles, active, tick);
         };
         if (ipt == 4) pass(k_sort_pass<4>);
         else if (ipt == 8) pass(k_sort_pass<8>);
@@ -628,16 +643,18 @@ static int launch_sort(Scratch& w, int64_t n, int passes, hipStream_t st)
 }
 
 template <bool HMAX>
-static void launch_nodes(const Plan& P, Scratch& w, double* a, hipStream_t st)
+static void launch_nodes(const Plan& P, Scratch& w, double* a, hipStream_t st,
+                         const int* active = nullptr, int tick = 0)
 {
     const TopLevels T = top_levels(P);
     for (int l = 1; l < T.first; ++l) {
         const int64_t t0 = P.level_task_off[l - 1], nt = P.level_task_off[l] - t0;
         hipLaunchKernelGGL(k_node_level<HMAX>, dim3(grid_of(nt, 256)), dim3(256), 0, st,
-                           w.node_tasks + t0, nt, a);
+                           w.node_tasks + t0, nt, a, active, tick);
     }
     if (T.first < T.n_levels)
-        hipLaunchKernelGGL(k_node_top<HMAX>, dim3(1), dim3(kTopThreads), 0, st, w.node_tasks, T, a);
+        hipLaunchKernelGGL(k_node_top<HMAX>, dim3(1), dim3(kTopThreads), 0, st, w.node_tasks, T, a,
+                           active, tick);
 }
 
 // The cell list of the current positions, the halos' bounding boxes and their
@@ -647,12 +664,13 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
                             int* status, int tick, int bmax)
 {
     const int64_t n = P.n_sorted;
+    const int* active = idle_word(P, w, tick, bmax);
     int cur = 0;
     if (P.n_max <= kSmallN) {
         auto small = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(P.n_halos), dim3(kSmallThreads), 0, st, s->x, s->y, s->z,
                                s->m, w.halos, w.cref, status, w.keys[0], w.vals[0], w.bin, tick,
-                               bmax, P.rank_shift);
+                               bmax, P.rank_shift, active);
         };
         if (P.n_max <= kSmallThreads) small(k_cell_small<1>);
         else if (P.n_max <= 2 * kSmallThreads) small(k_cell_small<2>);
@@ -664,9 +682,10 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
         if (passes > kSortMaxPasses || n > (int64_t)kTileValue || n_zero > w.sort_ws_n)
             return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_block_range, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0, st,
-                           s->x, s->y, s->z, s->m, w.blocks, w.brange, w.sort_ws, n_zero);
+                           s->x, s->y, s->z, s->m, w.blocks, w.brange, w.sort_ws, n_zero, active,
+                           tick);
         hipLaunchKernelGGL(k_halo_range, dim3(P.n_halos), dim3(kRangeThreads), 0, st, w.halos,
-                           w.brange, w.bbox, w.cref, status);
+                           w.brange, w.bbox, w.cref, status, active, tick);
         // at most 16 blocks per workgroup; from 64 workgroups on, fewer of them
         // are better: each adds up to kDigits words per pass to the same counts
         // (65536 particles: 10.3 us with 256 workgroups, 7.5 us with 64)
@@ -674,14 +693,14 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
         hipLaunchKernelGGL(k_morton_keys, dim3(grid_of(P.n_blocks, group)), dim3(kStreamBlock), 0,
                            st, s->x, s->y, s->z, w.blocks, P.n_blocks, group, w.halos, w.bbox,
                            w.keys[0], w.vals[0], w.bin, tick, bmax, P.rank_shift, passes,
-                           w.sort_ws);
-        cur = launch_sort(w, n, passes, st);
+                           w.sort_ws, active);
+        cur = launch_sort(w, n, passes, st, active, tick);
     }
     hipLaunchKernelGGL(k_bucket_fill, dim3(grid_of(P.n_buckets, 4)), dim3(256), 0, st, w.buckets,
                        P.n_buckets, w.vals[cur], w.keys[cur], s->x, s->y, s->z, s->vx, s->vy,
                        s->vz, s->m, s->id, s->h, w.sx, w.sy, w.sz, w.svx, w.svy, w.svz,
-                       w.sm, w.sid, w.sh, w.perm, w.box, w.sub, w.sub_n);
-    launch_nodes<false>(P, w, w.box, st);
+                       w.sm, w.sid, w.sh, w.perm, w.box, w.sub, w.sub_n, active, tick);
+    launch_nodes<false>(P, w, w.box, st, active, tick);
     return hipGetLastError();
 }
 

@@ -20,7 +20,7 @@ hipError_t launch_open_kick(const StreamBlock* d_blocks, int64_t n_blocks, const
                             const double* az, int8_t* bin, hipStream_t st);
 hipError_t launch_tick_drift(const StreamBlock* d_blocks, int64_t n_blocks, const HaloDev* d_halos,
                              double* x, double* y, double* z, double* vx, double* vy, double* vz,
-                             int tick, int bmax, hipStream_t st);
+                             const int8_t* bin, int* active, int tick, int bmax, hipStream_t st);
 hipError_t launch_diag(const StreamBlock* d_blocks, int64_t n_blocks, const HaloDev* d_halos,
                        int n_halos, const double* x, const double* y, const double* z,
                        const double* vx, const double* vy, const double* vz, const double* m,
@@ -596,7 +596,7 @@ sidm_status sidm_kdk_step(sidm_ctx* c, const sidm_halo* halos, int32_t n_halos,
         mark(2);
         for (int tick = 1; tick <= (1 << bmax) && e == hipSuccess; ++tick) {
             e = launch_tick_drift(c->w.blocks, P.n_blocks, c->w.halos, s->x, s->y, s->z, s->vx,
-                                  s->vy, s->vz, tick, bmax, st);
+                                  s->vy, s->vz, c->w.bin, c->w.tick_active, tick, bmax, st);
             if (e == hipSuccess) e = launch_cell_list(P, s, c->w, st, c->w.status, tick, bmax);
             if (e == hipSuccess)
                 e = launch_gravity(prec == SIDM_PREC_MIXED, P, c->w, s, 1, st, nullptr, nullptr,

@@ -150,6 +150,7 @@ struct Scratch {
     DevCounters* counters = nullptr;
     long long* ev_counts = nullptr;   // kEvCounts per halo
     int* status = nullptr;            // per halo
+    int* tick_active = nullptr;   // block steps: the last tick that ended a step
     int* sticky = nullptr;            // OR of the status words not yet read by the host
     unsigned long long* fp_dev = nullptr;   // fingerprint of the last call outside capture
 };
@@ -261,6 +262,15 @@ inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why,
     return true;
 }
 
+// The word by which the kernels of a tick know that it is idle, or null where
+// they run in any case: outside of cycles, at the last tick, which ends every
+// step, and where a halo uses the tree walk (its moments are not skipped).
+inline const int* idle_word(const Plan& P, const Scratch& w, int tick, int bmax)
+{
+    return tick > 0 && tick != (1 << bmax) && !P.has_tree && !P.items_tick.empty() ? w.tick_active
+                                                                                   : nullptr;
+}
+
 // Waves per bucket for the searches of a call with few buckets: the smallest
 // power of two (at most max_split) that gives kSearchWaves waves in all.
 constexpr int64_t kSearchWaves = 2048;
@@ -314,7 +324,7 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
               dalloc(w.box, 6 * w.nodes_cap) && dalloc(w.hmax, w.nodes_cap) &&
               dalloc(w.sub, kSubMax * w.buckets_cap) && dalloc(w.sub_n, w.buckets_cap) &&
               dalloc(w.owner, N) && dalloc(w.counters, 1) && dalloc(w.ev_counts, kEvCounts * H) &&
-              dalloc(w.status, H) && dalloc(w.sticky, 1) && dalloc(w.fp_dev, 1);
+              dalloc(w.status, H) && dalloc(w.sticky, 1) && dalloc(w.fp_dev, 1) && dalloc(w.tick_active, 1);
     if (!ok) {
         why = "device allocation failed";
         return false;
@@ -363,7 +373,7 @@ inline void free_scratch(Scratch& w)
     dfree(w.sh); dfree(w.sm); dfree(w.bin); dfree(w.mom); dfree(w.mom2); dfree(w.tree_terms); dfree(w.sid); dfree(w.perm); dfree(w.box); dfree(w.hmax);
     dfree(w.sub); dfree(w.sub_n);
     dfree(w.owner); dfree(w.events); dfree(w.cands); dfree(w.counters); dfree(w.ev_counts); dfree(w.status);
-    dfree(w.sticky); dfree(w.fp_dev);
+    dfree(w.sticky); dfree(w.fp_dev); dfree(w.tick_active);
     dfree(w.sym_items); dfree(w.symacc);
     w.sym_items_cap = w.symacc_n = 0;
 }

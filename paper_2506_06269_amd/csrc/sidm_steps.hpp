@@ -46,6 +46,14 @@ __device__ inline bool bin_active(const HaloDev& H, int b, int kl)
     return kl > 0 && (kl & ((1 << (H.max_bin - b)) - 1)) == 0;
 }
 
+// Whether no particle steps at this tick: `active` holds the last tick with one
+// that does (k_tick_drift), a value left by an earlier cycle only makes an idle
+// tick do its work.  Null: the tick is not skipped.
+__device__ inline bool tick_idle(const int* active, int tick)
+{
+    return active && *active != tick;
+}
+
 // Half of the step of bin b.
 __device__ inline double half_step(const HaloDev& H, int b)
 {
