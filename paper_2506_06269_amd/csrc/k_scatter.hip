@@ -297,8 +297,8 @@ __global__ __launch_bounds__(kBucket) void k_pairs(
     const double xi = sx[pl], yi = sy[pl], zi = sz[pl], hi = act ? sh[pl] : 0.0;
     const uint32_t idi = sid[pl];
     // the lane's particle from the centre of the bucket's box, in FP32
-    const double ctr[3] = {0.5 * (box[6 * b] + box[6 * b + 3]), 0.5 * (box[6 * b + 1] + box[6 * b + 4]),
-                           0.5 * (box[6 * b + 2] + box[6 * b + 5])};
+    const double* bb = box + 6 * b;
+    const double ctr[3] = {0.5 * (bb[0] + bb[3]), 0.5 * (bb[1] + bb[4]), 0.5 * (bb[2] + bb[5])};
     const float fx = act ? (float)(xi - ctr[0]) : 0.0f, fy = act ? (float)(yi - ctr[1]) : 0.0f,
                 fz = act ? (float)(zi - ctr[2]) : 0.0f, fh = (float)hi;
     // the rows of the accumulators that hold a particle (bit 15 - r)
