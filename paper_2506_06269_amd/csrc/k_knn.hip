@@ -127,19 +127,19 @@ __global__ __launch_bounds__(kBucket) void k_knn(
 
     // every candidate within reach of a lane's sphere (radius^2 r2 of the lane;
     // lanes with `off` set do not search); body(p, d2) runs on every lane for
-    // kKnnGroup candidates p at once and their squared distances d2 (infinite
-    // past the last one): their LDS reads and arithmetic overlap, and one
-    // branch serves them all
+    // kKnnGroup candidates p at once and their squared distances d2 (NaN, and p
+    // of no meaning, past the last one): their LDS reads and arithmetic overlap,
+    // and one branch serves them all
     auto visit = [&](double r2, bool off, auto body) __attribute__((always_inline)) {
         const int nq = search_groups(L.S, lane, sid_l, !off, xi, yi, zi, r2);
         if (nq == 0) return;
         const bool singles = nq == __popcll(__ballot(!off));   // every group one lane
         int bn = 0;   // candidates in LDS
         auto process = [&](int n) {
-            if (lane < kKnnGroup) {   // at most 2 kBucket - 1 entries are in use
-                L.x[n + lane] = INFINITY;
-                L.p[n + lane] = ~0u;
-            }
+            // at most 2 kBucket - 1 entries are in use; the distance of the
+            // others is NaN, in no range (an infinite one lies in a range that
+            // ends at infinity, and its index ~0 would be read)
+            if (lane < kKnnGroup) L.x[n + lane] = NAN;
             __syncthreads();
             for (int j = 0; j < n; j += kKnnGroup) {
                 uint32_t p[kKnnGroup];
