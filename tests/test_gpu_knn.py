@@ -173,6 +173,21 @@ def test_knn_coincident_particles(S, orc):
         assert np.array_equal(lists[:, :k], lref)
 
 
+@pytest.mark.parametrize("ids", ["per copy", "all equal"])
+def test_knn_lists_with_repeated_ids(S, orc, ids):
+    """Entries of one distance and one id each keep a place of their own."""
+    base = W.maxwell_box(200, seed=2)
+    s = {f: np.concatenate([base[f]] * 3) for f in ("x", "y", "z", "vx", "vy", "vz", "m")}
+    s["id"] = np.tile(np.arange(200, dtype=np.uint32) + 7, 3)
+    if ids == "all equal":
+        s["id"][:] = 7
+    for k in (2, 5, 70):
+        h, lists = _gpu_knn(S, [dict(n=600, eps=0.01, k=k)], s, want_list=True)
+        href, lref = orc.knn(s["x"], s["y"], s["z"], s["id"], k, want_list=True)
+        assert np.array_equal(h, href)
+        assert np.array_equal(lists[:, :k], lref)
+
+
 def test_knn_rejects_bad_k(S):
     s = W.maxwell_box(64, seed=0)
     dev = S.state_to_device(s)
