@@ -522,11 +522,14 @@ __device__ inline int tidal_groups(const HaloDev& H)
     return (int)(nb < kTidalBlocks ? nb : kTidalBlocks);
 }
 
-// per_halo workgroups for each halo (those past its own leave).  tid_in / tid_out: the state before and after the
+// Workgroup w0 + blockIdx.x: per_halo of them for each halo (those past its own
+// leave), or with `blocks` one for each streaming block (of which a halo keeps
+// the first ones).  tid_in / tid_out: the state before and after the
 // decisions on sums_in (none in the first launch); sums_out: this launch's sums
 // (kTidalSums per workgroup).  The last launch writes the record instead.
 __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
-    const HaloDev* __restrict__ halos, const double* __restrict__ x, const double* __restrict__ y,
+    const HaloDev* __restrict__ halos, const StreamBlock* __restrict__ blocks, int64_t w0,
+    const double* __restrict__ x, const double* __restrict__ y,
     const double* __restrict__ z, const double* __restrict__ m,
     const sidm_center* __restrict__ cen, const double* __restrict__ tid_in,
     double* __restrict__ tid_out, const double* __restrict__ sums_in,
@@ -539,13 +542,16 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
     __shared__ int inside[kTidalSums];
     __shared__ double field[kHostParts][64][3];
     static_assert(kHostParts <= NW && 2 * kTidalSums == 64, "a wave per component, a lane per side");
-    const int h = blockIdx.x / per_halo, g = blockIdx.x % per_halo, t = threadIdx.x;
+    const int t = threadIdx.x;
+    const int64_t wg = w0 + blockIdx.x;
+    const int h = blocks ? blocks[wg].halo : (int)(wg / per_halo);
     const HaloDev& H = halos[h];
+    const int64_t g = blocks ? wg - H.stream_block0 : wg % per_halo;
     const int groups = tidal_groups(H);
     if (g >= (last ? 1 : groups)) return;
     const sidm_center C = cen[h];
     double T[8];
-    for (int q = 0; q < 8; ++q) T[q] = tid_in[8 * h + q];
+    for (int q = 0; q < 8; ++q) T[q] = tid_in[8 * (int64_t)h + q];
     Bracket b{T[3], T[4]};
     double M_hi = T[6];   // mass within the upper bracket
     if (!first) {
@@ -601,11 +607,11 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
         return;
     }
     if (g == 0 && t < 8)
-        tid_out[8 * h + t] = t == 3   ? b.lo
-                             : t == 4 ? b.hi
-                             : t == 6 ? M_hi
-                             : t == 7 ? (first ? 0.0 : 1.0)
-                                      : T[t];
+        tid_out[8 * (int64_t)h + t] = t == 3   ? b.lo
+                                      : t == 4 ? b.hi
+                                      : t == 6 ? M_hi
+                                      : t == 7 ? (first ? 0.0 : 1.0)
+                                               : T[t];
     __syncthreads();   // the previous sums are read before red is reused
     if (t < kTidalSums) {
 #pragma clang fp contract(off)
@@ -624,7 +630,7 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
         // four particles' loads in flight
         constexpr int kLoads = 4;
         const int64_t step = (int64_t)groups * kTidalThreads;
-        for (int64_t i = (int64_t)g * kTidalThreads + t; i < H.n; i += kLoads * step) {
+        for (int64_t i = g * kTidalThreads + t; i < H.n; i += kLoads * step) {
 #pragma clang fp contract(off)
             double d2[kLoads], mp[kLoads];
 #pragma unroll
@@ -682,12 +688,21 @@ hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const Hal
     double* sum[2] = {sums, sums + n_blocks * kTidalSums};
     const int64_t nb = (n_max + kStreamBlock - 1) / kStreamBlock;
     const int groups = (int)(nb < kTidalBlocks ? nb : kTidalBlocks);
+    // many halos, the largest much larger than the others: a workgroup per
+    // streaming block instead of the largest halo's number for each
+    const bool by_block = (int64_t)groups * n_halos > 65536 && n_blocks < (int64_t)groups * n_halos;
     for (int it = 0; it <= kPasses; ++it) {
-        const int per_halo = it == kPasses ? 1 : groups;
-        hipLaunchKernelGGL(k_tidal_pass, dim3((unsigned)per_halo * (unsigned)n_halos),
-                           dim3(kTidalThreads), 0, st, d_halos, x, y, z, m, cen, state[it & 1],
-                           state[(it & 1) ^ 1], sum[(it & 1) ^ 1], sum[it & 1], per_halo, it == 0,
-                           it == kPasses, out);
+        const bool last = it == kPasses;
+        const int per_halo = last ? 1 : groups;
+        const bool blk = by_block && !last;
+        launch_chunks(blk ? n_blocks : (int64_t)per_halo * n_halos, kTidalThreads,
+                      [&](int64_t w0, int64_t count) {
+                          hipLaunchKernelGGL(
+                              k_tidal_pass, dim3((unsigned)count), dim3(kTidalThreads), 0, st,
+                              d_halos, blk ? d_blocks : (const StreamBlock*)nullptr, w0, x, y, z,
+                              m, cen, state[it & 1], state[(it & 1) ^ 1], sum[(it & 1) ^ 1],
+                              sum[it & 1], per_halo, it == 0, last, out);
+                      });
     }
     return hipGetLastError();
 }

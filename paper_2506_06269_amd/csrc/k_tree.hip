@@ -87,16 +87,17 @@ __global__ __launch_bounds__(kStreamBlock) void k_block_range(
         for (int c = 0; c < kRange; ++c) brange[kRange * (int64_t)blockIdx.x + c] = e[c];
 }
 
+// Per halo, from halo h0 on: its box and masses.
 constexpr int kRangeThreads = 1024;
 __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
-    const HaloDev* __restrict__ halos, const double* __restrict__ brange,
+    const HaloDev* __restrict__ halos, int h0, int n_halos, const double* __restrict__ brange,
     double* __restrict__ bbox, double* __restrict__ cmass, int* __restrict__ status,
     const int* __restrict__ active, int tick)
 {
     if (tick_idle(active, tick)) return;
     __shared__ double red[kRange * (kRangeThreads / 64)];
-    const HaloDev& H = halos[blockIdx.x];
-    const int t = threadIdx.x;
+    const int h = h0 + (int)blockIdx.x, t = threadIdx.x;
+    const HaloDev& H = halos[h];
     const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
     double e[kRange] = {INFINITY,  INFINITY,  INFINITY,  INFINITY, -INFINITY,
                         -INFINITY, -INFINITY, -INFINITY, 0.0};
@@ -108,10 +109,10 @@ __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
     block_range<kRangeThreads / 64>(e, red);
     if (t == 0) {
         for (int c = 0; c < 3; ++c) {
-            bbox[6 * blockIdx.x + c] = e[c];
-            bbox[6 * blockIdx.x + 3 + c] = e[4 + c];
+            bbox[6 * (int64_t)h + c] = e[c];
+            bbox[6 * (int64_t)h + 3 + c] = e[4 + c];
         }
-        put_mass(H, blockIdx.x, gridDim.x, e, cmass, status);
+        put_mass(H, h, n_halos, e, cmass, status);
     }
 }
 
@@ -364,8 +365,9 @@ static_assert(kSmallN == 8 * kSmallThreads, "the largest instantiation below");
 template <int IPT>
 __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const double* __restrict__ m, const HaloDev* __restrict__ halos, double* __restrict__ cmass,
-    int* __restrict__ status, unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
+    const double* __restrict__ m, const HaloDev* __restrict__ halos, int h0, int n_halos,
+    double* __restrict__ cmass, int* __restrict__ status, unsigned long long* __restrict__ keys,
+    uint32_t* __restrict__ vals,
     const int8_t* __restrict__ bin, int tick, int bmax, int rank_shift,
     const int* __restrict__ active)
 {
@@ -375,7 +377,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
     __shared__ uint32_t cnt[kSmallWaves][kDigits];
     __shared__ double red[kRange * kSmallWaves];
     __shared__ uint32_t sw[kDigits / 64];
-    const HaloDev& H = halos[blockIdx.x];
+    const int h = h0 + (int)blockIdx.x;
+    const HaloDev& H = halos[h];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int n = (int)H.n, q0 = wv * (64 * IPT) + lane;
     double px[IPT], py[IPT], pz[IPT];
@@ -398,7 +401,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
         }
     }
     block_range<kSmallWaves>(e, red);
-    if (t == 0) put_mass(H, blockIdx.x, gridDim.x, e, cmass, status);
+    if (t == 0) put_mass(H, h, n_halos, e, cmass, status);
     const double inv = key_scale(e, e + 4);
     unsigned long long key[IPT];
     uint32_t id[IPT], rank[IPT], dig[IPT];
@@ -668,9 +671,11 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
     int cur = 0;
     if (P.n_max <= kSmallN) {
         auto small = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(P.n_halos), dim3(kSmallThreads), 0, st, s->x, s->y, s->z,
-                               s->m, w.halos, w.cref, status, w.keys[0], w.vals[0], w.bin, tick,
-                               bmax, P.rank_shift, active);
+            launch_chunks(P.n_halos, kSmallThreads, [&](int64_t h0, int64_t count) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)count), dim3(kSmallThreads), 0, st, s->x,
+                                   s->y, s->z, s->m, w.halos, (int)h0, P.n_halos, w.cref, status,
+                                   w.keys[0], w.vals[0], w.bin, tick, bmax, P.rank_shift, active);
+            });
         };
         if (P.n_max <= kSmallThreads) small(k_cell_small<1>);
         else if (P.n_max <= 2 * kSmallThreads) small(k_cell_small<2>);
@@ -684,8 +689,11 @@ hipError_t launch_cell_list(const Plan& P, const sidm_state* s, Scratch& w, hipS
         hipLaunchKernelGGL(k_block_range, dim3((unsigned)P.n_blocks), dim3(kStreamBlock), 0, st,
                            s->x, s->y, s->z, s->m, w.blocks, w.brange, w.sort_ws, n_zero, active,
                            tick);
-        hipLaunchKernelGGL(k_halo_range, dim3(P.n_halos), dim3(kRangeThreads), 0, st, w.halos,
-                           w.brange, w.bbox, w.cref, status, active, tick);
+        launch_chunks(P.n_halos, kRangeThreads, [&](int64_t h0, int64_t count) {
+            hipLaunchKernelGGL(k_halo_range, dim3((unsigned)count), dim3(kRangeThreads), 0, st,
+                               w.halos, (int)h0, P.n_halos, w.brange, w.bbox, w.cref, status,
+                               active, tick);
+        });
         // at most 16 blocks per workgroup; from 64 workgroups on, fewer of them
         // are better: each adds up to kDigits words per pass to the same counts
         // (65536 particles: 10.3 us with 256 workgroups, 7.5 us with 64)

@@ -123,6 +123,17 @@ struct DevCounters {
     unsigned long long ticket;            // next work item of a persistent gravity launch
 };
 
+// Launches of `total` workgroups of `threads` as f(first, count), each within the
+// 2^32 work items that a grid may have (a call of 33001 halos, one of 65536
+// particles, would need more for its tidal radii: its larger grid was cut off).
+template <class F>
+inline void launch_chunks(int64_t total, int threads, F f)
+{
+    const int64_t most = (int64_t(1) << 31) / threads;
+    for (int64_t first = 0; first < total; first += most)
+        f(first, total - first < most ? total - first : most);
+}
+
 #ifdef __HIPCC__
 // 1/sqrt(r2) for finite r2 > 0: the hardware estimate refined by one Newton
 // step, y1 = y0 + y0 (1 - r2 y0^2) / 2, which squares the estimate's relative

@@ -1,0 +1,50 @@
+"""CPU checks of launch sizes and buffer sizes (csrc/sidm_plan.hpp, compiled for
+the host with g++): kernels with a workgroup per halo are cut into launches
+that a grid can hold and that cover every halo once."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+_SRC = r'''
+#include "sidm_plan.hpp"
+extern "C" int chunks(long long total, int threads, long long* first, long long* count, int cap) {
+    int k = 0;
+    sidm::launch_chunks(total, threads, [&](int64_t f, int64_t c) {
+        if (k < cap) { first[k] = f; count[k] = c; }
+        ++k;
+    });
+    return k;
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def L(tmp_path_factory):
+    d = tmp_path_factory.mktemp("sidm_launch")
+    src, so = str(d / "p.cpp"), str(d / "p.so")
+    with open(src, "w") as f:
+        f.write(_SRC)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2506_06269_amd", "csrc"), src, "-o", so,
+                    "-L", os.path.join(ROCM, "lib"), "-lamdhip64"], check=True)
+    return C.CDLL(so)
+
+
+@pytest.mark.parametrize("threads", [64, 256, 512, 1024])
+@pytest.mark.parametrize("total", [1, 4096, (1 << 22) - 1, 1 << 22, 10_000_001, 256 * 33001])
+def test_launches_fit_a_grid(L, total, threads):
+    first, count = (C.c_longlong * 64)(), (C.c_longlong * 64)()
+    L.chunks.argtypes = [C.c_longlong, C.c_int, C.c_void_p, C.c_void_p, C.c_int]
+    k = L.chunks(total, threads, first, count, 64)
+    assert 1 <= k <= 64
+    at = 0
+    for q in range(k):
+        assert first[q] == at and 0 < count[q] and count[q] * threads < 1 << 32
+        at += count[q]
+    assert at == total
+    assert k == 1 or total * threads > 1 << 31
