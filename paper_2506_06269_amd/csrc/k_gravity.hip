@@ -794,9 +794,14 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
 // the instructions alone 53), 4 x 256 108 ms, one-sided 158 ms.  The atomics
 // take some 6 % (half of them taken out: 97 ms); they go up steeply with their
 // number (i-side sums flushed every 2048, 512 and 256 j: 26.2, 29.8 and 52 ms at
-// 262144), so those sums are kept in two levels, a tile's and the item's (one
-// plain sum over 2048 j showed in the error against the oracle).  Items cut finer for halos of 16384 to 32768 were slower (the
-// i-side flushes).
+// 262144), so those sums are kept in two levels, a tile's and a run's of
+// kSymRun64 tiles (one plain sum over 2048 j showed in the error against the
+// oracle).  The length of an item grows with N^2, to 8192 tiles at 2^24, and
+// the error of a plain sum with it (up to 2.4e-15 there); a run's stays that
+// of 32 tiles, where the error is that of the compensated one-sided sums
+// (5.1e-16 of the force at 262144; both are the terms').  Runs of 8, 16 and 32
+// tiles and whole items: 407, 401, 399 and 399 ms at 2^20.  Items cut finer for
+// halos of 16384 to 32768 were slower (the i-side flushes).
 //
 // The totals are 128-bit fixed point in two words that never carry into each
 // other: x = v 2^s is cut into its nearest integer and the remainder times
@@ -805,6 +810,7 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
 // every partial sum (a single word of 64 bits would round them at 2^-61 of the
 // bound, 10^-10 of the force on a particle at a halo's edge).
 constexpr double kSymLow = 0x1p44;
+constexpr int kSymRun64 = 32;
 
 __device__ inline void fixed_add(unsigned long long* a, double x)
 {
@@ -974,7 +980,7 @@ __device__ inline void grav_sym64_body(const double* __restrict__ x, const doubl
     double sa, sp;
     sym_scales(H, mref, sa, sp);
     double xi[IREG], yi[IREG], zi[IREG], mi[IREG];
-    double sx[IREG], sy[IREG], sz[IREG], sq[IREG];   // sums over the item's tiles
+    double sx[IREG], sy[IREG], sz[IREG], sq[IREG];   // sums over a run of tiles
 #pragma unroll
     for (int r = 0; r < IREG; ++r) {
         const int64_t li = il0 + (int64_t)r * NT + t;
@@ -986,6 +992,7 @@ __device__ inline void grav_sym64_body(const double* __restrict__ x, const doubl
         }
         sx[r] = sy[r] = sz[r] = sq[r] = 0.0;
     }
+    int run = 0;   // tiles in the sums
     for (int64_t j0 = it.j0; j0 < it.j1; j0 += NT) {
         const int64_t lj0 = j0 - H.offset;
         // padding as in the one-sided tiles (no weight on either side)
@@ -1032,16 +1039,19 @@ __device__ inline void grav_sym64_body(const double* __restrict__ x, const doubl
                 fixed_add(a + 6, s3 * sp);
             }
         }
-    }
+        if (++run < kSymRun64 && j0 + NT < it.j1) continue;
+        run = 0;
 #pragma unroll
-    for (int r = 0; r < IREG; ++r) {
-        const int64_t li = il0 + (int64_t)r * NT + t;
-        if (li < H.n) {
-            unsigned long long* a = acc + 8 * (H.sbase + li);
-            fixed_add(a + 0, sx[r] * sa);
-            fixed_add(a + 2, sy[r] * sa);
-            fixed_add(a + 4, sz[r] * sa);
-            fixed_add(a + 6, sq[r] * sp);
+        for (int r = 0; r < IREG; ++r) {
+            const int64_t li = il0 + (int64_t)r * NT + t;
+            if (li < H.n) {
+                unsigned long long* a = acc + 8 * (H.sbase + li);
+                fixed_add(a + 0, sx[r] * sa);
+                fixed_add(a + 2, sy[r] * sa);
+                fixed_add(a + 4, sz[r] * sa);
+                fixed_add(a + 6, sq[r] * sp);
+            }
+            sx[r] = sy[r] = sz[r] = sq[r] = 0.0;
         }
     }
 }
