@@ -17,47 +17,54 @@ namespace sidm {
 
 // ---------------------------------------------------------------- bounding boxes
 // Box and mass range of a workgroup's particles: per-thread extrema e (min x,
-// y, z, m, max x, y, z, m) reduced over NW waves; every thread returns the
-// result.  red: 8 * NW words of LDS.
-template <int NW>
-__device__ inline void block_range(double (&e)[kRange], double* red)
+// y, z, m, max x, y, z, m, and whether any value is not finite; with C = kRange
+// also the sum of the masses' magnitudes) reduced over NW waves; every thread
+// returns the result.  red: C * NW words of LDS.
+template <int NW, int C>
+__device__ inline void block_range(double (&e)[C], double* red)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int c = 0; c < kRange; ++c) {
-        e[c] = c < 4 ? rows_min(row_min(e[c])) : rows_max(row_max(e[c]));
+    for (int c = 0; c < C; ++c) {
+        e[c] = c < 4          ? rows_min(row_min(e[c]))
+               : c < kExtrema ? rows_max(row_max(e[c]))
+                              : rows_sum(row_sum(e[c]));
         if (lane == 0) red[c * NW + wv] = e[c];
     }
     __syncthreads();
     static_assert(16 % NW == 0, "the waves' results repeat in a row of lanes");
 #pragma unroll
-    for (int c = 0; c < kRange; ++c) {
+    for (int c = 0; c < C; ++c) {
         const double v = red[c * NW + lane % NW];
-        e[c] = c < 4 ? row_min(v) : row_max(v);
+        e[c] = c < 4 ? row_min(v) : c < kExtrema ? row_max(v) : row_sum(v) * (NW / 16.0);
     }
 }
 
 // The common mass of a halo (cmass[h], 0 when its masses differ), the largest
 // magnitude of its masses (cmass[n_halos + h]), and whether the FP64 symmetric
 // tiles can sum it (cmass[2 n_halos + h]): their fixed-point totals need finite
-// values and scales, and hold a sum to 2^-104 of its bound n m 0.385 / eps^2,
-// which is below 2^-63 of n m / R^2, the least force scale of a box of side R,
-// for R up to 2^20 eps (workloads: 10^3 to 10^4).  With a status array, a halo that scatters
-// (sigma_m > 0) without a common mass is flagged: the probability of a pair
-// takes the mass of one member, which is only symmetric when the masses are
-// equal (each run of the paper's Table 1 has one particle mass), so such a
-// halo is not scattered.
-__device__ inline void put_mass(const HaloDev& H, int h, int n_halos, const double (&e)[kRange],
+// values and scales, and hold a sum to 2^-104 of its bound n m 0.385 / eps^2
+// with m the largest magnitude.  The least force scale of a box of side R is
+// M / R^2, M the sum of the magnitudes; the unit is below 2^-63 of it for
+// (n m / M) (R / eps)^2 up to 2^40 (equal masses: R up to 2^20 eps; workloads:
+// 10^3 to 10^4).  sum: M, or 0 for a halo too small for those tiles.  With a
+// status array, a halo that scatters (sigma_m > 0) without a common mass is
+// flagged: the probability of a pair takes the mass of one member, which is
+// only symmetric when the masses are equal (each run of the paper's Table 1 has
+// one particle mass), so such a halo is not scattered.
+__device__ inline void put_mass(const HaloDev& H, int h, int n_halos, const double* e, double sum,
                                 double* __restrict__ cmass, int* __restrict__ status)
 {
     const double lo = e[3], hi = e[7], top = fmax(fabs(lo), fabs(hi));
     const bool equal = lo == hi;
     cmass[h] = equal ? lo : 0.0;
     cmass[n_halos + h] = top;
-    const double side = fmax(fmax(e[4] - e[0], e[5] - e[1]), e[6] - e[2]);
+    const double side = fmax(fmax(e[4] - e[0], e[5] - e[1]), e[6] - e[2]) / H.eps;
     const double mref = equal && lo > 0.0 ? 1.0 : top;
-    cmass[2 * n_halos + h] = e[8] == 0.0 && side <= 0x1p20 * H.eps && H.eps2 > 0x1p-400 &&
-                                     H.eps2 < 0x1p400 && mref > 0x1p-400 && mref < 0x1p400
+    const double ratio = equal ? 1.0 : (double)H.n * top / sum;
+    cmass[2 * n_halos + h] = e[8] == 0.0 && sum > 0.0 && ratio * (side * side) <= 0x1p40 &&
+                                     H.eps2 > 0x1p-400 && H.eps2 < 0x1p400 &&
+                                     mref > 0x1p-400 && mref < 0x1p400
                                  ? 1.0
                                  : 0.0;
     if (status && !equal && H.sigma_m > 0.0) atomicOr(&status[h], SIDM_DEV_UNEQUAL_MASS);
@@ -81,7 +88,7 @@ __global__ __launch_bounds__(kStreamBlock) void k_block_range(
     const int64_t i = B.start + (t < B.count ? t : 0);
     const double px = x[i], py = y[i], pz = z[i], mi = m[i];
     const double nf = (px - px) + (py - py) + (pz - pz) + (mi - mi) == 0.0 ? 0.0 : 1.0;
-    double e[kRange] = {px, py, pz, mi, px, py, pz, mi, nf};
+    double e[kRange] = {px, py, pz, mi, px, py, pz, mi, nf, t < B.count ? fabs(mi) : 0.0};
     block_range<kStreamBlock / 64>(e, red);
     if (t == 0)
         for (int c = 0; c < kRange; ++c) brange[kRange * (int64_t)blockIdx.x + c] = e[c];
@@ -100,11 +107,11 @@ __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
     const HaloDev& H = halos[h];
     const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
     double e[kRange] = {INFINITY,  INFINITY,  INFINITY,  INFINITY, -INFINITY,
-                        -INFINITY, -INFINITY, -INFINITY, 0.0};
+                        -INFINITY, -INFINITY, -INFINITY, 0.0,      0.0};
     for (int64_t b = t; b < nb; b += kRangeThreads)
         for (int c = 0; c < kRange; ++c) {
             const double v = brange[kRange * (H.stream_block0 + b) + c];
-            e[c] = c < 4 ? fmin(e[c], v) : fmax(e[c], v);
+            e[c] = c < 4 ? fmin(e[c], v) : c < kExtrema ? fmax(e[c], v) : e[c] + v;
         }
     block_range<kRangeThreads / 64>(e, red);
     if (t == 0) {
@@ -112,7 +119,7 @@ __global__ __launch_bounds__(kRangeThreads) void k_halo_range(
             bbox[6 * (int64_t)h + c] = e[c];
             bbox[6 * (int64_t)h + 3 + c] = e[4 + c];
         }
-        put_mass(H, h, n_halos, e, cmass, status);
+        put_mass(H, h, n_halos, e, e[kExtrema], cmass, status);
     }
 }
 
@@ -375,14 +382,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
     __shared__ unsigned long long skey[kSmallThreads * IPT];
     __shared__ uint16_t sidx[kSmallThreads * IPT];
     __shared__ uint32_t cnt[kSmallWaves][kDigits];
-    __shared__ double red[kRange * kSmallWaves];
+    __shared__ double red[kExtrema * kSmallWaves];
     __shared__ uint32_t sw[kDigits / 64];
     const int h = h0 + (int)blockIdx.x;
     const HaloDev& H = halos[h];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int n = (int)H.n, q0 = wv * (64 * IPT) + lane;
     double px[IPT], py[IPT], pz[IPT];
-    double e[kRange] = {INFINITY,  INFINITY,  INFINITY,  INFINITY, -INFINITY,
+    double e[kExtrema] = {INFINITY,  INFINITY,  INFINITY,  INFINITY, -INFINITY,
                         -INFINITY, -INFINITY, -INFINITY, 0.0};
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
@@ -401,7 +408,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_cell_small(
         }
     }
     block_range<kSmallWaves>(e, red);
-    if (t == 0) put_mass(H, h, n_halos, e, cmass, status);
+    if (t == 0) put_mass(H, h, n_halos, e, 0.0, cmass, status);
     const double inv = key_scale(e, e + 4);
     unsigned long long key[IPT];
     uint32_t id[IPT], rank[IPT], dig[IPT];

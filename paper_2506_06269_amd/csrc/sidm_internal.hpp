@@ -22,7 +22,8 @@ constexpr int kTickSplit = 16;       // j-splits of a block-step tick
 constexpr int kSortBits = 8;         // radix digit width
 constexpr int kSortBlock = 256;      // threads per sort tile
 constexpr int kSortMaxPasses = 8;    // 64-bit keys
-constexpr int kRange = 9;            // min x, y, z, m, max x, y, z, m, whether any is not finite
+constexpr int kExtrema = 9;          // min x, y, z, m, max x, y, z, m, whether any is not finite
+constexpr int kRange = kExtrema + 1; // and the sum of |m|
 constexpr int64_t kSmallN = 8192;    // halos up to this size are sorted by one workgroup
 
 // Shape of the direct-sum gravity launch: i-particles per thread, threads per

@@ -33,6 +33,15 @@ __device__ inline double row_max(double v)
     return fmax(v, dpp_f64<0x121>(v));
 }
 
+// Sum over each row of 16 lanes, in the same order on every lane.
+__device__ inline double row_sum(double v)
+{
+    v += dpp_f64<0x128>(v);
+    v += dpp_f64<0x124>(v);
+    v += dpp_f64<0x122>(v);
+    return v + dpp_f64<0x121>(v);
+}
+
 // ... and over the rows of the wave (v uniform within each row).
 __device__ inline double rows_min(double v)
 {
@@ -44,6 +53,12 @@ __device__ inline double rows_max(double v)
 {
     v = fmax(v, __shfl_xor(v, 16, 64));
     return fmax(v, __shfl_xor(v, 32, 64));
+}
+
+__device__ inline double rows_sum(double v)
+{
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
 }
 
 // Maximum over the lanes of the wave (not NaN).

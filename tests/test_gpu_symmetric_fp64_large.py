@@ -85,3 +85,37 @@ def test_long_items_keep_small_tiles():
         worst = max(worst, float(abs(L(got[0][i]) - ref) / ref))
     print(f"worst {worst:.2e}", flush=True)
     assert worst < (32 * 0.45 + 16) * 2.0 ** -53
+
+
+@pytest.mark.parametrize("masses", ["equal", "one dominates"])
+def test_wide_boxes_by_mass(orc, masses):
+    """A box of 2^19 softenings: the totals hold the force at its edge when the
+    masses are equal, and do not when one of 41460 holds almost all mass (their
+    unit goes with n times the largest mass, the force with the mass): such a
+    halo gives the one-sided sums bit for bit."""
+    import torch
+    import paper_2506_06269_amd as S
+    n, eps = 41460, 0.01
+    s = dict(W.nfw_halo(n, seed=6))
+    s["z"] = s["z"].copy()
+    s["z"][123] = 2.0 ** 19 * eps + s["z"].min()
+    if masses != "equal":
+        s["m"] = np.full(n, 1e-8)
+        s["m"][5] = 1.0
+    dev = S.state_to_device(s)
+    ctx = S.sidm_create(0, n, 1)
+    halo = dict(n=n, eps=eps)
+    out = []
+    for min_n in (4096, 0):
+        S.sidm_set_symmetric(ctx, min_n)
+        S.sidm_gravity(ctx, [halo], dev, S.SIDM_PREC_FP64)
+        torch.cuda.synchronize()
+        h = S.state_to_host(dev)
+        out.append([h[f] for f in ("ax", "ay", "az", "pot")])
+    S.sidm_destroy(ctx)
+    same = all(np.array_equal(a, b) for a, b in zip(*out))
+    assert same == (masses != "equal")
+    ax, ay, az, pot, an = orc.gravity(s["x"], s["y"], s["z"], s["m"], 1.0, eps, want_norm=True)
+    got = out[0]
+    e = np.sqrt((got[0] - ax) ** 2 + (got[1] - ay) ** 2 + (got[2] - az) ** 2) / an
+    assert e.max() < 1e-12 and np.max(np.abs(got[3] - pot) / np.abs(pot)) < 1e-12
