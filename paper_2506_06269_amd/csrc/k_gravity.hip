@@ -634,18 +634,24 @@ __global__ __launch_bounds__(NT, kSymWaves) void k_grav_sym(
     }
 }
 
-// Zero fixed-point totals (`words` per particle) of the particles of halos that
-// take the symmetric tiles of this kind.
+// Zero fixed-point totals (four words per particle; with `low` given also the low
+// words of the FP64 totals) of the particles of halos that take the symmetric
+// tiles of this kind.
 __global__ __launch_bounds__(kStreamBlock) void k_sym_zero(const StreamBlock* __restrict__ blocks,
                                                            const HaloDev* __restrict__ halos,
                                                            unsigned long long* __restrict__ acc,
-                                                           int kind, int words)
+                                                           unsigned long long* __restrict__ low,
+                                                           int kind)
 {
     const StreamBlock B = blocks[blockIdx.x];
     const HaloDev& H = halos[B.halo];
     if (!(H.grav_sym & kind)) return;
-    unsigned long long* a = acc + words * (H.sbase + (B.start - H.offset));
-    for (int q = threadIdx.x; q < words * B.count; q += kStreamBlock) a[q] = 0ull;
+    const int64_t li = B.start - H.offset;
+    unsigned long long* a = acc + 4 * (H.sbase + li);
+    for (int q = threadIdx.x; q < 4 * B.count; q += kStreamBlock) a[q] = 0ull;
+    if (!low) return;
+    a = low + 4 * (H.part_base + li);
+    for (int q = threadIdx.x; q < 4 * B.count; q += kStreamBlock) a[q] = 0ull;
 }
 
 // ---------------------------------------------------------------- FP64 tiles
@@ -808,20 +814,22 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
 // kSymLow, each summed with integer atomics, so that the result does not
 // depend on the order in which items finish and keeps what FP64 holds of
 // every partial sum (a single word of 64 bits would round them at 2^-61 of the
-// bound, 10^-10 of the force on a particle at a halo's edge).
+// bound, 10^-10 of the force on a particle at a halo's edge).  The low words lie
+// in the first partial row of the halo, which the one-sided tiles leave alone
+// where the symmetric ones take the halo.
 constexpr double kSymLow = 0x1p44;
 constexpr int kSymRun64 = 32;
 
-__device__ inline void fixed_add(unsigned long long* a, double x)
+__device__ inline void fixed_add(unsigned long long* a, unsigned long long* low, double x)
 {
     const double hi = rint(x);
-    atomicAdd(a + 0, (unsigned long long)(long long)hi);
-    atomicAdd(a + 1, (unsigned long long)(long long)rint((x - hi) * kSymLow));
+    atomicAdd(a, (unsigned long long)(long long)hi);
+    atomicAdd(low, (unsigned long long)(long long)rint((x - hi) * kSymLow));
 }
 
-__device__ inline double fixed_value(const long long* q)
+__device__ inline double fixed_value(long long hi, long long low)
 {
-    return (double)q[0] + (double)q[1] / kSymLow;
+    return (double)hi + (double)low / kSymLow;
 }
 
 struct Words {
@@ -971,7 +979,8 @@ template <int IREG, int NT, bool EQM>
 __device__ inline void grav_sym64_body(const double* __restrict__ x, const double* __restrict__ y,
                                        const double* __restrict__ z, const double* __restrict__ m,
                                        const SymItem& it, const HaloDev& H, double mref,
-                                       unsigned long long* __restrict__ acc, SymLds64<NT>& L)
+                                       unsigned long long* __restrict__ acc,
+                                       unsigned long long* __restrict__ low, SymLds64<NT>& L)
 {
     constexpr int NW = NT / 64;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -1032,11 +1041,12 @@ __device__ inline void grav_sym64_body(const double* __restrict__ x, const doubl
                     s2 += L.jpart[w][t][2];
                     s3 += L.jpart[w][t][3];
                 }
-                unsigned long long* a = acc + 8 * (H.sbase + lj0 + t);
-                fixed_add(a + 0, -s0 * sa);
-                fixed_add(a + 2, -s1 * sa);
-                fixed_add(a + 4, -s2 * sa);
-                fixed_add(a + 6, s3 * sp);
+                unsigned long long* a = acc + 4 * (H.sbase + lj0 + t);
+                unsigned long long* l = low + 4 * (H.part_base + lj0 + t);
+                fixed_add(a + 0, l + 0, -s0 * sa);
+                fixed_add(a + 1, l + 1, -s1 * sa);
+                fixed_add(a + 2, l + 2, -s2 * sa);
+                fixed_add(a + 3, l + 3, s3 * sp);
             }
         }
         if (++run < kSymRun64 && j0 + NT < it.j1) continue;
@@ -1045,11 +1055,12 @@ __device__ inline void grav_sym64_body(const double* __restrict__ x, const doubl
         for (int r = 0; r < IREG; ++r) {
             const int64_t li = il0 + (int64_t)r * NT + t;
             if (li < H.n) {
-                unsigned long long* a = acc + 8 * (H.sbase + li);
-                fixed_add(a + 0, sx[r] * sa);
-                fixed_add(a + 2, sy[r] * sa);
-                fixed_add(a + 4, sz[r] * sa);
-                fixed_add(a + 6, sq[r] * sp);
+                unsigned long long* a = acc + 4 * (H.sbase + li);
+                unsigned long long* l = low + 4 * (H.part_base + li);
+                fixed_add(a + 0, l + 0, sx[r] * sa);
+                fixed_add(a + 1, l + 1, sy[r] * sa);
+                fixed_add(a + 2, l + 2, sz[r] * sa);
+                fixed_add(a + 3, l + 3, sq[r] * sp);
             }
             sx[r] = sy[r] = sz[r] = sq[r] = 0.0;
         }
@@ -1063,7 +1074,8 @@ __global__ __launch_bounds__(NT, IREG >= 8 || NT >= 512 ? 2 : 3) void k_grav_sym
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
     const double* __restrict__ m, const SymItem* __restrict__ items, int64_t n_items,
     unsigned long long* __restrict__ ticket, const HaloDev* __restrict__ halos,
-    const double* __restrict__ cmass, int n_halos, unsigned long long* __restrict__ acc)
+    const double* __restrict__ cmass, int n_halos, unsigned long long* __restrict__ acc,
+    unsigned long long* __restrict__ low)
 {
     __shared__ SymLds64<NT> L;
     const double* __restrict__ sym_ok = cmass + 2 * n_halos;
@@ -1083,7 +1095,7 @@ __global__ __launch_bounds__(NT, IREG >= 8 || NT >= 512 ? 2 : 3) void k_grav_sym
         const SymItem it = items[k];
         if (!takes(it.halo)) continue;   // uniform over the block
         grav_sym64_body<IREG, NT, EQM>(x, y, z, m, it, halos[it.halo],
-                                       EQM ? 1.0 : cmass[n_halos + it.halo], acc, L);
+                                       EQM ? 1.0 : cmass[n_halos + it.halo], acc, low, L);
     }
 }
 
@@ -1135,7 +1147,7 @@ __global__ __launch_bounds__(kStreamBlock) void k_grav_finalize(
         const double meq = cmass[B.halo];
         double sa, spp;
         sym_scales(H, meq > 0.0 ? 1.0 : cmass[n_halos + B.halo], sa, spp);
-        const long long* q = (const long long*)symacc + (kind == kSymMixed ? 4 : 8) * p;
+        const long long* q = (const long long*)symacc + 4 * p;
         const double ms = meq > 0.0 ? meq : 1.0;
         if (kind == kSymMixed) {
             sx = ms * ((double)q[0] / sa);
@@ -1143,10 +1155,11 @@ __global__ __launch_bounds__(kStreamBlock) void k_grav_finalize(
             sz = ms * ((double)q[2] / sa);
             sp = ms * ((double)q[3] / spp);
         } else {
-            sx = ms * (fixed_value(q + 0) / sa);
-            sy = ms * (fixed_value(q + 2) / sa);
-            sz = ms * (fixed_value(q + 4) / sa);
-            sp = ms * (fixed_value(q + 6) / spp);
+            const long long* l = (const long long*)partial + 4 * (H.part_base + li);
+            sx = ms * (fixed_value(q[0], l[0]) / sa);
+            sy = ms * (fixed_value(q[1], l[1]) / sa);
+            sz = ms * (fixed_value(q[2], l[2]) / sa);
+            sp = ms * (fixed_value(q[3], l[3]) / spp);
         }
     } else {
         // rows in flight together (1500 particles, 24 rows: 9.7 us one by one)
@@ -1315,9 +1328,10 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
                            w.sm, w.blocks, w.halos, w.sub, w.sub_n, w.xm32, active, tick);
     if (sym) {
         const int64_t slots = mixed ? w.slots_sym : w.slots_sym64;
+        unsigned long long* low = (unsigned long long*)w.partial;
         if (slots <= 0 || !w.symacc || !w.sym_items) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_sym_zero, dim3(nb), dim3(kStreamBlock), 0, st, w.blocks, w.halos,
-                           w.symacc, kind, mixed ? 4 : 8);
+                           w.symacc, mixed ? nullptr : low, kind);
         if (tile_begin) (void)hipEventRecord(tile_begin, st);
         tile_begin = nullptr;
         const unsigned grid = (unsigned)std::min<int64_t>(slots, P.n_sym_items);
@@ -1331,7 +1345,7 @@ hipError_t launch_gravity(bool mixed, const Plan& P, Scratch& w, const sidm_stat
             hipLaunchKernelGGL(k_ticket_reset, dim3(1), dim3(64), 0, st, w.counters);
             hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, w.sx, w.sy, w.sz, w.sm,
                                w.sym_items, P.n_sym_items, ticket, w.halos, w.cref, P.n_halos,
-                               w.symacc);
+                               w.symacc, low);
         };
         const bool ok = mixed ? with_sym_shape<true>(P.shape.ireg, P.shape.nt, launch_mixed)
                               : with_sym_shape<false>(P.shape.ireg, P.shape.nt, launch_fp64);

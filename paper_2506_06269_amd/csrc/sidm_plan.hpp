@@ -118,11 +118,11 @@ struct Scratch {
     int64_t grav_slots = 0;       // resident blocks of the gravity tiles on the whole device
     int64_t slots_mixed = 0, slots_fp64 = 0;   // of the plan's shape, per precision
     // symmetric tiles: work items, fixed-point totals (4 words per sorted
-    // particle, FP64 8), resident blocks
+    // particle; the low words of FP64 totals are in `partial`), resident blocks
     SymItem* sym_items = nullptr;
     int64_t sym_items_cap = 0;
     unsigned long long* symacc = nullptr;
-    int64_t symacc_n = 0;             // words
+    int64_t symacc_n = 0;             // particles
     int64_t slots_sym = 0, slots_sym64 = 0;
     // cell list
     unsigned long long* keys[2] = {nullptr, nullptr};
@@ -805,15 +805,14 @@ inline bool ensure_sym_tables(Scratch& w, const Plan& P, std::string& why)
         }
         w.sym_items_cap = P.n_sym_items;
     }
-    const int64_t words = (P.any_sym64 ? 8 : 4) * P.n_sorted;
-    if (words > w.symacc_n) {
+    if (P.n_sorted > w.symacc_n) {
         dfree(w.symacc);
         w.symacc_n = 0;
-        if (!dalloc(w.symacc, words)) {
+        if (!dalloc(w.symacc, 4 * P.n_sorted)) {
             why = "out of device memory for the symmetric tiles' totals";
             return false;
         }
-        w.symacc_n = words;
+        w.symacc_n = P.n_sorted;
     }
     return true;
 }
