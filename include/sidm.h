@@ -187,7 +187,8 @@ typedef struct {
 sidm_status sidm_create(sidm_ctx **out, int device, int64_t max_particles, int32_t max_halos);
 
 /* Sets the per-call event capacity, and the candidate capacity to four times
- * it (reallocates; call outside graph capture). */
+ * it; from the capacity of a new context on to at least two per particle, as
+ * there (reallocates; call outside graph capture). */
 sidm_status sidm_set_event_capacity(sidm_ctx *ctx, int64_t max_events);
 
 /* Releases the context and its scratch memory (waits for the device). */

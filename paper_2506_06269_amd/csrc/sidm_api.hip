@@ -368,8 +368,7 @@ sidm_status sidm_create(sidm_ctx** out, int device, int64_t max_particles, int32
     c->max_halos = max_halos;
     DeviceGuard g(device);
     std::string why;
-    const int64_t max_events = std::max<int64_t>(4096, max_particles / 8);
-    if (!alloc_scratch(c->w, max_particles, max_halos, max_events, why)) {
+    if (!alloc_scratch(c->w, max_particles, max_halos, default_events(max_particles), why)) {
         free_scratch(c->w);
         delete c;
         return SIDM_ERR_NOMEM;

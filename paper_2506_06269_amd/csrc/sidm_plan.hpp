@@ -242,18 +242,29 @@ inline void dfree(T*& p)
     p = nullptr;
 }
 
-// Events and the candidates of the exact decision (four per event slot: at the
-// benchmark's density a pair's draw falls below the bound some 70 times as
-// often as below P, and the default event buffer, N/8, holds about 50 times
-// a step's events; an overflow only costs a second pair pass).
-// Room for max_events events and, unless given, four times as many candidates.
-inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why,
-                           int64_t max_cands = 0)
+// Event slots of a new context.
+inline int64_t default_events(int64_t N) { return std::max<int64_t>(4096, N / 8); }
+
+// Room for candidates of the exact decision beside max_events events in a
+// context of N particles: four per event slot and, unless the caller asks for
+// fewer events than a new context has, at least two per particle.  At the
+// benchmark's density a pair's draw falls below the cheap bound of P some 70
+// times as often as below P, and N/8 slots hold about 50 times a step's events;
+// but a cycle over long steps passes four per slot early, and a second pair
+// pass then costs more than the first (65536 particles, 0.9 candidates each: 1.4
+// ms after 0.5).  An overflow only costs that pass.
+inline int64_t candidate_room(int64_t max_events, int64_t N)
+{
+    const int64_t room = 4 * max_events;
+    return max_events < default_events(N) ? room : std::max<int64_t>(room, 2 * N);
+}
+
+inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why)
 {
     dfree(w.events);
     dfree(w.cands);
     w.max_events = max_events;
-    w.max_cands = std::max<int64_t>(4 * max_events, max_cands);
+    w.max_cands = candidate_room(max_events, w.max_particles);
     if (!dalloc(w.events, max_events) || !dalloc(w.cands, w.max_cands)) {
         why = "cannot allocate the event buffers";
         w.max_events = w.max_cands = 0;
@@ -332,11 +343,7 @@ inline bool alloc_scratch(Scratch& w, int64_t N, int32_t H, int64_t max_events, 
     // the two key buffers of the radix sort are one allocation: outside the
     // sort its 2 N words serve as the hash table of the id check
     w.keys[1] = w.keys[0] + N;
-    // Some 60 pairs fall below the cheap bound of P for one that scatters, so
-    // that a cycle over long steps passes four candidates per event slot early,
-    // and the second pair pass costs more than the first (65536 particles, 0.9
-    // candidates each: 1.4 ms after 0.5): two per particle, 80 bytes each.
-    if (!realloc_events(w, max_events, why, 2 * N)) return false;
+    if (!realloc_events(w, max_events, why)) return false;
     // the counters, per-halo event counts, status words and tree term counts
     // read by the diagnostics start at zero (a context that has not stepped
     // yet reports no events and a clean status); the passes reset them later

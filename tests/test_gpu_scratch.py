@@ -32,3 +32,16 @@ def test_symmetric_tables(prec):
     print(f"{grown / n:.1f} B per particle", flush=True)
     # the totals, and 8 B for the work items and the granularity of allocations
     assert grown <= (32 + 8) * n
+
+
+def test_more_events_keep_the_candidates():
+    """Raising the event capacity does not lower the number of candidates (two
+    per particle of 80 bytes in a new context)."""
+    import paper_2506_06269_amd as S
+    n = 1 << 22
+    _free()   # torch's runtime first
+    ctx = S.sidm_create(0, n, 1)
+    before = _free()
+    S.sidm_set_event_capacity(ctx, n // 4)
+    assert _free() <= before
+    S.sidm_destroy(ctx)

@@ -1,6 +1,7 @@
 """CPU checks of launch sizes and buffer sizes (csrc/sidm_plan.hpp, compiled for
 the host with g++): kernels with a workgroup per halo are cut into launches
-that a grid can hold and that cover every halo once."""
+that a grid can hold and that cover every halo once; the room for candidates of
+the scattering decisions grows with the room for events."""
 import ctypes as C
 import os
 import subprocess
@@ -19,6 +20,8 @@ extern "C" int chunks(long long total, int threads, long long* first, long long*
     });
     return k;
 }
+extern "C" long long room(long long events, long long n) { return sidm::candidate_room(events, n); }
+extern "C" long long events0(long long n) { return sidm::default_events(n); }
 '''
 
 
@@ -48,3 +51,17 @@ def test_launches_fit_a_grid(L, total, threads):
         at += count[q]
     assert at == total
     assert k == 1 or total * threads > 1 << 31
+
+
+@pytest.mark.parametrize("n", [2, 1000, 32768, 65536, 1 << 20, 1 << 24])
+def test_candidate_room(L, n):
+    L.room.restype = L.events0.restype = C.c_longlong
+    L.room.argtypes = [C.c_longlong, C.c_longlong]
+    L.events0.argtypes = [C.c_longlong]
+    e0 = L.events0(n)
+    assert e0 == max(4096, n // 8)
+    events = sorted({1, 4, e0 // 2, e0 - 1, e0, e0 + 1, 2 * e0, 4 * n, 8 * n + 1})
+    room = [L.room(e, n) for e in events]
+    assert all(a <= b for a, b in zip(room, room[1:]))
+    for e, r in zip(events, room):
+        assert r == 4 * e if e < e0 else r == max(4 * e, 2 * n)
