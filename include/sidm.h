@@ -179,16 +179,17 @@ typedef struct {
  * Creates a context on HIP device `device` with scratch memory for up to
  * `max_particles` particles in total and `max_halos` halos per call, and room
  * for max(4096, max_particles / 8) scattering events per call and for
- * four times as many candidates, or two per particle if that is more (pairs
- * whose draw falls below the cheap bound of P and whose decision needs the
- * overlap integral; when they are more, a second pair pass decides them all,
- * with the same result).  Allocates
- * device memory (SIDM_ERR_NOMEM on failure).  *out is NULL on error. */
+ * four times as many candidates, or two per particle if that is more and
+ * takes at most an eighth of the device's free memory (pairs whose draw falls
+ * below the cheap bound of P and whose decision needs the overlap integral;
+ * when they are more, a second pair pass decides them all, with the same
+ * result).  Allocates device memory (SIDM_ERR_NOMEM on failure).  *out is NULL
+ * on error. */
 sidm_status sidm_create(sidm_ctx **out, int device, int64_t max_particles, int32_t max_halos);
 
 /* Sets the per-call event capacity, and the candidate capacity to four times
- * it; from the capacity of a new context on to at least two per particle, as
- * there (reallocates; call outside graph capture). */
+ * it; from the capacity of a new context on to at least two per particle, by
+ * the rule there (reallocates; call outside graph capture). */
 sidm_status sidm_set_event_capacity(sidm_ctx *ctx, int64_t max_events);
 
 /* Releases the context and its scratch memory (waits for the device). */

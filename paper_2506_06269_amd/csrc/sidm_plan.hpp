@@ -252,11 +252,16 @@ inline int64_t default_events(int64_t N) { return std::max<int64_t>(4096, N / 8)
 // times as often as below P, and N/8 slots hold about 50 times a step's events;
 // but a cycle over long steps passes four per slot early, and a second pair
 // pass then costs more than the first (65536 particles, 0.9 candidates each: 1.4
-// ms after 0.5).  An overflow only costs that pass.
-inline int64_t candidate_room(int64_t max_events, int64_t N)
+// ms after 0.5).  An overflow only costs that pass, so the second rule is left
+// out where it would take more than an eighth of the free device memory: a
+// context as large as the card holds, and the tables of its plan (up to 560 B per
+// particle with block steps), need it more (two candidates are 160 B, a
+// particle's other scratch is 270).
+inline int64_t candidate_room(int64_t max_events, int64_t N, int64_t free_bytes)
 {
-    const int64_t room = 4 * max_events;
-    return max_events < default_events(N) ? room : std::max<int64_t>(room, 2 * N);
+    const int64_t room = 4 * max_events, more = std::max<int64_t>(room, 2 * N);
+    if (max_events < default_events(N)) return room;
+    return (more - room) * (int64_t)sizeof(CandRec) <= free_bytes / 8 ? more : room;
 }
 
 inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why)
@@ -264,7 +269,9 @@ inline bool realloc_events(Scratch& w, int64_t max_events, std::string& why)
     dfree(w.events);
     dfree(w.cands);
     w.max_events = max_events;
-    w.max_cands = candidate_room(max_events, w.max_particles);
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) free_bytes = 0;
+    w.max_cands = candidate_room(max_events, w.max_particles, (int64_t)free_bytes);
     if (!dalloc(w.events, max_events) || !dalloc(w.cands, w.max_cands)) {
         why = "cannot allocate the event buffers";
         w.max_events = w.max_cands = 0;

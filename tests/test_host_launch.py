@@ -20,7 +20,10 @@ extern "C" int chunks(long long total, int threads, long long* first, long long*
     });
     return k;
 }
-extern "C" long long room(long long events, long long n) { return sidm::candidate_room(events, n); }
+extern "C" long long room(long long events, long long n, long long free_bytes) {
+    return sidm::candidate_room(events, n, free_bytes);
+}
+extern "C" int cand_bytes() { return (int)sizeof(sidm::CandRec); }
 extern "C" long long events0(long long n) { return sidm::default_events(n); }
 '''
 
@@ -56,12 +59,27 @@ def test_launches_fit_a_grid(L, total, threads):
 @pytest.mark.parametrize("n", [2, 1000, 32768, 65536, 1 << 20, 1 << 24])
 def test_candidate_room(L, n):
     L.room.restype = L.events0.restype = C.c_longlong
-    L.room.argtypes = [C.c_longlong, C.c_longlong]
+    L.room.argtypes = [C.c_longlong, C.c_longlong, C.c_longlong]
     L.events0.argtypes = [C.c_longlong]
     e0 = L.events0(n)
     assert e0 == max(4096, n // 8)
     events = sorted({1, 4, e0 // 2, e0 - 1, e0, e0 + 1, 2 * e0, 4 * n, 8 * n + 1})
-    room = [L.room(e, n) for e in events]
+    room = [L.room(e, n, 1 << 50) for e in events]
     assert all(a <= b for a, b in zip(room, room[1:]))
     for e, r in zip(events, room):
         assert r == 4 * e if e < e0 else r == max(4 * e, 2 * n)
+
+
+def test_candidate_room_where_memory_is_short(L):
+    """Two candidates per particle only where what they add to four per event
+    slot is at most an eighth of the free memory."""
+    L.room.restype = L.events0.restype = C.c_longlong
+    L.room.argtypes = [C.c_longlong, C.c_longlong, C.c_longlong]
+    L.events0.argtypes = [C.c_longlong]
+    n = 1 << 28
+    e0 = L.events0(n)
+    more = (2 * n - 4 * e0) * L.cand_bytes()
+    assert L.room(e0, n, 8 * more) == 2 * n
+    assert L.room(e0, n, 8 * more - 8) == 4 * e0
+    assert L.room(e0, n, 0) == 4 * e0
+    assert L.room(8 * n, n, 0) == 32 * n
