@@ -409,11 +409,14 @@ sidm_status sidm_set_launch_shape(sidm_ctx *ctx, int32_t ireg, int32_t threads,
  * each unordered pair once and applies it to both members; the reactions are
  * summed in fixed point (64 bits, FP64 128) with integer atomics, so the result
  * is deterministic: it does not depend on the order in which the work items
- * finish.  The results agree with the one-sided tiles to FP32 (FP64) rounding.
+ * finish.  The results agree with the one-sided tiles to FP32 (FP64) rounding,
+ * and to it depend on how the call's halos are cut into work items.
  * Halos need a softening eps > 0.  min_n = 0 turns them off; the default is
  * 4096.  Tree halos, the ticks of a cycle of block time steps (when some
  * direct-sum halo has max_bin > 0) and, in FP64, a halo with a value that is
- * not finite or whose box is over 2^20 eps use the one-sided sums.
+ * not finite or whose totals the fixed point cannot hold (n max|m| / sum|m| times
+ * the square of the box's side over eps above 2^40: with equal masses a side
+ * over 2^20 eps) use the one-sided sums.
  * Changing it invalidates graphs captured before.  SIDM_ERR_INVALID for
  * min_n < 0. */
 sidm_status sidm_set_symmetric(sidm_ctx *ctx, int64_t min_n);

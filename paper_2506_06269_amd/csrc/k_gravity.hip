@@ -796,18 +796,17 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
 // instructions and a v_rsq_f64 for both directions, where the one-sided tiles
 // take 16 and one for each; the sum of a j's reaction over the wave adds 63
 // instructions per four j, so more i-particles per thread are better.  Forces
-// of 524288 particles in 8 x 256: 100 ms (57 cycles per wave and interaction;
-// the instructions alone 53), 4 x 256 108 ms, one-sided 158 ms.  The atomics
-// take some 6 % (half of them taken out: 97 ms); they go up steeply with their
-// number (i-side sums flushed every 2048, 512 and 256 j: 26.2, 29.8 and 52 ms at
-// 262144), so those sums are kept in two levels, a tile's and a run's of
-// kSymRun64 tiles (one plain sum over 2048 j showed in the error against the
-// oracle).  The length of an item grows with N^2, to 8192 tiles at 2^24, and
-// the error of a plain sum with it (up to 2.4e-15 there); a run's stays that
-// of 32 tiles, where the error is that of the compensated one-sided sums
-// (5.1e-16 of the force at 262144; both are the terms').  Runs of 8, 16 and 32
-// tiles and whole items: 407, 401, 399 and 399 ms at 2^20.  Items cut finer for
-// halos of 16384 to 32768 were slower (the i-side flushes).
+// of 524288 particles in 8 x 256: 99 ms (57 cycles per wave and interaction; the
+// instructions alone 53), 4 x 256 106 ms, one-sided 151 ms.
+//
+// The i-side sums are kept in two levels, a tile's and a run's of kSymRun64
+// tiles: one plain sum over 2048 j showed in the error against the oracle, and
+// over an item, whose length grows with N^2 to 8192 tiles at 2^24, the error
+// would grow with it (to 2.4e-15 there).  A run's stays that of 32 tiles, where
+// the error is that of the compensated one-sided sums (5.1e-16 of the force at
+// 262144; both are the terms').  Runs of 1, 2, 8, 16 and 32 tiles and whole items
+// at 2^20: 437, 417, 399, 397, 396 and 396 ms.  Items cut finer for halos of 16384
+// to 32768 were slower (the i-side flushes).
 //
 // The totals are 128-bit fixed point in two words that never carry into each
 // other: x = v 2^s is cut into its nearest integer and the remainder times
@@ -816,7 +815,9 @@ __global__ __launch_bounds__(NT) void k_grav_fp64(
 // every partial sum (a single word of 64 bits would round them at 2^-61 of the
 // bound, 10^-10 of the force on a particle at a halo's edge).  The low words lie
 // in the first partial row of the halo, which the one-sided tiles leave alone
-// where the symmetric ones take the halo.
+// where the symmetric ones take the halo: no memory of their own, and an
+// atomic instruction of a wave touches 16 lines instead of the 32 of words side
+// by side (2^18 particles in 8 x 256 26.7 -> 25.6 ms, in 2 x 128 53.8 -> 33.0).
 constexpr double kSymLow = 0x1p44;
 constexpr int kSymRun64 = 32;
 

@@ -17,9 +17,9 @@
 // a usable h0, take the general search, with a private 32-bin histogram per
 // lane (an LDS column, written with LDS atomics that return nothing):
 //   1. a histogram of the distances within a starting radius: 1.15 times h0
-//      when it is usable, else an estimate out of the nearest members of the
-//      particle's compact sub-range; the radius grows until the sphere holds
-//      k others;
+//      when it is usable, else an estimate out of the nearest of the particles
+//      up to a bucket before and after in sorted order; the radius grows until
+//      the sphere holds k others;
 //   2. a visit restricted to the shell of the bin that holds the k-th
 //      collects that bin's members (at most 16, kept sorted in registers) or,
 //      if it holds more, records their min..max, whose histogram (step 1 over

@@ -41,13 +41,13 @@ constexpr int kNumShapes = 9;
 constexpr int kShapeIreg[kNumShapes] = {2, 4, 8, 2, 4, 8, 2, 4, 8};
 constexpr int kShapeNt[kNumShapes] = {128, 128, 128, 256, 256, 256, 512, 512, 512};
 
-// Symmetric tiles (the mixed direct sums of large halos, each unordered pair
-// evaluated once) run in the launch shape of the one-sided tiles; by default
+// Symmetric tiles (the direct sums of large halos, each unordered pair evaluated
+// once) run in the launch shape of the one-sided tiles; by default
 // halos of at least kSymMinN particles take them.
 constexpr int64_t kSymMinN = 4096;
-// The FP64 sums take them from kSymMinN64 particles on (4 x 256, symmetric and
-// one-sided: 0.42 and 0.30 ms at 16384, 0.84 and 0.81 at 32768, 2.1 and 2.8 at
-// 65536); no less than kSymMinN.
+// The FP64 sums take them from kSymMinN64 particles on (whole calls in 4 x 256,
+// symmetric and one-sided: 0.40 and 0.32 ms at 16384, 0.79 and 0.82 at 32768,
+// 0.98 and 1.27 at 40960, 2.0 and 2.8 at 65536); no less than kSymMinN.
 constexpr int64_t kSymMinN64 = 40960;
 constexpr int kSymMixed = 1, kSymFp64 = 2;   // HaloDev::grav_sym
 constexpr int kSymFold = 4;           // j-tiles per flush of the i-side sums

@@ -575,15 +575,17 @@ inline void choose_splits(std::vector<HaloDev>& hd, int64_t partial_rows, int64_
 
 // Symmetric tiles: marks the halos large enough for them (softened, direct
 // sum, at least sym_min_n particles; none for sym_min_n = 0; the FP64 sums from
-// kSymMinN64 on) and cuts their
-// work: each i-block of ireg * nt against the j from its own start to the
-// halo's end, in ranges of L, about 32 items per resident block over all such
-// halos, largest first.  L is a multiple of nt; below four i-blocks a multiple
-// of the tiles between two flushes of the i-side sums, and never less than
-// that (an item's fixed cost is a few per cent of such a range), so that where
-// a range is cut does not change the sums.  With at least four i-blocks per
-// range 65536 particles in 4 x 256 gave 544 items for 1024 resident blocks
-// (forces in 2.03 ms, now 1.36).
+// kSymMinN64 on) and cuts their work, in both precisions alike: each i-block of
+// ireg * nt against the j from its own start to the halo's end, in ranges of L,
+// about 32 items per resident block of the mixed tiles over all such halos,
+// largest first.  L is a multiple of nt; below four i-blocks a multiple of the
+// tiles between two flushes of the mixed i-side sums, and never less than that
+// (an item's fixed cost is a few per cent of such a range), so that there the
+// place of a cut does not change the mixed sums.  It does change the FP64 ones
+// (flushed at the end of an item) and, from four i-blocks on, the mixed ones:
+// to rounding, the forces of a large halo depend on what shares its call.  With
+// at least four i-blocks per range 65536 particles in 4 x 256 gave 544 items
+// for 1024 resident blocks (forces in 2.03 ms, now 1.36).
 inline void make_sym_items(std::vector<HaloDev>& halos, const GravShape& shape,
                            int64_t sym_min_n, int64_t sym_slots, std::vector<SymItem>& items)
 {
@@ -615,8 +617,8 @@ inline void make_sym_items(std::vector<HaloDev>& halos, const GravShape& shape,
 }
 
 // sym_min_n: direct-sum halos of at least that many particles take the
-// symmetric tiles in mixed precision (0: none); sym_slots: resident blocks of
-// those tiles, which sets how finely their j-ranges are cut.
+// symmetric tiles (0: none; FP64 see kSymMinN64); sym_slots: resident blocks of
+// the mixed ones, which sets how finely their j-ranges are cut.
 inline bool build_plan(Plan& P, const Scratch& w, const sidm_halo* halos, int32_t n_halos,
                        const GravShape& shape, int64_t slots, std::string& why,
                        int64_t sym_min_n = 0, int64_t sym_slots = 0)
