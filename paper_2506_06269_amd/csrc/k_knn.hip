@@ -26,7 +26,10 @@
 //      that range) refines the choice; equal values end the refinement.
 // Typical cost: one visit when warm; three for the general search.
 //
-// Bound by vector issue: about 75 cycles per candidate and wave (eight FP64
+// Bound by vector issue and the waits between (a warm call of 2^20: vector units
+// busy 51 % of the cycles, waves waiting 38 %; 200003 without previous sizes,
+// one round of waves of which the slowest last three times the mean: 27 and 41
+// %): about 75 cycles per candidate and wave (eight FP64
 // operations of four cycles, three comparisons, four LDS reads shared by four
 // candidates), most of the rest the tests that select them.  A call of 2^20
 // particles (k 64) takes 1.73 ms warm and 5.6 ms without previous sizes, the

@@ -15,12 +15,13 @@
 // Lambda for those and appends the events (u < P) to the event buffer (when the
 // candidate buffer is full, the pair pass decides the rest itself).
 //
-// What bounds it: half of the time is per-pair work, a chain of LDS reads,
-// gathered velocities and ten dependent rounds of the generator at three waves
-// per SIMD (145 registers), so each lane takes two pairs at once (64 halos: 5.4
-// -> 4.9 ms; four waves with fewer registers: 6.0); a quarter is the search,
-// a quarter the screen and the queue.  One in six screened pairs is accepted; in
-// double precision on the vector unit they took half of the pass.
+// What bounds it: vector issue (N = 500009: busy 69 % of the cycles, waves
+// waiting 30 %; 2^20 74 %).  Half of the time is per-pair work, a chain of LDS
+// reads, gathered velocities and ten dependent rounds of the generator at three
+// waves per SIMD (145 registers), so each lane takes two pairs at once (64
+// halos: 5.4 -> 4.9 ms; four waves with fewer registers: 6.0); a quarter is the
+// search, a quarter the screen and the queue.  One in six screened pairs is
+// accepted; in double precision on the vector unit they took half of the pass.
 //            N = 500009 (126 M pairs)   2^20 (265 M)   64 halos (571 M)   8192
 //   bucket after bucket, chunk boxes   2.10 ms   3.7   7.4   0.110
 //   candidates a lane each             1.42      2.65  5.9   0.074
