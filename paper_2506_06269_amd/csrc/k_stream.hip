@@ -453,11 +453,20 @@ __global__ __launch_bounds__(kStreamBlock) void k_tidal_init(
 // launches of a mass pass and 60 of a one-workgroup sum and decision, 6 and 11
 // us each at 2^20 particles, became 13 of 15 us (a chain of loads, square roots
 // and fields; the sums themselves take 3).
+//
+// That chain is every workgroup's, and a compute unit holds one workgroup of
+// 512 threads (168 registers), so a call takes about one workgroup per compute
+// unit, dealt out to the halos by their sizes: with up to 256 for each of them 40
+// halos of 50000 took 3.27 ms (1.10 with the 120 launches), now 0.31.  Beyond
+// kTidalFew halos, all of them small, a wave per halo is enough and a compute
+// unit holds twelve: 20000 halos of 70 take 1.45 ms (9.53 in workgroups of 512,
+// 3.42 with the 120 launches).
 constexpr int kTidalLevels = 5;
 constexpr int kTidalSums = 1 << kTidalLevels;   // 31 nodes (entry q - 1) and the upper bracket
 constexpr int kTidalSteps = 60;
-constexpr int kTidalThreads = 512;
-constexpr int kTidalBlocks = 256;               // workgroups per halo at most
+constexpr int kTidalBlocks = 256;               // workgroups of 512 threads in all, about
+constexpr int kTidalFew = 256;                  // more halos than this, of at most
+constexpr int64_t kTidalWaveN = 4096;           // this many particles: a wave per halo
 static_assert(kTidalSteps % kTidalLevels == 0, "whole launches");
 
 struct Bracket {
@@ -515,39 +524,43 @@ __device__ inline bool tidal_inside(const HaloDev& H, const double (*field)[64][
     return H.G * M / (r * r) > tide;
 }
 
-// Workgroups of a halo's passes.
-__device__ inline int tidal_groups(const HaloDev& H)
+// Workgroups of the passes over a halo of n of the call's n_total particles, at
+// most `most` in all and at least one: its share, no more than its streaming
+// blocks.
+__host__ __device__ inline int tidal_groups(int64_t n, int64_t n_total, int most)
 {
-    const int64_t nb = (H.n + kStreamBlock - 1) / kStreamBlock;
-    return (int)(nb < kTidalBlocks ? nb : kTidalBlocks);
+    const int64_t nb = (n + kStreamBlock - 1) / kStreamBlock, share = n * most / n_total;
+    return (int)(share < 1 ? 1 : share < nb ? share : nb);
 }
 
 // Workgroup w0 + blockIdx.x: per_halo of them for each halo (those past its own
 // leave), or with `blocks` one for each streaming block (of which a halo keeps
 // the first ones).  tid_in / tid_out: the state before and after the
 // decisions on sums_in (none in the first launch); sums_out: this launch's sums
-// (kTidalSums per workgroup).  The last launch writes the record instead.
-__global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
+// (kTidalSums per workgroup).  The last launch writes the record instead.  NT
+// threads, at most MOST workgroups per halo.
+template <int NT, int MOST>
+__global__ __launch_bounds__(NT) void k_tidal_pass(
     const HaloDev* __restrict__ halos, const StreamBlock* __restrict__ blocks, int64_t w0,
     const double* __restrict__ x, const double* __restrict__ y,
     const double* __restrict__ z, const double* __restrict__ m,
     const sidm_center* __restrict__ cen, const double* __restrict__ tid_in,
     double* __restrict__ tid_out, const double* __restrict__ sums_in,
-    double* __restrict__ sums_out, int per_halo, int first, int last,
+    double* __restrict__ sums_out, int per_halo, int64_t n_total, int first, int last,
     sidm_tidal* __restrict__ out)
 {
-    constexpr int NW = kTidalThreads / 64, NG = kTidalThreads / kTidalSums;
+    constexpr int NW = NT / 64, NG = NT / kTidalSums;
     __shared__ double red[NG][kTidalSums];
     __shared__ double rad2[kTidalSums];
     __shared__ int inside[kTidalSums];
     __shared__ double field[kHostParts][64][3];
-    static_assert(kHostParts <= NW && 2 * kTidalSums == 64, "a wave per component, a lane per side");
+    static_assert(2 * kTidalSums == 64, "a lane per side");
     const int t = threadIdx.x;
     const int64_t wg = w0 + blockIdx.x;
     const int h = blocks ? blocks[wg].halo : (int)(wg / per_halo);
     const HaloDev& H = halos[h];
     const int64_t g = blocks ? wg - H.stream_block0 : wg % per_halo;
-    const int groups = tidal_groups(H);
+    const int groups = tidal_groups(H.n, n_total, MOST);
     if (g >= (last ? 1 : groups)) return;
     const sidm_center C = cen[h];
     double T[8];
@@ -557,7 +570,7 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
     if (!first) {
         // the sums of the previous pass, in workgroup order
         const int c = t % kTidalSums, part = t / kTidalSums;
-        constexpr int kRows = kTidalBlocks / NG;
+        constexpr int kRows = (MOST + NG - 1) / NG;
         double w[kRows], v = 0.0;
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
@@ -567,7 +580,7 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
 #pragma unroll
         for (int u = 0; u < kRows; ++u) v += w[u];
         red[part][c] = v;
-        if (t / 64 < kHostParts) tidal_part(H, C, T, b, t / 64, t & 63, field);
+        for (int k = t / 64; k < kHostParts; k += NW) tidal_part(H, C, T, b, k, t & 63, field);
         __syncthreads();
         if (t < kTidalSums) {
             double M = 0.0;
@@ -629,8 +642,8 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
     if (C.index >= 0) {
         // four particles' loads in flight
         constexpr int kLoads = 4;
-        const int64_t step = (int64_t)groups * kTidalThreads;
-        for (int64_t i = g * kTidalThreads + t; i < H.n; i += kLoads * step) {
+        const int64_t step = (int64_t)groups * NT;
+        for (int64_t i = g * NT + t; i < H.n; i += kLoads * step) {
 #pragma clang fp contract(off)
             double d2[kLoads], mp[kLoads];
 #pragma unroll
@@ -671,8 +684,8 @@ __global__ __launch_bounds__(kTidalThreads) void k_tidal_pass(
 }
 
 hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const HaloDev* d_halos,
-                        int n_halos, int64_t n_max, const double* x, const double* y, const double* z,
-                        const double* m, const double* pot, double* bsum, sidm_center* cen,
+                        int n_halos, int64_t n_max, int64_t n_total, const double* x,
+                        const double* y, const double* z, const double* m, const double* pot, double* bsum, sidm_center* cen,
                         double* tid, double* sums, sidm_tidal* out, hipStream_t st)
 {
     hipLaunchKernelGGL(k_center_block, dim3((unsigned)n_blocks), dim3(kStreamBlock), 0, st,
@@ -686,24 +699,28 @@ hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const Hal
     constexpr int kPasses = kTidalSteps / kTidalLevels;
     double* state[2] = {tid, tid + 8 * (int64_t)n_halos};
     double* sum[2] = {sums, sums + n_blocks * kTidalSums};
-    const int64_t nb = (n_max + kStreamBlock - 1) / kStreamBlock;
-    const int groups = (int)(nb < kTidalBlocks ? nb : kTidalBlocks);
-    // many halos, the largest much larger than the others: a workgroup per
-    // streaming block instead of the largest halo's number for each
-    const bool by_block = (int64_t)groups * n_halos > 65536 && n_blocks < (int64_t)groups * n_halos;
-    for (int it = 0; it <= kPasses; ++it) {
-        const bool last = it == kPasses;
-        const int per_halo = last ? 1 : groups;
-        const bool blk = by_block && !last;
-        launch_chunks(blk ? n_blocks : (int64_t)per_halo * n_halos, kTidalThreads,
-                      [&](int64_t w0, int64_t count) {
-                          hipLaunchKernelGGL(
-                              k_tidal_pass, dim3((unsigned)count), dim3(kTidalThreads), 0, st,
-                              d_halos, blk ? d_blocks : (const StreamBlock*)nullptr, w0, x, y, z,
-                              m, cen, state[it & 1], state[(it & 1) ^ 1], sum[(it & 1) ^ 1],
-                              sum[it & 1], per_halo, it == 0, last, out);
-                      });
-    }
+    const bool waves = n_halos > kTidalFew && n_max <= kTidalWaveN;
+    const int groups = waves ? 1 : tidal_groups(n_max, n_total, kTidalBlocks);
+    // one halo much larger than the others: a workgroup per streaming block
+    // instead of the largest halo's number for each
+    const bool by_block = n_blocks < (int64_t)groups * n_halos;
+    auto passes = [&](auto kern, int threads) {
+        for (int it = 0; it <= kPasses; ++it) {
+            const bool last = it == kPasses;
+            const int per_halo = last ? 1 : groups;
+            const StreamBlock* blk = by_block && !last ? d_blocks : nullptr;
+            launch_chunks(blk ? n_blocks : (int64_t)per_halo * n_halos, threads,
+                          [&](int64_t w0, int64_t count) {
+                              hipLaunchKernelGGL(kern, dim3((unsigned)count), dim3(threads), 0, st,
+                                                 d_halos, blk, w0, x, y, z, m, cen, state[it & 1],
+                                                 state[(it & 1) ^ 1], sum[(it & 1) ^ 1],
+                                                 sum[it & 1], per_halo, n_total, it == 0, last,
+                                                 out);
+                          });
+        }
+    };
+    if (waves) passes(k_tidal_pass<64, 1>, 64);
+    else passes(k_tidal_pass<512, kTidalBlocks>, 512);
     return hipGetLastError();
 }
 
