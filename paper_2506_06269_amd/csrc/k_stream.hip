@@ -456,7 +456,8 @@ __global__ __launch_bounds__(kStreamBlock) void k_tidal_init(
 //
 // That chain is every workgroup's, and a compute unit holds one workgroup of
 // 512 threads (168 registers), so a call takes about one workgroup per compute
-// unit, dealt out to the halos by their sizes: with up to 256 for each of them 40
+// unit, dealt out to the halos by their sizes in the plan (HaloDev::tidal_wg;
+// a division here would add 0.4 us to each pass): with up to 256 for each of them 40
 // halos of 50000 took 3.27 ms (1.10 with the 120 launches), now 0.31.  Beyond
 // kTidalFew halos, all of them small, a wave per halo is enough and a compute
 // unit holds twelve: 20000 halos of 70 take 1.45 ms (9.53 in workgroups of 512,
@@ -464,7 +465,6 @@ __global__ __launch_bounds__(kStreamBlock) void k_tidal_init(
 constexpr int kTidalLevels = 5;
 constexpr int kTidalSums = 1 << kTidalLevels;   // 31 nodes (entry q - 1) and the upper bracket
 constexpr int kTidalSteps = 60;
-constexpr int kTidalBlocks = 256;               // workgroups of 512 threads in all, about
 constexpr int kTidalFew = 256;                  // more halos than this, of at most
 constexpr int64_t kTidalWaveN = 4096;           // this many particles: a wave per halo
 static_assert(kTidalSteps % kTidalLevels == 0, "whole launches");
@@ -524,15 +524,6 @@ __device__ inline bool tidal_inside(const HaloDev& H, const double (*field)[64][
     return H.G * M / (r * r) > tide;
 }
 
-// Workgroups of the passes over a halo of n of the call's n_total particles, at
-// most `most` in all and at least one: its share, no more than its streaming
-// blocks.
-__host__ __device__ inline int tidal_groups(int64_t n, int64_t n_total, int most)
-{
-    const int64_t nb = (n + kStreamBlock - 1) / kStreamBlock, share = n * most / n_total;
-    return (int)(share < 1 ? 1 : share < nb ? share : nb);
-}
-
 // Workgroup w0 + blockIdx.x: per_halo of them for each halo (those past its own
 // leave), or with `blocks` one for each streaming block (of which a halo keeps
 // the first ones).  tid_in / tid_out: the state before and after the
@@ -546,7 +537,7 @@ __global__ __launch_bounds__(NT) void k_tidal_pass(
     const double* __restrict__ z, const double* __restrict__ m,
     const sidm_center* __restrict__ cen, const double* __restrict__ tid_in,
     double* __restrict__ tid_out, const double* __restrict__ sums_in,
-    double* __restrict__ sums_out, int per_halo, int64_t n_total, int first, int last,
+    double* __restrict__ sums_out, int per_halo, int first, int last,
     sidm_tidal* __restrict__ out)
 {
     constexpr int NW = NT / 64, NG = NT / kTidalSums;
@@ -557,10 +548,11 @@ __global__ __launch_bounds__(NT) void k_tidal_pass(
     static_assert(2 * kTidalSums == 64, "a lane per side");
     const int t = threadIdx.x;
     const int64_t wg = w0 + blockIdx.x;
-    const int h = blocks ? blocks[wg].halo : (int)(wg / per_halo);
+    // (without blocks there are fewer workgroups than streaming blocks or halos)
+    const int h = blocks ? blocks[wg].halo : (int)((uint32_t)wg / (uint32_t)per_halo);
     const HaloDev& H = halos[h];
-    const int64_t g = blocks ? wg - H.stream_block0 : wg % per_halo;
-    const int groups = tidal_groups(H.n, n_total, MOST);
+    const int64_t g = blocks ? wg - H.stream_block0 : (uint32_t)wg % (uint32_t)per_halo;
+    const int groups = MOST == 1 ? 1 : H.tidal_wg;
     if (g >= (last ? 1 : groups)) return;
     const sidm_center C = cen[h];
     double T[8];
@@ -580,7 +572,11 @@ __global__ __launch_bounds__(NT) void k_tidal_pass(
 #pragma unroll
         for (int u = 0; u < kRows; ++u) v += w[u];
         red[part][c] = v;
-        for (int k = t / 64; k < kHostParts; k += NW) tidal_part(H, C, T, b, k, t & 63, field);
+        if (NW >= kHostParts) {
+            if (t / 64 < kHostParts) tidal_part(H, C, T, b, t / 64, t & 63, field);
+        } else {
+            for (int k = t / 64; k < kHostParts; k += NW) tidal_part(H, C, T, b, k, t & 63, field);
+        }
         __syncthreads();
         if (t < kTidalSums) {
             double M = 0.0;
@@ -684,7 +680,7 @@ __global__ __launch_bounds__(NT) void k_tidal_pass(
 }
 
 hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const HaloDev* d_halos,
-                        int n_halos, int64_t n_max, int64_t n_total, const double* x,
+                        int n_halos, int64_t n_max, int wg_max, const double* x,
                         const double* y, const double* z, const double* m, const double* pot, double* bsum, sidm_center* cen,
                         double* tid, double* sums, sidm_tidal* out, hipStream_t st)
 {
@@ -700,7 +696,7 @@ hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const Hal
     double* state[2] = {tid, tid + 8 * (int64_t)n_halos};
     double* sum[2] = {sums, sums + n_blocks * kTidalSums};
     const bool waves = n_halos > kTidalFew && n_max <= kTidalWaveN;
-    const int groups = waves ? 1 : tidal_groups(n_max, n_total, kTidalBlocks);
+    const int groups = waves ? 1 : wg_max;
     // one halo much larger than the others: a workgroup per streaming block
     // instead of the largest halo's number for each
     const bool by_block = n_blocks < (int64_t)groups * n_halos;
@@ -714,13 +710,12 @@ hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const Hal
                               hipLaunchKernelGGL(kern, dim3((unsigned)count), dim3(threads), 0, st,
                                                  d_halos, blk, w0, x, y, z, m, cen, state[it & 1],
                                                  state[(it & 1) ^ 1], sum[(it & 1) ^ 1],
-                                                 sum[it & 1], per_halo, n_total, it == 0, last,
-                                                 out);
+                                                 sum[it & 1], per_halo, it == 0, last, out);
                           });
         }
     };
     if (waves) passes(k_tidal_pass<64, 1>, 64);
-    else passes(k_tidal_pass<512, kTidalBlocks>, 512);
+    else passes(k_tidal_pass<512, kTidalWg>, 512);
     return hipGetLastError();
 }
 

@@ -33,7 +33,7 @@ hipError_t launch_center(const StreamBlock* d_blocks, int64_t n_blocks, const Ha
                          const double* z, const double* m, const double* pot, double* bsum,
                          sidm_center* out, hipStream_t st);
 hipError_t launch_tidal(const StreamBlock* d_blocks, int64_t n_blocks, const HaloDev* d_halos,
-                        int n_halos, int64_t n_max, int64_t n_total, const double* x,
+                        int n_halos, int64_t n_max, int wg_max, const double* x,
                         const double* y, const double* z, const double* m, const double* pot, double* bsum, sidm_center* cen,
                         double* tid, double* sums, sidm_tidal* out, hipStream_t st);
 }  // namespace sidm
@@ -697,7 +697,7 @@ sidm_status sidm_tidal_radius(sidm_ctx* c, const sidm_halo* halos, int32_t n_hal
     if ((r = enter(c, halos, n_halos, s, st, cap)) != SIDM_OK) return r;
     if ((r = guard(c, st, cap)) != SIDM_OK) return r;
     const Plan& P = c->plan;
-    hipError_t e = launch_tidal(c->w.blocks, P.n_blocks, c->w.halos, n_halos, P.n_max, P.n_sorted,
+    hipError_t e = launch_tidal(c->w.blocks, P.n_blocks, c->w.halos, n_halos, P.n_max, P.tidal_wg_max,
                                 s->x, s->y, s->z, s->m, s->pot, c->w.bsum, c->w.center, c->w.tidal, c->w.tidal_sums,
                                 out, st);
     if (e != hipSuccess) return hip_fail(c, e, "tidal radius launch");

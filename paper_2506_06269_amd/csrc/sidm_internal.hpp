@@ -25,6 +25,7 @@ constexpr int kSortMaxPasses = 8;    // 64-bit keys
 constexpr int kExtrema = 9;          // min x, y, z, m, max x, y, z, m, whether any is not finite
 constexpr int kRange = kExtrema + 1; // and the sum of |m|
 constexpr int64_t kSmallN = 8192;    // halos up to this size are sorted by one workgroup
+constexpr int kTidalWg = 256;        // workgroups of a pass of the tidal radius, about
 
 // Shape of the direct-sum gravity launch: i-particles per thread, threads per
 // block (also the j-particles of one LDS tile), and whether the blocks are
@@ -79,7 +80,7 @@ struct HaloDev {
     int64_t sbase;                        // first position in the sorted (compact) order
     int32_t rank;                         // halo rank by offset (high bits of the sort key)
     int32_t grav_sym;                     // kSym* bits: direct sums run the symmetric tiles
-    int32_t pad;
+    int32_t tidal_wg;                     // workgroups of a pass of the tidal radius
 };
 
 // A block of the streaming kernels never spans two halos.

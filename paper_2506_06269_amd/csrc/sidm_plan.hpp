@@ -167,6 +167,7 @@ struct Plan {
     GravShape shape;                  // launch shape of the direct-sum tiles
     int halo_bits = 0;                // bits of a halo index
     int64_t n_max = 0;                // particles of the largest halo
+    int32_t tidal_wg_max = 1;         // largest HaloDev::tidal_wg
     std::vector<HaloDev> halos;
     std::vector<StreamBlock> blocks;
     std::vector<GravItem> items;          // one-sided: the halos without symmetric tiles first
@@ -616,6 +617,15 @@ inline void make_sym_items(std::vector<HaloDev>& halos, const GravShape& shape,
     });
 }
 
+// Workgroups of a pass of the tidal radius over a halo of n of the call's n_total
+// particles: its share of kTidalWg, at least one and no more than its streaming
+// blocks.
+inline int32_t tidal_workgroups(int64_t n, int64_t n_total)
+{
+    const int64_t nb = (n + kStreamBlock - 1) / kStreamBlock;
+    return (int32_t)std::max<int64_t>(1, std::min(nb, n * kTidalWg / n_total));
+}
+
 // sym_min_n: direct-sum halos of at least that many particles take the
 // symmetric tiles (0: none; FP64 see kSymMinN64); sym_slots: resident blocks of
 // the mixed ones, which sets how finely their j-ranges are cut.
@@ -651,6 +661,8 @@ inline bool build_plan(Plan& P, const Scratch& w, const sidm_halo* halos, int32_
         H.sbase = sbase[h];
         H.rank = P.rank_of[h];
         P.n_max = std::max(P.n_max, H.n);
+        H.tidal_wg = tidal_workgroups(H.n, P.n_sorted);
+        P.tidal_wg_max = std::max(P.tidal_wg_max, H.tidal_wg);
         // streaming blocks
         H.stream_block0 = (int64_t)P.blocks.size();
         for (int64_t s0 = 0; s0 < S.n; s0 += kStreamBlock)

@@ -1,7 +1,8 @@
 """CPU checks of launch sizes and buffer sizes (csrc/sidm_plan.hpp, compiled for
 the host with g++): kernels with a workgroup per halo are cut into launches
 that a grid can hold and that cover every halo once; the room for candidates of
-the scattering decisions grows with the room for events."""
+the scattering decisions grows with the room for events; the workgroups of a
+tidal-radius pass are shared out by the halos' sizes."""
 import ctypes as C
 import os
 import subprocess
@@ -23,6 +24,7 @@ extern "C" int chunks(long long total, int threads, long long* first, long long*
 extern "C" long long room(long long events, long long n, long long free_bytes) {
     return sidm::candidate_room(events, n, free_bytes);
 }
+extern "C" int tidal_wg(long long n, long long total) { return sidm::tidal_workgroups(n, total); }
 extern "C" int cand_bytes() { return (int)sizeof(sidm::CandRec); }
 extern "C" long long events0(long long n) { return sidm::default_events(n); }
 '''
@@ -83,3 +85,14 @@ def test_candidate_room_where_memory_is_short(L):
     assert L.room(e0, n, 8 * more - 8) == 4 * e0
     assert L.room(e0, n, 0) == 4 * e0
     assert L.room(8 * n, n, 0) == 32 * n
+
+
+@pytest.mark.parametrize("sizes", [[2], [255], [257], [65536], [1 << 24], [50000] * 40, [300] * 7,
+                                   [1 << 24] * 3, [100000] + [300] * 500, [1 << 12, 1 << 17] * 32])
+def test_tidal_workgroups(L, sizes):
+    L.tidal_wg.argtypes = [C.c_longlong, C.c_longlong]
+    wg = [L.tidal_wg(n, sum(sizes)) for n in sizes]
+    assert all(1 <= w <= -(-n // 256) for w, n in zip(wg, sizes))
+    assert sum(w for w in wg if w > 1) <= 256
+    if len(sizes) == 1:
+        assert wg[0] == min(256, -(-sizes[0] // 256))
